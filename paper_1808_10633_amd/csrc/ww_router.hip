@@ -283,8 +283,7 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const float *__restrict_
 }
 
 // Gradient of the mean binary cross-entropy over n samples, 128 samples per
-// block (two waves of 64), every product on MFMA (BF16 operands, FP32
-// accumulation):
+// block, every product on MFMA (BF16 operands, FP32 accumulation):
 //   forward   Z1^T = W1 X^T, Z2^T = W2 H1^T (as in inference), logit in FP32;
 //   deltas    g = (sigmoid(logit) - t) / n, D2 = w3 g [z2 > 0] (per sample),
 //             D1^T = W2^T D2^T, masked by [z1 > 0]: the C-layout registers of
@@ -300,34 +299,55 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const float *__restrict_
 // D2 and the masked D1 are rounded to BF16; z1, z2, H2, the logit, g and every
 // sum are FP32.  part[b][0..NPARAM-1] = the block's gradient sums,
 // part[b][NPARAM] = its loss sum.
+// A training batch (4096 samples) is 32 blocks: the kernel is bound by the
+// latency of one block, so a block runs as GW = 8 waves of 16 samples each
+// and its 14 weight-gradient tiles are spread over the waves.  The block's
+// features are read four at a time where X is 16-byte aligned.
 constexpr int TS = 136;          // LDS row stride (BF16 elements) of the sample-contiguous copies
+constexpr int GW = 8, GT = 64 * GW;
 
-__global__ __launch_bounds__(128) void mlp_grad_kernel(const float *__restrict__ th,
-                                                       const float *__restrict__ X,
-                                                       const float *__restrict__ t, int n,
-                                                       float invn, float *__restrict__ part)
+__global__ __launch_bounds__(GT) void mlp_grad_kernel(const float *__restrict__ th,
+                                                      const float *__restrict__ X,
+                                                      const float *__restrict__ t, int n,
+                                                      float invn, float *__restrict__ part)
 {
     __shared__ short xs[128 * XS];       // [sample][feature]: forward B operand
     __shared__ short xT[64 * TS];        // [feature | ones | zeros][sample]
     __shared__ short h1T[48 * TS];       // [hidden 1 | ones | zeros][sample]
     __shared__ short d1T[32 * TS], d2T[32 * TS];
-    __shared__ float red[2][NH + 2];
+    __shared__ float red[GW][NH + 2];
     const int tid = threadIdx.x;
     const long base = (long)blockIdx.x * 128;
-    for (int e = tid; e < 128 * NIN; e += 128) {
-        const int m = e / NIN, k = e - m * NIN;
-        const long g = base + m;
-        const short v = g < n ? f2bf(X[g * NIN + k]) : (short)0;
-        xs[m * XS + k] = v;
-        xT[k * TS + m] = v;
+    if (((uintptr_t)X & 15) == 0) {
+        constexpr int NV = NIN / 4;
+#pragma unroll
+        for (int e = tid; e < 128 * NV; e += GT) {
+            const int m = e / NV, k = 4 * (e - m * NV);
+            f4 x = { 0.f, 0.f, 0.f, 0.f };
+            if (base + m < n) x = *(const f4 *)(X + (base + m) * NIN + k);
+            bf4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = f2bf(x[i]);
+                xT[(k + i) * TS + m] = v[i];
+            }
+            *(bf4 *)(xs + m * XS + k) = v;
+        }
+    } else {
+        for (int e = tid; e < 128 * NIN; e += GT) {
+            const int m = e / NIN, k = e - m * NIN;
+            const long g = base + m;
+            const short v = g < n ? f2bf(X[g * NIN + k]) : (short)0;
+            xs[m * XS + k] = v;
+            xT[k * TS + m] = v;
+        }
     }
     const short one = f2bf(1.0f);
-    for (int e = tid; e < 16 * 128; e += 128) {
+    for (int e = tid; e < 16 * 128; e += GT) {
         const int rr = e >> 7, m = e & 127;
         xT[(NIN + rr) * TS + m] = rr == 0 ? one : (short)0;
         h1T[(NH + rr) * TS + m] = rr == 0 ? one : (short)0;
     }
-    __syncthreads();
     MlpRegs R;
     load_mlp(th, R);
     const int w = tid >> 6, l = tid & 63, r = l & 15, q = l >> 4;
@@ -339,77 +359,71 @@ __global__ __launch_bounds__(128) void mlp_grad_kernel(const float *__restrict__
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) a2t[jt][kt][i] = f2bf(th[OW2 + (16 * kt + 4 * q + i) * NH + 16 * jt + r]);
-    float gw3[2][4] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
-    float gb3 = 0.f, gl = 0.f;
+    const int col = 16 * w + r;                        // this lane's sample within the block
+    const long gi = base + col;
+    const float tt = gi < n ? t[gi] : 0.f;
+    __syncthreads();
+    f4 z1[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        const int col = 64 * w + 16 * st + r;          // this lane's sample within the block
-        const short *gx = xs + (64 * w + 16 * st) * XS;
-        f4 z1[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
+    for (int kt = 0; kt < 3; ++kt) {
+        const bf4 bx = *(const bf4 *)(xs + col * XS + 16 * kt + 4 * q);
 #pragma unroll
-        for (int kt = 0; kt < 3; ++kt) {
-            const bf4 bx = *(const bf4 *)(gx + r * XS + 16 * kt + 4 * q);
+        for (int ot = 0; ot < 2; ++ot)
+            z1[ot] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.a1[ot][kt], bx, z1[ot], 0, 0, 0);
+    }
+    bf4 h1[2];
 #pragma unroll
-            for (int ot = 0; ot < 2; ++ot)
-                z1[ot] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.a1[ot][kt], bx, z1[ot], 0, 0, 0);
+    for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            z1[ot][i] += R.b1[ot][i];
+            h1[ot][i] = f2bf(fmaxf(z1[ot][i], 0.f));
+            h1T[(16 * ot + 4 * q + i) * TS + col] = h1[ot][i];
         }
-        bf4 h1[2];
+    f4 z2[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int ot = 0; ot < 2; ++ot)
+            z2[ot] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.a2[ot][kt], h1[kt], z2[ot], 0, 0, 0);
+    float zl = 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                z1[ot][i] += R.b1[ot][i];
-                h1[ot][i] = f2bf(fmaxf(z1[ot][i], 0.f));
-                h1T[(16 * ot + 4 * q + i) * TS + col] = h1[ot][i];
-            }
-        f4 z2[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
+    for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int ot = 0; ot < 2; ++ot)
-                z2[ot] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.a2[ot][kt], h1[kt], z2[ot], 0, 0, 0);
-        float zl = 0.f;
-#pragma unroll
-        for (int ot = 0; ot < 2; ++ot)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                z2[ot][i] += R.b2[ot][i];
-                zl += R.w3[ot][i] * fmaxf(z2[ot][i], 0.f);
-            }
-        zl += __shfl_xor(zl, 16);
-        zl += __shfl_xor(zl, 32);
-        const float z = zl + R.b3;                     // logit of sample `col` (every q)
-        const long gi = base + col;
-        float g = 0.f, lo = 0.f;
-        if (gi < n) {
-            const float tt = t[gi];
-            g = (1.0f / (1.0f + expf(-z)) - tt) * invn;
-            lo = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - tt * z;
+        for (int i = 0; i < 4; ++i) {
+            z2[ot][i] += R.b2[ot][i];
+            zl += R.w3[ot][i] * fmaxf(z2[ot][i], 0.f);
         }
-        if (q == 0) { gb3 += g; gl += lo; }
-        bf4 d2[2];
+    zl += __shfl_xor(zl, 16);
+    zl += __shfl_xor(zl, 32);
+    const float z = zl + R.b3;                         // logit of sample `col` (every q)
+    float g = 0.f, lo = 0.f;
+    if (gi < n) {
+        g = (1.0f / (1.0f + expf(-z)) - tt) * invn;
+        lo = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - tt * z;
+    }
+    float gw3[2][4], gb3 = q == 0 ? g : 0.f, gl = q == 0 ? lo : 0.f;
+    bf4 d2[2];
 #pragma unroll
-        for (int ot = 0; ot < 2; ++ot)
+    for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float h2 = fmaxf(z2[ot][i], 0.f);
-                gw3[ot][i] += g * h2;
-                d2[ot][i] = f2bf(z2[ot][i] > 0.f ? R.w3[ot][i] * g : 0.f);
-                d2T[(16 * ot + 4 * q + i) * TS + col] = d2[ot][i];
-            }
-        f4 d1[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
+        for (int i = 0; i < 4; ++i) {
+            gw3[ot][i] = g * fmaxf(z2[ot][i], 0.f);
+            d2[ot][i] = f2bf(z2[ot][i] > 0.f ? R.w3[ot][i] * g : 0.f);
+            d2T[(16 * ot + 4 * q + i) * TS + col] = d2[ot][i];
+        }
+    f4 d1[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int jt = 0; jt < 2; ++jt)
-                d1[jt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a2t[jt][kt], d2[kt], d1[jt], 0, 0, 0);
+    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int jt = 0; jt < 2; ++jt)
+            d1[jt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a2t[jt][kt], d2[kt], d1[jt], 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                d1T[(16 * jt + 4 * q + i) * TS + col] = f2bf(z1[jt][i] > 0.f ? d1[jt][i] : 0.f);
-    }
-    // dw3, db3 and the loss: sums over the 16 lanes of a row group, then the two waves
+    for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            d1T[(16 * jt + 4 * q + i) * TS + col] = f2bf(z1[jt][i] > 0.f ? d1[jt][i] : 0.f);
+    // dw3, db3 and the loss: sums over the 16 lanes of a row group, then the waves
 #pragma unroll
     for (int m = 1; m < 16; m <<= 1) {
 #pragma unroll
@@ -428,57 +442,69 @@ __global__ __launch_bounds__(128) void mlp_grad_kernel(const float *__restrict__
     }
     __syncthreads();
     float *pb = part + (long)blockIdx.x * (NPARAM + 1);
-    if (tid < NH) pb[OW3 + tid] = red[0][tid] + red[1][tid];
-    if (tid == NH) pb[OB3] = red[0][NH] + red[1][NH];
-    if (tid == NH + 1) pb[NPARAM] = red[0][NH + 1] + red[1][NH + 1];
-    // weight gradients over the 128 samples: wave w takes output rows 16w..16w+15
-    f4 g1[4] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f },
-                 { 0.f, 0.f, 0.f, 0.f } };
-    f4 g2[3] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
+    if (tid < NH + 2) {
+        float sum = red[0][tid];
+#pragma unroll
+        for (int i = 1; i < GW; ++i) sum += red[i][tid];
+        pb[tid < NH ? OW3 + tid : tid == NH ? OB3 : NPARAM] = sum;
+    }
+    // weight gradients over the 128 samples, 16x16 tiles: wave w takes tile
+    // (w & 1, w >> 1) of dW1 | db1 (2 x 4 tiles) and, for w < 6, tile
+    // (w & 1, w >> 1) of dW2 | db2 (2 x 3 tiles)
+    const int oh = w & 1, nt = w >> 1;
+    f4 g1 = { 0.f, 0.f, 0.f, 0.f }, g2 = { 0.f, 0.f, 0.f, 0.f };
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
         const int s0 = 16 * ks + 4 * q;
-        const bf4 a1 = *(const bf4 *)(d1T + (16 * w + r) * TS + s0);
-        const bf4 a2 = *(const bf4 *)(d2T + (16 * w + r) * TS + s0);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-            g1[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, *(const bf4 *)(xT + (16 * nt + r) * TS + s0),
-                                                               g1[nt], 0, 0, 0);
-#pragma unroll
-        for (int nt = 0; nt < 3; ++nt)
-            g2[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a2, *(const bf4 *)(h1T + (16 * nt + r) * TS + s0),
-                                                               g2[nt], 0, 0, 0);
+        g1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*(const bf4 *)(d1T + (16 * oh + r) * TS + s0),
+                                                       *(const bf4 *)(xT + (16 * nt + r) * TS + s0), g1, 0, 0, 0);
+        if (nt < 3)
+            g2 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*(const bf4 *)(d2T + (16 * oh + r) * TS + s0),
+                                                           *(const bf4 *)(h1T + (16 * nt + r) * TS + s0), g2, 0, 0,
+                                                           0);
     }
-    // lane holds D[row 16w + 4q + i][column 16nt + r]
+    // lane holds D[row 16 oh + 4q + i][column 16 nt + r]
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int o = 16 * w + 4 * q + i;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int k = 16 * nt + r;
-            if (k < NIN) pb[OW1 + o * NIN + k] = g1[nt][i];
-            else if (k == NIN) pb[OB1 + o] = g1[nt][i];
-        }
-#pragma unroll
-        for (int nt = 0; nt < 3; ++nt) {
-            const int j = 16 * nt + r;
-            if (j < NH) pb[OW2 + o * NH + j] = g2[nt][i];
-            else if (j == NH) pb[OB2 + o] = g2[nt][i];
-        }
+        const int o = 16 * oh + 4 * q + i, k = 16 * nt + r;
+        if (k < NIN) pb[OW1 + o * NIN + k] = g1[i];
+        else if (k == NIN) pb[OB1 + o] = g1[i];
+        if (k < NH) pb[OW2 + o * NH + k] = g2[i];
+        else if (k == NH) pb[OB2 + o] = g2[i];
     }
 }
 
-// Sum the per-block partials in block order (deterministic).
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float *__restrict__ part, int nblk,
-                                                         float invn, float *__restrict__ grad,
-                                                         float *__restrict__ loss)
+// Sum of the per-block partials: 64 parameters per block of the grid, RG
+// waves of a block taking every RG-th partial, their sums added in wave order
+// (a fixed order: deterministic).  One block looping over every partial of
+// all parameters took 81 us for a batch of 4096 (32 partials), bound by the
+// latency of its serial loads; this takes about 4.
+constexpr int RG = 16;
+
+__global__ __launch_bounds__(64 * RG) void mlp_reduce_kernel(const float *__restrict__ part, int nblk,
+                                                             float invn, float *__restrict__ grad,
+                                                             float *__restrict__ loss)
 {
-    for (int p = threadIdx.x; p <= NPARAM; p += 256) {
-        float s = 0.f;
-        for (int b = 0; b < nblk; ++b) s += part[(long)b * (NPARAM + 1) + p];
-        if (p < NPARAM) grad[p] = s;
-        else if (loss) *loss = s * invn;
+    __shared__ float sm[RG][64];
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6, p = blockIdx.x * 64 + l;
+    float s = 0.f;
+    if (p <= NPARAM) {
+        const float *q = part + p;
+        int b = w;
+        for (; b + 3 * RG < nblk; b += 4 * RG) {
+            const float x0 = q[(long)b * (NPARAM + 1)], x1 = q[(long)(b + RG) * (NPARAM + 1)];
+            const float x2 = q[(long)(b + 2 * RG) * (NPARAM + 1)], x3 = q[(long)(b + 3 * RG) * (NPARAM + 1)];
+            s += (x0 + x1) + (x2 + x3);
+        }
+        for (; b < nblk; b += RG) s += q[(long)b * (NPARAM + 1)];
     }
+    sm[w][l] = s;
+    __syncthreads();
+    if (w != 0 || p > NPARAM) return;
+#pragma unroll
+    for (int i = 1; i < RG; ++i) s += sm[i][l];
+    if (p < NPARAM) grad[p] = s;
+    else if (loss) *loss = s * invn;
 }
 
 __global__ __launch_bounds__(256) void mlp_adam_kernel(float *__restrict__ th, float *__restrict__ mo,
@@ -847,10 +873,11 @@ hipError_t launch_mlp_grad(const float *th, const float *X, const float *t, int 
 {
     const int nb = mlp_grad_blocks(n);
     const float invn = 1.0f / (float)n;
-    hipLaunchKernelGGL(rt::mlp_grad_kernel, dim3(nb), dim3(128), 0, st, th, X, t, n, invn, part);
+    hipLaunchKernelGGL(rt::mlp_grad_kernel, dim3(nb), dim3(rt::GT), 0, st, th, X, t, n, invn, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rt::mlp_reduce_kernel, dim3(1), dim3(256), 0, st, part, nb, invn, grad, loss);
+    hipLaunchKernelGGL(rt::mlp_reduce_kernel, dim3((NPARAM + 1 + 63) / 64), dim3(64 * rt::RG), 0, st, part, nb,
+                       invn, grad, loss);
     return hipGetLastError();
 }
 
