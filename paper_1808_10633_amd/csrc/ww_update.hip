@@ -24,13 +24,14 @@ __global__ __launch_bounds__(256) void update_kernel(UpdArgs<T> a)
 
 constexpr int MX_TX = 64, MX_TY = 4, MX_KZ = 16;   // march tile: x lanes, y rows, z cells
 constexpr int NXCD = 8;                              // MI355X: 8 XCDs, blocks dealt round-robin
+constexpr int MX_BLOCKS = 1024;                      // blocks that fill the chip (four per CU)
 
-// Three active axes: one thread per (i, j) column segment of MX_KZ cells,
+// Three active axes: one thread per (i, j) column segment of kz cells,
 // marching in k (up::march_column).  Hardware block b runs on XCD b % 8;
 // blocks are renumbered so that each XCD owns a contiguous range of tiles
 // (neighbouring rows share its L2).
 template <typename T, bool BONLY, bool STAG>
-__global__ __launch_bounds__(256) void update_march_kernel(UpdArgs<T> a, int ntx, int nty, int ntz,
+__global__ __launch_bounds__(256) void update_march_kernel(UpdArgs<T> a, int ntx, int nty, int ntz, int kz,
                                                            int per_xcd)
 {
     const Geom &G = a.G;
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(256) void update_march_kernel(UpdArgs<T> a, int ntx
     const int bx = lb % ntx, by = (lb / ntx) % nty, bz = lb / (ntx * nty);
     const int i = bx * MX_TX + threadIdx.x, j = by * MX_TY + threadIdx.y;
     if (i >= G.n[0] || j >= G.n[1]) return;
-    const int k0 = bz * MX_KZ, k1 = min(k0 + MX_KZ, G.n[2]);
+    const int k0 = bz * kz, k1 = min(k0 + kz, G.n[2]);
     up::march_column<T, BONLY, STAG>(a, i, j, k0, k1);
 }
 
@@ -60,18 +61,25 @@ hipError_t launch_update(const T *u0, const T *acc_in, T *acc_out, T *out, const
     a.G = G;
     a.c = c;
     if (G.act[0] && G.act[1] && G.act[2]) {
-        int ntx = (G.n[0] + MX_TX - 1) / MX_TX, nty = (G.n[1] + MX_TY - 1) / MX_TY,
-            ntz = (G.n[2] + MX_KZ - 1) / MX_KZ;
+        const int ntx = (G.n[0] + MX_TX - 1) / MX_TX, nty = (G.n[1] + MX_TY - 1) / MX_TY;
+        // A march is a serial chain of one memory latency (about 6 us with
+        // the arithmetic) per cell.  Segments of MX_KZ cells reuse the carried
+        // fluxes best and serve boxes that fill the chip with them; smaller
+        // boxes are cut into shorter segments, down to one cell, until they
+        // do: at 32^3 (16 blocks of 16 cells) the FP64 update took 112 us.
+        int kz = MX_KZ;
+        while (kz > 1 && (long)ntx * nty * ((G.n[2] + kz - 1) / kz) < MX_BLOCKS) kz /= 2;
+        const int ntz = (G.n[2] + kz - 1) / kz;
         int nb = ntx * nty * ntz, per = (nb + NXCD - 1) / NXCD;
         const dim3 grd(per * NXCD), blk(MX_TX, MX_TY);
         if (c.bonly && c.stag)
-            hipLaunchKernelGGL((update_march_kernel<T, true, true>), grd, blk, 0, st, a, ntx, nty, ntz, per);
+            hipLaunchKernelGGL((update_march_kernel<T, true, true>), grd, blk, 0, st, a, ntx, nty, ntz, kz, per);
         else if (c.bonly)
-            hipLaunchKernelGGL((update_march_kernel<T, true, false>), grd, blk, 0, st, a, ntx, nty, ntz, per);
+            hipLaunchKernelGGL((update_march_kernel<T, true, false>), grd, blk, 0, st, a, ntx, nty, ntz, kz, per);
         else if (c.stag)
-            hipLaunchKernelGGL((update_march_kernel<T, false, true>), grd, blk, 0, st, a, ntx, nty, ntz, per);
+            hipLaunchKernelGGL((update_march_kernel<T, false, true>), grd, blk, 0, st, a, ntx, nty, ntz, kz, per);
         else
-            hipLaunchKernelGGL((update_march_kernel<T, false, false>), grd, blk, 0, st, a, ntx, nty, ntz, per);
+            hipLaunchKernelGGL((update_march_kernel<T, false, false>), grd, blk, 0, st, a, ntx, nty, ntz, kz, per);
         return hipGetLastError();
     }
     long ncell = (long)G.n[0] * G.n[1] * G.n[2];
