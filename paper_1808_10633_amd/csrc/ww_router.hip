@@ -23,7 +23,7 @@ namespace rt {
 typedef short bf4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr int YZ_PW = 32;         // positions per y/z tile of the routed sweep (8 faces each)
+constexpr int YZ_PW = 32, YZ_FT = 8;   // positions and faces per y/z tile of the routed sweep
 constexpr int QREG = 64;          // troubled-queue regions (atomic counters)
 static_assert(QREG == ROUTED_QUEUE_REGIONS, "queue regions");
 constexpr int OW1 = 0, OB1 = 1536, OW2 = 1568, OB2 = 2592, OW3 = 2624, OB3 = 2656;
@@ -619,12 +619,12 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
                                                            unsigned long long *__restrict__ queue,
                                                            int32_t *__restrict__ qcount, long qcap,
                                                            unsigned char *__restrict__ mask, int reuse,
-                                                           XFuse<float> xf)
+                                                           XFuse<float> xf, sw::XSegArgs XA, sw::YZArgs YA)
 {
     static_assert(!FUSED || DIR == 0, "the fused tail belongs to the x sweep");
     // tiles as the plain sweeps: x in flattened 256-face segments (rows of
     // XSEG_MIN faces or more) or 4 rows x 64 faces; y/z 32 positions x 8 faces
-    constexpr int NC = DIR == 0 ? sw::XSEG_CELLS : sw::yz_cells<YZ_PW>();
+    constexpr int NC = DIR == 0 ? sw::XSEG_CELLS : sw::yz_cells<YZ_PW, YZ_FT>();
     __shared__ float sq[sw::NQ * NC];
     __shared__ __align__(16) short xs[4 * 32 * XS];     // 32 feature rows per wave
     __shared__ int wcnt[4], wact[4];
@@ -640,12 +640,18 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
     if constexpr (DIR == 0) {
         cstr = 1;
         if (FUSED || F.cnt[0] >= sw::XSEG_MIN) {
-            const sw::XSeg X = sw::xseg_setup(F, blockIdx.x);
-            sw::xseg_stage<float, false, true>(u, G, F, P, X, sq);
+            const XTile X = xtile(blockIdx.x * 256u, XA.total, XA.nf, XA.n1);
+            sw::xseg_stage<float, false, true>(u + sw::xseg_base(G, F, X), G.sv, sw::xseg_jump(G, F), P.gamma, X, tid,
+                                               sq);
             __syncthreads();
             sw::stage_end();
-            act = sw::xseg_face(F, X, tid, pos, off);
             nface = X.nface;
+            act = tid < nface;
+            const int t = act ? tid : nface - 1, s = X.row_of(t);
+            pos[0] = X.face_x(t, s);
+            pos[1] = F.lo[1] + X.jj(s);
+            pos[2] = F.lo[2] + X.kk(s);
+            off = X.cell_of(t, s);
         } else {
             const int cm[8] = { 0, 1, 2, 3, 4, 5, 6, 7 };
             const int ta = blockIdx.x, tb = blockIdx.y, nlast = G.n[0] + 2;
@@ -670,10 +676,16 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
         }
     } else {
         cstr = YZ_PW;
-        sw::yz_stage<DIR, YZ_PW, float, true>(u, G, F, P, blockIdx.x, blockIdx.y, sq);
+        constexpr int A = 0, B = DIR == 1 ? 2 : 1;
+        const sw::YZTile<DIR == 0 ? 1 : DIR, YZ_PW, YZ_FT> t(YA, blockIdx.x, blockIdx.y, tid);
+        sw::yz_stage<DIR == 0 ? 1 : DIR, YZ_PW, YZ_FT, float, true>(u, G, F, P.gamma, YA, t, sq);
         __syncthreads();
         sw::stage_end();
-        act = sw::yz_face<DIR, YZ_PW>(F, blockIdx.x, blockIdx.y, tid, pos, off);
+        pos[A] = t.pos_a(F, YA);
+        pos[B] = t.pos_b(F);
+        pos[N] = t.f0 + t.fr;
+        off = t.fr * YZ_PW + t.pl;
+        act = t.pl < t.np && pos[N] < F.cnt[N];
     }
     // --- features and the MLP
     bool troubled = false;
@@ -957,14 +969,17 @@ hipError_t launch_routed_sweep(int dir, const float *u, float *flux, const Geom 
     const long cap = routed_queue_capacity(dir, F);
     const dim3 grid((unsigned)na, (unsigned)nb), blk(64, 4), qgrid(32, rt::QREG), qblk(128);
     const XFuse<float> nofuse{};
+    const sw::XSegArgs XA = sw::xseg_args(F);
+    const sw::YZArgs YA = dir == 2 ? sw::yz_args<2, rt::YZ_PW, rt::YZ_FT>(F, 1)
+                                   : sw::yz_args<1, rt::YZ_PW, rt::YZ_FT>(F, 1);
     switch (dir) {
     case 0:
         if (fused)
             hipLaunchKernelGGL((rt::routed_sweep_kernel<0, true>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
-                               force, nsmooth, queue, qcount, cap, mask, reuse, *xf);
+                               force, nsmooth, queue, qcount, cap, mask, reuse, *xf, XA, YA);
         else
             hipLaunchKernelGGL((rt::routed_sweep_kernel<0, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
-                               force, nsmooth, queue, qcount, cap, mask, reuse, nofuse);
+                               force, nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA);
         if (force == 0)
             hipLaunchKernelGGL(rt::troubled_kernel<0>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
         if (fused && force == 0)
@@ -976,13 +991,13 @@ hipError_t launch_routed_sweep(int dir, const float *u, float *flux, const Geom 
         break;
     case 1:
         hipLaunchKernelGGL((rt::routed_sweep_kernel<1, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr, force,
-                           nsmooth, queue, qcount, cap, mask, reuse, nofuse);
+                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA);
         if (force == 0)
             hipLaunchKernelGGL(rt::troubled_kernel<1>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
         break;
     default:
         hipLaunchKernelGGL((rt::routed_sweep_kernel<2, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr, force,
-                           nsmooth, queue, qcount, cap, mask, reuse, nofuse);
+                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA);
         if (force == 0)
             hipLaunchKernelGGL(rt::troubled_kernel<2>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
         break;

@@ -15,6 +15,9 @@ namespace {
 // Hardware block b runs on XCD b % 8 (blocks are dealt round-robin to the
 // eight XCDs, each with its own L2).
 constexpr int NXCD = 8;
+// 256-thread blocks of a launch: HIP takes fewer than 2^32 threads per axis.
+// Tile and face numbers therefore fit 32 bits.
+constexpr long MAX_BLOCKS = 1L << 24;
 
 // x sweeps stage the cells' fluxes with the cells (sw::NQ_PRE) in FP32 only:
 // the FP32 fused x sweep ran 1.8 % faster at 512^3.  The FP64 sweeps ran 2 %
@@ -26,33 +29,30 @@ template <typename T> constexpr bool pre_x() { return sizeof(T) == 4; }
 // the sweep axis) are renumbered so that each XCD walks whole columns of
 // tiles, tb fastest.  A tile's 5 halo rows along the sweep axis were staged
 // by the tile before it on the same XCD and come from that XCD's L2.
-__device__ __forceinline__ bool column_tile(long ntile, long nb, long per_xcd, int &ta, int &tb)
+__device__ __forceinline__ bool column_tile(const sw::YZArgs &Y, uint32_t &ta, uint32_t &tb)
 {
-    const long lb = (long)(blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;
-    if (lb >= ntile) return false;
-    ta = (int)(lb / nb);
-    tb = (int)(lb - (long)ta * nb);
+    const uint32_t lb = (blockIdx.x % NXCD) * Y.per_xcd + blockIdx.x / NXCD;
+    if (lb >= Y.ntile) return false;
+    ta = Y.nb.div(lb);
+    tb = lb - ta * Y.nb.d;
     return true;
 }
 
-// DIR 0: 2-D grid (ta, tb); DIR 1, 2: 1-D grid in column order.
-template <int DIR, int FT, typename T, bool WZ, bool GLF>
-__global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_kernel(const T *__restrict__ u, T *__restrict__ flux,
-                                                     Geom G, FaceBox F, Phys P, long nb, long ntile,
-                                                     long per_xcd)
+// x sweep of short rows: 2-D grid (ta, tb) of 4 rows x 64 faces.
+template <typename T, bool WZ, bool GLF>
+__global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xrows_kernel(const T *__restrict__ u,
+                                                           T *__restrict__ flux, Geom G, FaceBox F, Phys P)
 {
-    __shared__ T sq[sw::NQ * sw::tile_cells<DIR, FT>()];
-    int ta = blockIdx.x, tb = blockIdx.y;
-    if (DIR != 0 && !column_tile(ntile, nb, per_xcd, ta, tb)) return;
-    sw::sweep_tile<DIR, FT, T, WZ, GLF>(u, flux, G, F, P, ta, tb, sq);
+    __shared__ T sq[sw::NQ * sw::tile_cells<0, 4>()];
+    sw::sweep_tile<0, 4, T, WZ, GLF>(u, flux, G, F, P, blockIdx.x, blockIdx.y, sq);
 }
 
 template <typename T, bool WZ, bool GLF>
 __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xseg_kernel(const T *__restrict__ u, T *__restrict__ flux,
-                                                         Geom G, FaceBox F, Phys P)
+                                                         Geom G, FaceBox F, Phys P, sw::XSegArgs A)
 {
     __shared__ T sq[sw::nq<pre_x<T>()>() * sw::XSEG_CELLS];
-    sw::sweep_tile_xseg<T, WZ, GLF, pre_x<T>()>(u, flux, G, F, P, blockIdx.x, sq);
+    sw::sweep_tile_xseg<T, WZ, GLF, pre_x<T>()>(u, flux, G, F, P, A, blockIdx.x, sq);
 }
 
 // The fused x sweep renumbers blocks so that each XCD walks a contiguous
@@ -62,13 +62,14 @@ __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xseg_kernel(const T *_
 template <typename T, bool WZ, bool GLF>
 __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xfused_kernel(const T *__restrict__ u,
                                                            T *__restrict__ flux, Geom G, FaceBox F, Phys P,
-                                                           XFuse<T> xf, long ntile, long per_xcd)
+                                                           XFuse<T> xf, sw::XSegArgs A, uint32_t ntile,
+                                                           uint32_t per_xcd)
 {
     __shared__ T sq[sw::nq<pre_x<T>()>() * sw::XSEG_CELLS];
     __shared__ T hx[5 * sw::TILE * sw::ROWS];
-    const long tile = (long)(blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;
+    const uint32_t tile = (blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;
     if (tile >= ntile) return;
-    sw::sweep_tile_xseg_fused<T, WZ, GLF, pre_x<T>()>(u, flux, G, F, P, tile, sq, hx, xf);
+    sw::sweep_tile_xseg_fused<T, WZ, GLF, pre_x<T>()>(u, flux, G, F, P, A, tile, sq, hx, xf);
 }
 
 template <typename T, bool WZ, bool GLF>
@@ -78,73 +79,69 @@ hipError_t launch_xfused(const T *u, T *flux, const Geom &G, const FaceBox &F, c
     const long total = (long)F.cnt[0] * F.cnt[1] * F.cnt[2];
     const long nt = (total - 1 + sw::XFUSE_STRIDE - 1) / sw::XFUSE_STRIDE;
     const long per = (nt + NXCD - 1) / NXCD;
+    if (per * NXCD >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((sweep_xfused_kernel<T, WZ, GLF>), dim3((unsigned)(per * NXCD)), dim3(sw::TILE, sw::ROWS), 0,
-                       st, u, flux, G, F, P, xf, nt, per);
+                       st, u, flux, G, F, P, xf, sw::xseg_args(F), (uint32_t)nt, (uint32_t)per);
     return hipGetLastError();
 }
 
-// FP64 y/z sweeps: 32 positions x 8 faces per tile (1.6 staged cells per
-// face instead of 2.25 with 64 x 4, in 43 KB of LDS); measured 3 % faster at
-// 512^3.  FP32 keeps 64 positions x 8 faces (sweep_tile, FT = 8).
-constexpr int YZ_PW_F64 = 32;
+// y/z tiles.  FP64: 32 positions x 8 faces (1.6 staged cells per face instead
+// of 2.25 with 64 x 4, in 43 KB of LDS), measured 3 % faster at 512^3.  FP32:
+// 64 positions x 8 faces, two faces per thread; the FP64 shape is 12 % slower
+// there.
+template <typename T> constexpr int yz_pw() { return sizeof(T) == 8 ? 32 : 64; }
+constexpr int YZ_FT = 8;
 
-template <int DIR, int PW, typename T, bool WZ, bool GLF>
+template <int DIR, typename T, bool WZ, bool GLF>
 __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_yz_kernel(const T *__restrict__ u, T *__restrict__ flux,
-                                                       Geom G, FaceBox F, Phys P, long nb, long ntile,
-                                                       long per_xcd)
+                                                       Geom G, FaceBox F, Phys P, sw::YZArgs Y)
 {
-    __shared__ T sq[sw::NQ * sw::yz_cells<PW>()];
-    int ta, tb;
-    if (!column_tile(ntile, nb, per_xcd, ta, tb)) return;
-    sw::sweep_tile_yz<DIR, PW, T, WZ, GLF>(u, flux, G, F, P, ta, tb, sq);
+    constexpr int PW = yz_pw<T>();
+    __shared__ T sq[sw::NQ * sw::yz_cells<PW, YZ_FT>()];
+    uint32_t ta, tb;
+    if (!column_tile(Y, ta, tb)) return;
+    sw::sweep_tile_yz<DIR, PW, YZ_FT, T, WZ, GLF>(u, flux, G, F, P, Y, ta, tb, sq);
 }
 
-template <int DIR, int FT, typename T, bool WZ, bool GLF>
-hipError_t launch_dir(const T *u, T *flux, const Geom &G, const FaceBox &F, const Phys &P,
-                      hipStream_t st)
+template <int DIR, typename T, bool WZ, bool GLF>
+hipError_t launch_yz(const T *u, T *flux, const Geom &G, const FaceBox &F, const Phys &P, hipStream_t st)
 {
-    if (DIR != 0 && sizeof(T) == 8) {
-        constexpr int PW = YZ_PW_F64, B = (DIR == 1) ? 2 : 1;
-        const long npos = (long)F.cnt[0] * F.cnt[B];
-        const long na = (npos + PW - 1) / PW, nb = (F.cnt[DIR] + 256 / PW - 1) / (256 / PW);
-        const long nt = na * nb, per = (nt + NXCD - 1) / NXCD;
-        hipLaunchKernelGGL((sweep_yz_kernel<DIR == 0 ? 1 : DIR, PW, T, WZ, GLF>), dim3((unsigned)(per * NXCD)),
-                           dim3(sw::TILE, sw::ROWS), 0, st, u, flux, G, F, P, nb, nt, per);
-        return hipGetLastError();
-    }
-    if (DIR == 0 && F.cnt[0] >= sw::XSEG_MIN) {
+    constexpr int PW = yz_pw<T>(), B = DIR == 1 ? 2 : 1;
+    const long nt = ((long)F.cnt[0] * F.cnt[B] + PW - 1) / PW * ((F.cnt[DIR] + YZ_FT - 1) / YZ_FT);
+    if (nt + NXCD >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
+    const sw::YZArgs Y = sw::yz_args<DIR, PW, YZ_FT>(F, NXCD);
+    hipLaunchKernelGGL((sweep_yz_kernel<DIR, T, WZ, GLF>), dim3(Y.per_xcd * NXCD), dim3(sw::TILE, sw::ROWS), 0, st,
+                       u, flux, G, F, P, Y);
+    return hipGetLastError();
+}
+
+template <typename T, bool WZ, bool GLF>
+hipError_t launch_x(const T *u, T *flux, const Geom &G, const FaceBox &F, const Phys &P, hipStream_t st)
+{
+    if (F.cnt[0] >= sw::XSEG_MIN) {
         // long rows: flattened face segments, no ragged tile per row
         const long total = (long)F.cnt[0] * F.cnt[1] * F.cnt[2];
         const long nt = (total + sw::TILE * sw::ROWS - 1) / (sw::TILE * sw::ROWS);
+        if (nt >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
         hipLaunchKernelGGL((sweep_xseg_kernel<T, WZ, GLF>), dim3((unsigned)nt), dim3(sw::TILE, sw::ROWS), 0, st,
-                           u, flux, G, F, P);
+                           u, flux, G, F, P, sw::xseg_args(F));
         return hipGetLastError();
     }
     long na, nb;
-    sw::sweep_tiles<DIR, FT>(F, na, nb);
-    if (DIR == 0) {
-        hipLaunchKernelGGL((sweep_kernel<DIR, FT, T, WZ, GLF>), dim3((unsigned)na, (unsigned)nb),
-                           dim3(sw::TILE, sw::ROWS), 0, st, u, flux, G, F, P, nb, na * nb, 0L);
-    } else {
-        const long nt = na * nb, per = (nt + NXCD - 1) / NXCD;
-        hipLaunchKernelGGL((sweep_kernel<DIR, FT, T, WZ, GLF>), dim3((unsigned)(per * NXCD)),
-                           dim3(sw::TILE, sw::ROWS), 0, st, u, flux, G, F, P, nb, nt, per);
-    }
+    sw::sweep_tiles<0, 4>(F, na, nb);
+    hipLaunchKernelGGL((sweep_xrows_kernel<T, WZ, GLF>), dim3((unsigned)na, (unsigned)nb),
+                       dim3(sw::TILE, sw::ROWS), 0, st, u, flux, G, F, P);
     return hipGetLastError();
 }
-
-// faces per y/z tile of the FP32 sweep (FP64 y/z sweeps use sweep_yz_kernel)
-template <typename T> constexpr int ft_of() { return sizeof(T) == 8 ? 4 : 8; }
 
 template <typename T, bool WZ, bool GLF>
 hipError_t launch_dirs(int dir, const T *u, T *flux, const Geom &G, const FaceBox &F, const Phys &P,
                        hipStream_t st)
 {
-    constexpr int FT = ft_of<T>();
     switch (dir) {
-    case 0: return launch_dir<0, FT, T, WZ, GLF>(u, flux, G, F, P, st);
-    case 1: return launch_dir<1, FT, T, WZ, GLF>(u, flux, G, F, P, st);
-    default: return launch_dir<2, FT, T, WZ, GLF>(u, flux, G, F, P, st);
+    case 0: return launch_x<T, WZ, GLF>(u, flux, G, F, P, st);
+    case 1: return launch_yz<1, T, WZ, GLF>(u, flux, G, F, P, st);
+    default: return launch_yz<2, T, WZ, GLF>(u, flux, G, F, P, st);
     }
 }
 

@@ -29,6 +29,7 @@
 //      primitive columns; the flux is stored in grid components.
 // The sweep axis is a template parameter: no data is transposed.
 #pragma once
+#include "ww_index.h"
 #include "ww_internal.h"
 #include "ww_update_dev.h"
 
@@ -272,6 +273,30 @@ __device__ __forceinline__ void stage_values(const T (&w)[8], double gamma, T *q
 #pragma unroll
         for (int c = 1; c < 7; ++c) q[(13 + c) * qs] = F[c];
     }
+}
+
+// A wave-uniform pointer to device memory, kept in scalar registers: without
+// this the compiler reassociates (base + v sv) + lane offset into per-lane
+// 64-bit multiplies, two quarter-rate instructions per address.
+template <typename T>
+using GlobalPtr = T __attribute__((address_space(1))) *;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> uniform(T *p)
+{
+    GlobalPtr<T> g = (GlobalPtr<T>)p;
+    asm("" : "+s"(g));
+    return g;
+}
+// Load, store of the element at a 32-bit byte offset (per lane) from a uniform base.
+template <typename T>
+__device__ __forceinline__ T ld32(const T *base, uint32_t elem)
+{
+    return *(GlobalPtr<const T>)((GlobalPtr<const char>)uniform(base) + (uint32_t)(elem * (uint32_t)sizeof(T)));
+}
+template <typename T>
+__device__ __forceinline__ void st32(T *base, uint32_t elem, T x)
+{
+    *(GlobalPtr<T>)((GlobalPtr<char>)uniform(base) + (uint32_t)(elem * (uint32_t)sizeof(T))) = x;
 }
 
 // Stage one cell: its variables read from the state (cm: sweep-frame order).
@@ -892,105 +917,163 @@ __device__ __forceinline__ void sweep_tile_xflat_fused(const T *__restrict__ u, 
 
 // x sweep over the flattened (row, face) space, for rows of at least
 // XSEG_MIN faces: tile t takes the TILE*ROWS consecutive faces t*256 ..
-// of the row-major face sequence, which touch at most 4 rows; for each row
-// it stages the cells of its face segment with the 3 + 2 halo (256 + 5*4
+// of the row-major face sequence, which touch at most 4 rows (XTile); it
+// stages the cells of its row segments with their 3 + 2 halo (256 + 5*4
 // cells at most, the size of the regular x tile) and each thread takes one
 // face.  Only the last tile of the sweep is ragged.
 constexpr int XSEG_MIN = 86;
 constexpr int XSEG_CELLS = ROWS * NCX;
 
-// Segment table of one tile: segment s = faces fa_s.. of row r_lo + s at
-// transverse cell (j_s, k_s), staged from LDS offset o_s, holding tile-local
-// faces from b_s on.  Kept in scalars (a dynamically indexed array would
-// live in scratch), and the row -> (j, k) divisions are done once per
-// segment, not per cell.
-struct XSeg {
-    long g0;
-    int nf, nface, fa0, fa1, fa2, fa3, o1, o2, o3, o4, b1, b2, b3;
-    int j0, j1, j2, j3, k0, k1, k2, k3;
-    __device__ int fa(int s) const { return s == 0 ? fa0 : s == 1 ? fa1 : s == 2 ? fa2 : fa3; }
-    __device__ int off(int s) const { return s == 0 ? 0 : s == 1 ? o1 : s == 2 ? o2 : o3; }
-    __device__ int bs(int s) const { return s == 0 ? 0 : s == 1 ? b1 : s == 2 ? b2 : b3; }
-    __device__ int j(int s) const { return s == 0 ? j0 : s == 1 ? j1 : s == 2 ? j2 : j3; }
-    __device__ int k(int s) const { return s == 0 ? k0 : s == 1 ? k1 : s == 2 ? k2 : k3; }
+// Scalar constants of an x sweep's tiles (launch constants).
+struct XSegArgs {
+    FastDiv nf, n1;            // faces per row, rows per plane of the face box
+    uint32_t total;            // faces of the sweep
 };
-
-// stride: first face of tile t is t * stride (TILE*ROWS, or TILE*ROWS - 1 for
-// tiles that overlap by one face).
-__device__ __forceinline__ XSeg xseg_setup(const FaceBox &F, long tile, int stride = TILE * ROWS)
+__host__ inline XSegArgs xseg_args(const FaceBox &F)
 {
-    constexpr int TF = TILE * ROWS;
-    XSeg X;
-    X.nf = F.cnt[0];
-    const long total = (long)F.cnt[1] * F.cnt[2] * X.nf;
-    X.g0 = tile * stride;
-    const long g1 = (X.g0 + TF - 1 < total - 1) ? X.g0 + TF - 1 : total - 1;
-    X.nface = (int)(g1 - X.g0 + 1);
-    const long r_lo = X.g0 / X.nf;
-    const int nseg = (int)(g1 / X.nf - r_lo) + 1;      // <= 4 since nf >= XSEG_MIN
-    X.fa0 = X.fa1 = X.fa2 = X.fa3 = X.o1 = X.o2 = X.o3 = X.o4 = X.b1 = X.b2 = X.b3 = 0;
-    X.j0 = X.j1 = X.j2 = X.j3 = X.k0 = X.k1 = X.k2 = X.k3 = 0;
-    int o = 0, bsum = 0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int a = s == 0 ? (int)(X.g0 - r_lo * X.nf) : 0;
-        const int b = s == nseg - 1 ? (int)(g1 - (r_lo + s) * X.nf) : X.nf - 1;
-        const long row = r_lo + s;
-        const int jj = F.lo[1] + (int)(row % F.cnt[1]), kk = F.lo[2] + (int)(row / F.cnt[1]);
-        o += s < nseg ? b - a + 6 : 0;
-        bsum += s < nseg ? b - a + 1 : 0;                // faces of segments 0..s
-        if (s == 0) { X.fa0 = a; X.o1 = o; X.b1 = bsum; X.j0 = jj; X.k0 = kk; }
-        if (s == 1) { X.fa1 = a; X.o2 = o; X.b2 = bsum; X.j1 = jj; X.k1 = kk; }
-        if (s == 2) { X.fa2 = a; X.o3 = o; X.b3 = bsum; X.j2 = jj; X.k2 = kk; }
-        if (s == 3) { X.fa3 = a; X.o4 = o; X.j3 = jj; X.k3 = kk; }
-    }
-    return X;
+    XSegArgs A;
+    A.nf = FastDiv((uint32_t)F.cnt[0]);
+    A.n1 = FastDiv((uint32_t)F.cnt[1]);
+    A.total = (uint32_t)F.sc;
+    return A;
 }
 
-// Stage the tile's cells (x sweep frame), sq with stride XSEG_CELLS.
+// State index of the tile's first staged cell, and the jump of state_rel.
+__device__ __forceinline__ long xseg_base(const Geom &G, const FaceBox &F, const XTile &X)
+{
+    return G.base + (X.fa0 - 3) + (long)(F.lo[1] + X.jj0) * G.s[1] + (long)(F.lo[2] + X.kk0) * G.s[2];
+}
+__device__ __forceinline__ uint32_t xseg_jump(const Geom &G, const FaceBox &F)
+{
+    return (uint32_t)(G.s[2] - (long)F.cnt[1] * G.s[1]);
+}
+
+
+// Stage the tile's cells (x sweep frame), sq with stride XSEG_CELLS; ub: the
+// state at the tile's first cell.  A thread's loads first (stage_tile's
+// order), at 32-bit offsets: a tile spans at most nine state rows of at most
+// 2^20 + 6 cells.
 template <typename T, bool PRE = false, bool LIN = false>
-__device__ __forceinline__ void xseg_stage(const T *__restrict__ u, const Geom &G, const FaceBox & /*F*/,
-                                           const Phys &P, const XSeg &X, T *sq)
+__device__ __forceinline__ void xseg_stage(const T *__restrict__ ub, long sv, uint32_t jump, double gamma,
+                                           const XTile &X, int tid, T *sq)
 {
-    const int cm[8] = { 0, 1, 2, 3, 4, 5, 6, 7 };
-    stage_tile<(XSEG_CELLS + 255) / 256, PRE, LIN>(u, G.sv, cm, P.gamma, sq, XSEG_CELLS, X.o4,
-                                                  [&](int c, long &id) {
-        const int s = (c >= X.o1) + (c >= X.o2) + (c >= X.o3);
-        const int x = X.fa(s) - 3 + (c - X.off(s));
-        id = G.base + x * G.s[0] + X.j(s) * G.s[1] + (long)X.k(s) * G.s[2];
-        return true;
-    });
-}
-
-// Face of thread tid: position and LDS offset of its cell i-2 (stride 1).
-__device__ __forceinline__ bool xseg_face(const FaceBox & /*F*/, const XSeg &X, int tid, int (&pos)[3], int &off)
-{
-    const int t = tid < X.nface ? tid : X.nface - 1;
-    const int s = (t >= X.b1) + (t >= X.b2) + (t >= X.b3);
-    const int f = X.fa(s) + (t - X.bs(s));
-    pos[0] = f;
-    pos[1] = X.j(s);
-    pos[2] = X.k(s);
-    off = X.off(s) + (f - X.fa(s));      // stencil cells f-3 .. f+2 from segment offset f - fa
-    return tid < X.nface;
+    constexpr int IT = (XSEG_CELLS + 255) / 256;
+    T w[IT][8];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int c = tid + it * TILE * ROWS;
+        if (c < X.ncell) {
+            const uint32_t r = X.state_rel(c, jump);
+#pragma unroll
+            for (int v = 0; v < 8; ++v) w[it][v] = ld32(ub + v * sv, r);
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int c = tid + it * TILE * ROWS;
+        if (c < X.ncell) stage_values<T, PRE, LIN>(w[it], gamma, sq + c, XSEG_CELLS);
+    }
 }
 
 template <typename T, bool WZ = false, bool GLF = false, bool PRE = false>
 __device__ __forceinline__ void sweep_tile_xseg(const T *__restrict__ u, T *__restrict__ flux,
                                                 const Geom &G, const FaceBox &F, const Phys &P,
-                                                long tile, T *sq)
+                                                const XSegArgs &A, uint32_t tile, T *sq)
 {
     stage_begin();
-    const XSeg X = xseg_setup(F, tile);
-    xseg_stage<T, PRE>(u, G, F, P, X, sq);
+    const int tid = threadIdx.x + TILE * threadIdx.y;
+    const XTile X = xtile(tile * (TILE * ROWS), A.total, A.nf, A.n1);
+    xseg_stage<T, PRE>(u + xseg_base(G, F, X), G.sv, xseg_jump(G, F), P.gamma, X, tid, sq);
     __syncthreads();
     stage_end();
-    int pos[3], off;
-    if (xseg_face(F, X, threadIdx.x + TILE * threadIdx.y, pos, off)) {
+    if (tid < X.nface) {
         T out[7];
-        face_flux<T, false, WZ, GLF, true, PRE>(sq, XSEG_CELLS, off, 1, P.gamma, P.igm1, (T)P.eps, out, nullptr,
-                                                P.ag);
-        store_face<0, T>(flux, F, pos, out);
+        face_flux<T, false, WZ, GLF, true, PRE>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma, P.igm1,
+                                                (T)P.eps, out, nullptr, P.ag);
+        // faces are stored in the order of their numbers; the x frame is the grid's
+        T *const fb = flux + X.g0;
+#pragma unroll
+        for (int c = 0; c < 7; ++c) st32<T>(fb + c * F.sc, tid, out[c]);
+    }
+}
+
+// The cell between tile faces t and t + 1 of row s (face x index f): its y
+// and z faces' fluxes and RK arrays, read at 32-bit offsets from the tile's
+// scalar bases (fused_cell_load's values, without its 64-bit products: those
+// and the row divisions were a fifth of the fused sweep's VALU time).  A row
+// of the x faces advances both face boxes by a row of n0 + 2 faces; passing
+// to the next plane, the y faces' rows (one fewer per plane) lag by one.
+template <typename T>
+struct FusedTile {
+    const T *fy, *fz;          // y, z face fluxes at row 0 of the tile, x face 0's cell
+    const T *u0, *acc_in;      // RK arrays at the tile's first staged cell
+    T *acc_out, *out;
+    int nx2;                   // n0 + 2
+};
+template <typename T>
+__device__ __forceinline__ FusedTile<T> fused_tile(const XFuse<T> &xf, long ubase, const XTile &X)
+{
+    FusedTile<T> B;
+    B.nx2 = X.nf + 1;
+    B.fy = xf.fy + 1 + (long)(X.jj0 - 1) * B.nx2 + (long)X.kk0 * xf.by.s[2];
+    B.fz = xf.fz + 1 + (long)X.jj0 * B.nx2 + (long)(X.kk0 - 1) * xf.bz.s[2];
+    B.u0 = xf.u0 + ubase;
+    B.acc_in = xf.acc_in + ubase;
+    B.acc_out = xf.acc_out + ubase;
+    B.out = xf.out + ubase;
+    return B;
+}
+
+template <typename T>
+__device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedTile<T> &B, long sv, int f, int s,
+                                                bool wrapped, uint32_t rel, FusedCell<T> &c)
+{
+    const int hs[5] = { 0, 1, 2, 3, 6 }, hv[5] = { 0, 1, 2, 3, 7 };
+    const uint32_t ry = f + __umul24(s - (wrapped ? 1 : 0), B.nx2), rz = f + __umul24(s, B.nx2);
+    const StageCoef &q = xf.c;
+    const bool u0 = (q.mode == 1 && q.s < 3) || q.mode == 2;
+    const bool ac = (q.mode == 1 && q.s > 0) || (q.mode == 2 && q.a1 != 0.0);
+#pragma unroll
+    for (int h = 0; h < 5; ++h) {
+        c.fyl[h] = ld32(B.fy + hs[h] * xf.by.sc, ry);
+        c.fyr[h] = ld32(B.fy + hs[h] * xf.by.sc + B.nx2, ry);
+        c.fzl[h] = ld32(B.fz + hs[h] * xf.bz.sc, rz);
+        c.fzr[h] = ld32(B.fz + hs[h] * xf.bz.sc + xf.bz.s[2], rz);
+        c.w0[h] = u0 ? ld32(B.u0 + hv[h] * sv, rel) : T(0);
+        c.w1[h] = ac ? ld32(B.acc_in + hv[h] * sv, rel) : T(0);
+    }
+}
+
+// The RK combination of that cell from its x fluxes and the loaded values
+// (fused_cell_rk's expressions: identical results).
+template <typename T>
+__device__ __forceinline__ void fused_tile_store(const XFuse<T> &xf, const FusedTile<T> &B, const Geom &G,
+                                                 const T *hx, int nh, int t, uint32_t rel, const FusedCell<T> &c)
+{
+    const int hv[5] = { 0, 1, 2, 3, 7 };
+    const T idx = T(G.idl[0]), idy = T(G.idl[1]), idz = T(G.idl[2]);
+    const StageCoef &q = xf.c;
+    const T bdt = T(q.bdt), cdt = T(q.cdt), a0 = T(q.a0), a1 = T(q.a1);
+#pragma unroll
+    for (int h = 0; h < 5; ++h) {
+        T L = T(0);
+        L -= (hx[h * nh + t + 1] - hx[h * nh + t]) * idx;
+        L -= (c.fyr[h] - c.fyl[h]) * idy;
+        L -= (c.fzr[h] - c.fzl[h]) * idz;
+        T *const out = B.out + hv[h] * G.sv, *const acc = B.acc_out + hv[h] * G.sv;
+        if (q.mode == 0) {
+            st32<T>(out, rel, L);
+        } else if (q.mode == 2) {
+            st32<T>(out, rel, q.a1 != 0.0 ? a0 * c.w0[h] + a1 * c.w1[h] + cdt * L : a0 * c.w0[h] + cdt * L);
+        } else if (q.s == 0) {
+            st32<T>(acc, rel, c.w0[h] + bdt * L);
+            st32<T>(out, rel, c.w0[h] + cdt * L);
+        } else if (q.s < 3) {
+            st32<T>(acc, rel, c.w1[h] + bdt * L);
+            st32<T>(out, rel, c.w0[h] + cdt * L);
+        } else {
+            st32<T>(out, rel, c.w1[h] + cdt * L);
+        }
     }
 }
 
@@ -1009,106 +1092,156 @@ constexpr int XFUSE_STRIDE = TILE * ROWS - 1;
 template <typename T, bool WZ = false, bool GLF = false, bool PRE = false>
 __device__ __forceinline__ void sweep_tile_xseg_fused(const T *__restrict__ u, T *__restrict__ flux,
                                                       const Geom &G, const FaceBox &F, const Phys &P,
-                                                      long tile, T *sq, T *hx, const XFuse<T> &xf)
+                                                      const XSegArgs &A, uint32_t tile, T *sq, T *hx,
+                                                      const XFuse<T> &xf)
 {
     stage_begin();
-    const XSeg X = xseg_setup(F, tile, XFUSE_STRIDE);
-    xseg_stage<T, PRE>(u, G, F, P, X, sq);
+    const int tid = threadIdx.x + TILE * threadIdx.y;
+    const XTile X = xtile(tile * XFUSE_STRIDE, A.total, A.nf, A.n1);
+    const long ubase = xseg_base(G, F, X);
+    const uint32_t jump = xseg_jump(G, F);
+    xseg_stage<T, PRE>(u + ubase, G.sv, jump, P.gamma, X, tid, sq);
     __syncthreads();
     stage_end();
-    const int tid = threadIdx.x + TILE * threadIdx.y;
     constexpr int NH = TILE * ROWS;
-    int pos[3], off;
-    const bool valid = xseg_face(F, X, tid, pos, off);
+    const bool valid = tid < X.nface;
     if (valid) {
         T out[7];
-        face_flux<T, false, WZ, GLF, true, PRE>(sq, XSEG_CELLS, off, 1, P.gamma, P.igm1, (T)P.eps, out, nullptr,
-                                                P.ag);
+        face_flux<T, false, WZ, GLF, true, PRE>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma, P.igm1,
+                                                (T)P.eps, out, nullptr, P.ag);
         hx[0 * NH + tid] = out[0];
         hx[1 * NH + tid] = out[1];
         hx[2 * NH + tid] = out[2];
         hx[3 * NH + tid] = out[3];
         hx[4 * NH + tid] = out[6];
-        const long total = (long)F.cnt[1] * F.cnt[2] * F.cnt[0];
-        if (tid < XFUSE_STRIDE || X.g0 + tid == total - 1) {
-            const long fi = F.idx(pos[0], pos[1], pos[2]);
-            flux[4 * F.sc + fi] = out[4];
-            flux[5 * F.sc + fi] = out[5];
+        if (tid < XFUSE_STRIDE || X.g0 + tid == A.total - 1) {
+            st32<T>(flux + 4 * F.sc + X.g0, tid, out[4]);
+            st32<T>(flux + 5 * F.sc + X.g0, tid, out[5]);
         }
     }
-    // the cell between faces tid and tid + 1 of one row (face f sits at f - 1/2)
-    const int i = pos[0], j = pos[1], k = pos[2];
-    const bool cell = valid && tid < XFUSE_STRIDE && tid + 1 < X.nface && i + 1 < F.cnt[0] && j >= 0 &&
-                      j < G.n[1] && k >= 0 && k < G.n[2];
+    // the cell between faces tid and tid + 1 of one row (face f sits at f - 1/2);
+    // interior rows are 1..n of the face box's transverse numbering
+    const int s = X.row_of(tid), f = X.face_x(tid, s), jj = X.jj(s), kk = X.kk(s);
+    const bool cell = valid && tid < XFUSE_STRIDE && tid + 1 < X.nface && f + 1 < X.nf && jj >= 1 &&
+                      jj <= G.n[1] && kk >= 1 && kk <= G.n[2];
+    const uint32_t rel = X.state_rel(X.cell_of(tid, s) + 3, jump);
+    const FusedTile<T> B = fused_tile(xf, ubase, X);
     FusedCell<T> fc;
-    if (cell) fused_cell_load<T>(xf, G, i, j, k, fc);
+    if (cell) fused_tile_load(xf, B, G.sv, f, s, s >= X.sw, rel, fc);
     __syncthreads();
-    if (cell) fused_cell_store<T>(xf, G, hx, NH, tid, fc);
+    if (cell) fused_tile_store(xf, B, G, hx, NH, tid, rel, fc);
 }
 
 // y or z sweep with PW positions of the transverse plane (x fastest) per
-// tile and 256/PW faces along the sweep, one face per thread: fewer
-// positions per tile stage fewer halo cells per face ((FT+5)/FT) in the
-// same LDS.
-template <int PW>
-__host__ __device__ constexpr int yz_cells() { return PW * (256 / PW + 5); }
+// tile and FT faces along the sweep: fewer positions per tile stage fewer
+// halo cells per face ((FT+5)/FT) in the same LDS.
+template <int PW, int FT>
+__host__ __device__ constexpr int yz_cells() { return PW * (FT + 5); }
 
-template <int DIR, int PW, typename T, bool LIN = false>
-__device__ __forceinline__ void yz_stage(const T *__restrict__ u, const Geom &G, const FaceBox &F,
-                                         const Phys &P, int ta, int tb, T *sq)
+// Scalar constants of a y/z sweep's tiles (launch constants).
+struct YZArgs {
+    FastDiv na, nb;            // positions along x, tiles along the sweep axis
+    uint32_t npos, ntile, per_xcd;
+};
+
+// Tile (ta, tb) of a y/z sweep, one thread's place in it.  Element offsets
+// within a tile are 32-bit: they stay within one variable (or face
+// component), and a context keeps at least three states of eight variables,
+// so that one variable holds at most 288 GB / 96 B = 3.0e9 < 2^32 elements.
+template <int DIR, int PW, int FT>
+struct YZTile {
+    static constexpr int N = DIR, A = 0, B = DIR == 1 ? 2 : 1;
+    uint32_t a0, b0;           // first position
+    int np, f0;                // positions of the tile, first face
+    int pl, fr;                // the thread's position and row within the tile
+    int q;                     // rows its position lies beyond (a0, b0)'s
+    __device__ __forceinline__ YZTile(const YZArgs &Y, uint32_t ta, uint32_t tb, int tid)
+    {
+        const uint32_t p0 = ta * PW;
+        b0 = Y.na.div(p0);
+        a0 = p0 - b0 * Y.na.d;
+        np = (int)(Y.npos - p0 < (uint32_t)PW ? Y.npos - p0 : (uint32_t)PW);
+        f0 = (int)tb * FT;
+        pl = tid % PW;
+        fr = PW == TILE ? __builtin_amdgcn_readfirstlane(tid / PW) : tid / PW;
+        q = yz_rows_on(a0, pl, Y.na, PW);
+    }
+    __device__ __forceinline__ int pos_a(const FaceBox &F, const YZArgs &Y) const
+    {
+        return F.lo[A] + (int)(a0 + pl - q * Y.na.d);
+    }
+    __device__ __forceinline__ int pos_b(const FaceBox &F) const { return F.lo[B] + (int)b0 + q; }
+    // offset of the thread's face row fr from the tile's first face in the flux box
+    __device__ __forceinline__ uint32_t face_rel(const FaceBox &F, const YZArgs &Y, int row) const
+    {
+        return (uint32_t)pl + (uint32_t)q * (uint32_t)(F.s[B] - Y.na.d) + (uint32_t)row * (uint32_t)F.s[N];
+    }
+    __device__ __forceinline__ long face_base(const FaceBox &F) const
+    {
+        return (long)a0 + (long)b0 * F.s[B] + (long)f0 * F.s[N];
+    }
+};
+
+template <int DIR, int PW, int FT, typename T, bool LIN = false>
+__device__ __forceinline__ void yz_stage(const T *__restrict__ u, const Geom &G, const FaceBox &F, double gamma,
+                                         const YZArgs &Y, const YZTile<DIR, PW, FT> &t, T *sq)
 {
-    constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3;
-    constexpr int FTY = 256 / PW, NC = yz_cells<PW>();
-    constexpr int A = 0, B = (DIR == 1) ? 2 : 1;
+    constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3, B = DIR == 1 ? 2 : 1;
+    constexpr int NC = yz_cells<PW, FT>(), RP = 256 / PW;
     const int cm[8] = { 0, 1 + N, 1 + T1, 1 + T2, 4 + N, 4 + T1, 4 + T2, 7 };
-    const int tid = threadIdx.x + TILE * threadIdx.y;
-    const int nlast = G.n[N] + 2;
-    const int npos = F.cnt[A] * F.cnt[B];
-    const int f0 = tb * FTY;
+    const T *const ub = u + (G.base + F.lo[0] + (long)t.a0 + (long)(F.lo[B] + (int)t.b0) * G.s[B] +
+                             (long)(t.f0 - 3) * G.s[N]);
+    const int rows = min(FT + 5, G.n[N] + 6 - t.f0);     // the state's rows end at n + 2
+    if (t.pl >= t.np) return;
+    const uint32_t rel = (uint32_t)t.pl + (uint32_t)t.q * (uint32_t)(G.s[B] - Y.na.d);
     // one cell after another (a thread's loads first, as stage_tile does,
     // measured 2 % slower here)
-    for (int c = tid; c < NC; c += 256) {
-        const int rr = c / PW, pc = c - rr * PW;
-        const int p = ta * PW + pc, y = f0 - 3 + rr;
-        if (p < npos && y <= nlast) {
-            const int ca = F.lo[A] + p % F.cnt[A], cb = F.lo[B] + p / F.cnt[A];
-            const long id = G.base + ca * G.s[A] + cb * G.s[B] + (long)y * G.s[N];
-            stage_cell<T, false, LIN>(u, id, G.sv, cm, P.gamma, sq + c, NC);
+    for (int r = t.fr; r < rows; r += RP) {
+        const uint32_t e = rel + (uint32_t)r * (uint32_t)G.s[N];
+        T w[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) w[v] = uniform(ub + cm[v] * G.sv)[e];
+        stage_values<T, false, LIN>(w, gamma, sq + (r * PW + t.pl), NC);
+    }
+}
+
+template <int DIR, int PW, int FT, typename T, bool WZ = false, bool GLF = false>
+__device__ __forceinline__ void sweep_tile_yz(const T *__restrict__ u, T *__restrict__ flux,
+                                              const Geom &G, const FaceBox &F, const Phys &P, const YZArgs &Y,
+                                              uint32_t ta, uint32_t tb, T *sq)
+{
+    constexpr int T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3;
+    stage_begin();
+    const YZTile<DIR, PW, FT> t(Y, ta, tb, threadIdx.x + TILE * threadIdx.y);
+    yz_stage<DIR, PW, FT, T>(u, G, F, P.gamma, Y, t, sq);
+    __syncthreads();
+    stage_end();
+    T *const fb = flux + t.face_base(F);
+    for (int r = t.fr; r < FT; r += 256 / PW) {
+        if (t.pl < t.np && t.f0 + r < F.cnt[DIR]) {
+            T out[7];
+            face_flux<T, false, WZ, GLF>(sq, yz_cells<PW, FT>(), r * PW + t.pl, PW, P.gamma, P.igm1, (T)P.eps, out,
+                                         nullptr, P.ag);
+            const uint32_t rel = t.face_rel(F, Y, r);
+            const int gc[7] = { 0, 1 + DIR, 1 + T1, 1 + T2, 4, 5, 6 };   // sweep frame -> grid component
+#pragma unroll
+            for (int c = 0; c < 7; ++c) uniform(fb + gc[c] * F.sc)[rel] = out[c];
         }
     }
 }
 
-// Face of thread tid: position and LDS offset of its cell i-2 (stride PW).
-template <int DIR, int PW>
-__device__ __forceinline__ bool yz_face(const FaceBox &F, int ta, int tb, int tid, int (&pos)[3], int &off)
+template <int DIR, int PW, int FT>
+__host__ inline YZArgs yz_args(const FaceBox &F, uint32_t nxcd)
 {
-    constexpr int FTY = 256 / PW, N = DIR, A = 0, B = (DIR == 1) ? 2 : 1;
-    const int npos = F.cnt[A] * F.cnt[B];
-    const int fr = tid / PW, pl = tid - fr * PW;
-    const int p = ta * PW + pl;
-    pos[A] = F.lo[A] + p % F.cnt[A];
-    pos[B] = F.lo[B] + p / F.cnt[A];
-    pos[N] = tb * FTY + fr;
-    off = fr * PW + pl;
-    return p < npos && pos[N] < F.cnt[N];
-}
-
-template <int DIR, int PW, typename T, bool WZ = false, bool GLF = false>
-__device__ __forceinline__ void sweep_tile_yz(const T *__restrict__ u, T *__restrict__ flux,
-                                              const Geom &G, const FaceBox &F, const Phys &P,
-                                              int ta, int tb, T *sq)
-{
-    stage_begin();
-    yz_stage<DIR, PW, T>(u, G, F, P, ta, tb, sq);
-    __syncthreads();
-    stage_end();
-    int pos[3], off;
-    if (yz_face<DIR, PW>(F, ta, tb, threadIdx.x + TILE * threadIdx.y, pos, off)) {
-        T out[7];
-        face_flux<T, false, WZ, GLF>(sq, yz_cells<PW>(), off, PW, P.gamma, P.igm1, (T)P.eps, out, nullptr,
-                                     P.ag);
-        store_face<DIR, T>(flux, F, pos, out);
-    }
+    constexpr int B = DIR == 1 ? 2 : 1;
+    YZArgs Y;
+    Y.npos = (uint32_t)F.cnt[0] * (uint32_t)F.cnt[B];
+    Y.na = FastDiv((uint32_t)F.cnt[0]);
+    const uint32_t na = (Y.npos + PW - 1) / PW, nb = (uint32_t)(F.cnt[DIR] + FT - 1) / FT;
+    Y.nb = FastDiv(nb);
+    Y.ntile = na * nb;
+    Y.per_xcd = (Y.ntile + nxcd - 1) / nxcd;
+    return Y;
 }
 
 // Number of tiles (ta, tb) of a sweep.
