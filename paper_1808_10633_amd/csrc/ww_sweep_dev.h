@@ -10,12 +10,15 @@
 //
 // Per interface:
 //   1. the six stencil cells i-2..i+3 are read from LDS; their physical
-//      fluxes are formed; the central combination (-F_{i-1} + 7F_i + 7F_{i+1}
-//      - F_{i+2})/12 (kept doubled) and the five cell-to-cell differences of F
-//      and U are taken (eq. 1 is linear in these; the projection rows carry the
-//      1/2 of the Lax-Friedrichs split, a power-of-two scaling), and the
-//      largest |lambda^s| per field over the stencil gives the local
-//      Lax-Friedrichs speed;
+//      fluxes are formed; the mean flux of cells i and i+1 and the five
+//      cell-to-cell differences of F and U are taken (eq. 1 is linear in
+//      these; the projection rows carry the 1/2 of the Lax-Friedrichs split, a
+//      power-of-two scaling), and the largest |lambda^s| per field over the
+//      stencil gives the local Lax-Friedrichs speed.  The central term of eq.
+//      (1) is (-F_{i-1} + 7F_i + 7F_{i+1} - F_{i+2})/12 = (F_i + F_{i+1})/2
+//      + (DF_{i-1/2} - DF_{i+3/2})/12: its first part sums over the fields to
+//      itself (R L = I) and is added to the back-projected rest unprojected,
+//      its second uses the differences projected for the weights;
 //   2. the mean state of cells i and i+1 (arithmetic mean of the primitive
 //      variables) gives the seven-wave eigen-system with the Roe-Balsara
 //      normalisation; the left eigenvectors are applied as
@@ -123,38 +126,41 @@ __device__ __forceinline__ void stage_end() { __builtin_amdgcn_s_setprio(0); }
 // d = (1, 6, 3)/10 and the 1/3, 1/6 of eq. (2) into the (epsilon + IS_k).
 constexpr double SQ18 = 4.2426406871192851464, SQ12 = 3.4641016151377545870;
 
-// phi_N of eq. (2) with the weights of eqs. (3)-(7).  ee = (epsilon/4,
-// sqrt(18) epsilon/4, sqrt(12) epsilon/4).
+// The nonlinear part of phi_N of eq. (2) with the weights of eqs. (3)-(7),
+// phi_N + (b - 2c + d)/12 = omega_0 (a-2b+c)/3 + omega_2 (b-2c+d)/6.
+// ee = (epsilon/4, sqrt(18) epsilon/4, sqrt(12) epsilon/4).
+// With r_0 = sqrt(18) q_0, r_1 = q_1, r_2 = sqrt(12) q_2 (q_k = (epsilon +
+// IS_k)/4, as in phi_n) and R_k = r_k^2: A = R_1 R_2, B = R_0 R_1, C = R_0 R_2
+// are 12, 6 and 36 times the common-denominator numerators of alpha_0,
+// alpha_2, alpha_1, so omega_0 = 3A / S and omega_2 = 6B / S with
+// S = 3A + 6B + C, and the result is (A (a-2b+c) + B (b-2c+d)) / S (one
+// reciprocal, no separate scaling of the differences), returned as num / S.
+template <typename T>
+__device__ __forceinline__ void phi_fold(T a, T b, T c, T d, const T (&ee)[3], T &num, T &inv)
+{
+    const T b2 = b * b, c2 = c * c;
+    T r0 = fma(a, fma(T(4 * SQ18), a, T(-11 * SQ18) * b), fma(T(10 * SQ18), b2, ee[1]));
+    T r1 = fma(T(4), b2 + c2, fma(T(-5), b * c, ee[0]));
+    T r2 = fma(d, fma(T(4 * SQ12), d, T(-11 * SQ12) * c), fma(T(10 * SQ12), c2, ee[2]));
+    if constexpr (sizeof(T) == 4) {
+        // FP32: keep the products of the squares in range (see phi_n)
+        const T s = __builtin_amdgcn_rcpf(fmax(r0, fmax(r1, r2)));
+        r0 *= s; r1 *= s; r2 *= s;
+    }
+    r0 *= r0; r1 *= r1; r2 *= r2;
+    const T A = r1 * r2, B = r0 * r1;
+    inv = frcp_w(fma(T(3), A, fma(T(6), B, r0 * r2)));
+    const T y = fma(T(-2), c, b) + d;
+    num = fma(A, fma(T(-2), b, a) + c, B * y);
+}
+
+// phi_N of eq. (2) for the variants:
 // WZ: the WENO-Z weights of Borges et al. (2008) instead (exponent 1, an
 // ablation): alpha_k = d_k (1 + tau5 / (eps + IS_k)), tau5 = |IS_0 - IS_2|.
 // LBL: also the largest deviation of a weight from the linear weights.
-// FOLD: the folded form below (fewer instructions; two more values live).
-template <typename T, bool LBL = false, bool WZ = false, bool FOLD = true>
-__device__ __forceinline__ T phi_n(T a, T b, T c, T d, const T (&ee)[3], T *dev = nullptr)
+template <typename T, bool LBL, bool WZ>
+__device__ __forceinline__ T phi_n(T a, T b, T c, T d, const T (&ee)[3], T *dev)
 {
-    if constexpr (!WZ && !LBL && FOLD) {
-        // With r_0 = sqrt(18) q_0, r_1 = q_1, r_2 = sqrt(12) q_2 (q_k as
-        // below) and R_k = r_k^2: A = R_1 R_2, B = R_0 R_1, C = R_0 R_2 are
-        // 12, 6 and 36 times the common-denominator numerators of alpha_0,
-        // alpha_2, alpha_1, so omega_0 = 3A / S and omega_2 = 6B / S with
-        // S = 3A + 6B + C, and eq. (2) becomes
-        //   phi = (A (a-2b+c) + B (b-2c+d)) / S - (b-2c+d)/12
-        // (one reciprocal, no separate scaling of the differences).
-        const T b2 = b * b, c2 = c * c;
-        T r0 = fma(a, fma(T(4 * SQ18), a, T(-11 * SQ18) * b), fma(T(10 * SQ18), b2, ee[1]));
-        T r1 = fma(T(4), b2 + c2, fma(T(-5), b * c, ee[0]));
-        T r2 = fma(d, fma(T(4 * SQ12), d, T(-11 * SQ12) * c), fma(T(10 * SQ12), c2, ee[2]));
-        if constexpr (sizeof(T) == 4) {
-            // FP32: keep the products of the squares in range (see below)
-            const T s = __builtin_amdgcn_rcpf(fmax(r0, fmax(r1, r2)));
-            r0 *= s; r1 *= s; r2 *= s;
-        }
-        r0 *= r0; r1 *= r1; r2 *= r2;
-        const T A = r1 * r2, B = r0 * r1;
-        const T inv = frcp_w(fma(T(3), A, fma(T(6), B, r0 * r2)));
-        const T y = fma(T(-2), c, b) + d;
-        return fma(fma(A, fma(T(-2), b, a) + c, B * y), inv, T(-1.0 / 12.0) * y);
-    }
     const T e4 = ee[0];
     // Smoothness indicators of eqs. (5)-(7), expanded into the quadratic forms
     // IS_0 = 16a^2 - 44ab + 40b^2, IS_1 = 16b^2 - 20bc + 16c^2,
@@ -200,12 +206,14 @@ __device__ __forceinline__ T phi_n(T a, T b, T c, T d, const T (&ee)[3], T *dev 
     return fma(inv, fma(n0, x3, n2 * y6), T(-0.5) * y6);
 }
 
-// eq. (1) for one field.  cc: projected central term; df, du: projected flux
-// and state differences (k = 0..4 at i-3/2 .. i+5/2), both already carrying
-// the 1/2 of the Lax-Friedrichs split; al: LF speed.
-template <typename T, bool LBL = false, bool WZ = false, bool FOLD = true>
-__device__ __forceinline__ T weno_field(T cc, const T (&df)[5], const T (&du)[5], T al, const T (&ee)[3],
-                                        T *dev = nullptr)
+// eq. (1) for one field, less the projected mean flux l (F_i + F_{i+1})/2.
+// df, du: projected flux and state differences (k = 0..4 at i-3/2 .. i+5/2),
+// both already carrying the 1/2 of the Lax-Friedrichs split; al: LF speed.
+// The remaining central part (df_1 - df_3)/6 and the linear parts of the two
+// phi_N, (dp_1 - 2dp_2 + dp_3)/12 and -(dm_1 - 2dm_2 + dm_3)/12, add up to
+// (dp_1 - dp_2 + dm_2 - dm_3)/6.
+template <typename T, bool LBL = false, bool WZ = false>
+__device__ __forceinline__ T weno_field(const T (&df)[5], const T (&du)[5], T al, const T (&ee)[3], T *dev = nullptr)
 {
     T dp[5], dm[5];
 #pragma unroll
@@ -213,26 +221,38 @@ __device__ __forceinline__ T weno_field(T cc, const T (&df)[5], const T (&du)[5]
         dp[k] = fma(al, du[k], df[k]);
         dm[k] = fma(-al, du[k], df[k]);
     }
-    return cc - phi_n<T, LBL, WZ, FOLD>(dp[0], dp[1], dp[2], dp[3], ee, dev)
-              + phi_n<T, LBL, WZ, FOLD>(dm[4], dm[3], dm[2], dm[1], ee, dev);
+    if constexpr (LBL || WZ) {
+        return T(1.0 / 6.0) * (df[1] - df[3]) - phi_n<T, LBL, WZ>(dp[0], dp[1], dp[2], dp[3], ee, dev)
+                                              + phi_n<T, LBL, WZ>(dm[4], dm[3], dm[2], dm[1], ee, dev);
+    } else {
+        T np, ip, nm, im;
+        phi_fold<T>(dp[0], dp[1], dp[2], dp[3], ee, np, ip);
+        phi_fold<T>(dm[4], dm[3], dm[2], dm[1], ee, nm, im);
+        const T lin = T(1.0 / 6.0) * ((dp[1] - dp[2]) + (dm[2] - dm[3]));
+        return fma(nm, im, fma(-np, ip, lin));
+    }
 }
 
 // Sweep-frame physical flux of one cell (rho, mn, mt1, mt2, Bt1, Bt2, E
 // components) from its conserved variables w, pressure p and 1/rho; returns
-// the normal velocity.
+// the normal velocity.  The fused operations are written out and nothing else
+// is contracted, here and where the fluxes are differenced: the values then
+// do not depend on what else a kernel does with them, and kernels that compute
+// one flux two ways (fused and separate update) agree bit for bit.
 template <typename T>
 __device__ __forceinline__ T cell_flux(const T (&w)[8], T p, T ir, T (&F)[7])
 {
+#pragma clang fp contract(off)
     const T mn = w[1], m1 = w[2], m2 = w[3], bn = w[4], b1 = w[5], b2 = w[6], e = w[7];
     const T vn = mn * ir, v1 = m1 * ir, v2 = m2 * ir;
-    const T pt = p + T(0.5) * (bn * bn + b1 * b1 + b2 * b2);
+    const T pt = fma(T(0.5), fma(b2, b2, fma(b1, b1, bn * bn)), p);
     F[0] = mn;
-    F[1] = mn * vn + pt - bn * bn;
-    F[2] = m1 * vn - bn * b1;
-    F[3] = m2 * vn - bn * b2;
-    F[4] = vn * b1 - v1 * bn;
-    F[5] = vn * b2 - v2 * bn;
-    F[6] = (e + pt) * vn - bn * (vn * bn + v1 * b1 + v2 * b2);
+    F[1] = fma(-bn, bn, fma(mn, vn, pt));
+    F[2] = fma(m1, vn, -(bn * b1));
+    F[3] = fma(m2, vn, -(bn * b2));
+    F[4] = fma(vn, b1, -(v1 * bn));
+    F[5] = fma(vn, b2, -(v2 * bn));
+    F[6] = fma(e + pt, vn, -(bn * fma(v2, b2, fma(v1, b1, vn * bn))));
     return vn;
 }
 
@@ -345,51 +365,41 @@ __device__ __forceinline__ void stage_tile(const T *__restrict__ u, long sv, con
 // from the linear weights (the label of a troubled interface).
 // GLF: the LF speed of field s is ag[s] (global speeds of the sweep, an
 // ablation) instead of the largest |lambda^s| over the six cells.
-// FOLD: phi_n's folded form (off where the register budget is exhausted).
 // PRE: the cells were staged with their fluxes and v_n (NQ_PRE quantities).
-template <typename T, bool LBL = false, bool WZ = false, bool GLF = false, bool FOLD = true, bool PRE = false>
+// STASH: the mean flux waits in LDS (the thread's own 7 values, a block apart).
+template <typename T, bool LBL = false, bool WZ = false, bool GLF = false, bool PRE = false, bool STASH = false>
 __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int off, int cstr,
                                           double gamma, double igm1, T eps, T (&out)[7],
-                                          T *dev = nullptr, const double *ag = nullptr)
+                                          T *dev = nullptr, const double *ag = nullptr, T *stash = nullptr)
 {
 #define QQ(q, j) sq[(q) * qs + off + (j) * cstr]
-    T C[7], dY[5][7], dZ[5][7], am[7];
+    T Fs[7], dY[5][7], dZ[5][7], am[7];
     T Fp[7], Up[7];
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-        T vn, cf, cs, ca, Fj[7], Uj[7];
+#pragma clang fp contract(off)
+        T vn, Fj[7];
+        const T w[8] = { QQ(0, j), QQ(1, j), QQ(2, j), QQ(3, j), QQ(4, j), QQ(5, j), QQ(6, j), QQ(7, j) };
         if constexpr (PRE) {
-            const T r = QQ(0, j), mn = QQ(1, j), m1 = QQ(2, j), m2 = QQ(3, j);
-            const T b1 = QQ(5, j), b2 = QQ(6, j), e = QQ(7, j);
-            vn = QQ(13, j); cf = QQ(10, j); cs = QQ(11, j); ca = QQ(12, j);
-            Fj[0] = mn;
+            vn = QQ(13, j);
+            Fj[0] = w[1];
 #pragma unroll
             for (int c = 1; c < 7; ++c) Fj[c] = QQ(13 + c, j);
-            Uj[0] = r; Uj[1] = mn; Uj[2] = m1; Uj[3] = m2; Uj[4] = b1; Uj[5] = b2; Uj[6] = e;
         } else {
-            // cell_flux's expressions, written out and in this order (the FP64
-            // kernels' register allocation at 256 VGPRs follows the order of
-            // the LDS reads)
-            T r = QQ(0, j), mn = QQ(1, j), m1 = QQ(2, j), m2 = QQ(3, j);
-            T bn = QQ(4, j), b1 = QQ(5, j), b2 = QQ(6, j), e = QQ(7, j);
-            T p = QQ(8, j), ir = QQ(9, j);
-            cf = QQ(10, j); cs = QQ(11, j); ca = QQ(12, j);
-            vn = mn * ir;
-            T v1 = m1 * ir, v2 = m2 * ir;
-            T pt = p + T(0.5) * (bn * bn + b1 * b1 + b2 * b2);
-            Fj[0] = mn; Fj[1] = mn * vn + pt - bn * bn; Fj[2] = m1 * vn - bn * b1; Fj[3] = m2 * vn - bn * b2;
-            Fj[4] = vn * b1 - v1 * bn; Fj[5] = vn * b2 - v2 * bn;
-            Fj[6] = (e + pt) * vn - bn * (vn * bn + v1 * b1 + v2 * b2);
-            Uj[0] = r; Uj[1] = mn; Uj[2] = m1; Uj[3] = m2; Uj[4] = b1; Uj[5] = b2; Uj[6] = e;
+            vn = cell_flux(w, QQ(8, j), QQ(9, j), Fj);
         }
+        const T cf = QQ(10, j), cs = QQ(11, j), ca = QQ(12, j);
+        const T Uj[7] = { w[0], w[1], w[2], w[3], w[5], w[6], w[7] };
         T lam[7] = { fabs(vn - cf), fabs(vn - ca), fabs(vn - cs), fabs(vn),
                      fabs(vn + cs), fabs(vn + ca), fabs(vn + cf) };
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
             am[c] = (j == 0) ? lam[c] : fmax(am[c], lam[c]);
-            if (j == 1) C[c] = -Fj[c];
-            if (j == 2 || j == 3) C[c] += T(7) * Fj[c];
-            if (j == 4) C[c] = (C[c] - Fj[c]) * T(1.0 / 6.0);   // twice the central term
+            if (j == 3) {                                  // twice the mean flux
+                const T sum = Fp[c] + Fj[c];
+                if constexpr (STASH) stash[c * TILE * ROWS] = sum;
+                else Fs[c] = sum;
+            }
             if (j > 0) { dY[j - 1][c] = Fj[c] - Fp[c]; dZ[j - 1][c] = Uj[c] - Up[c]; }
             Fp[c] = Fj[c];
             Up[c] = Uj[c];
@@ -412,11 +422,12 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
     double b2b = 0.5 * ((double)QQ(6, 2) + (double)QQ(6, 3));
     double pb = 0.5 * ((double)QQ(8, 2) + (double)QQ(8, 3));
 #undef QQ
-    // FP32 storage: 1/rho, a and 1/a^2, c_f and 1/c_f^2 from one reciprocal
-    // square root each, and c_s = a c_A / c_f with c_A = |B_n| rho^-1/2.  The
-    // FP64 kernels sit at the 256-VGPR limit, where the longer live ranges of
-    // that form spill; they take each quantity separately.
-    constexpr bool LEAN = sizeof(T) == 4;
+    // 1/rho, a and 1/a^2, c_f and 1/c_f^2 from one reciprocal square root
+    // each, and c_s = a c_A / c_f with c_A = |B_n| rho^-1/2 (four fewer roots
+    // and reciprocals, 1 % of the FP64 y sweep).  The FP64 WENO-Z kernels have
+    // no registers left for the longer live ranges of that form; they take
+    // each quantity separately.
+    constexpr bool LEAN = sizeof(T) == 4 || !WZ;
     double irb, isr = 0.0;
     if constexpr (LEAN) { isr = frsq(rb); irb = isr * isr; }
     else irb = frcp(rb);
@@ -492,7 +503,6 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
         T pB = e1 * X[4] + e2 * X[5], qB = e1 * X[5] - e2 * X[4];
         X[1] = w1; X[2] = pv; X[3] = qv; X[4] = pB; X[5] = qB; X[6] = w6;
     };
-    xf(C);
 #pragma unroll
     for (int k = 0; k < 5; ++k) { xf(dY[k]); xf(dZ[k]); }
 
@@ -503,17 +513,16 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
     // One wave pair (sigma = -1 field index lo, sigma = +1 field index hi).
     // proj(X, odd, even) gives the odd and even parts of the row applied to X.
     auto pair = [&](auto proj, int lo, int hi, T &S, T &D) {
-        T oc, ec, odf[5], edf[5], odu[5], edu[5];
-        proj(C, oc, ec);
+        T odf[5], edf[5], odu[5], edu[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) { proj(dY[k], odf[k], edf[k]); proj(dZ[k], odu[k], edu[k]); }
         T df[5], du[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) { df[k] = edf[k] + odf[k]; du[k] = edu[k] + odu[k]; }
-        T fplus = weno_field<T, LBL, WZ, FOLD>(ec + oc, df, du, am[hi], ee, dev);
+        T fplus = weno_field<T, LBL, WZ>(df, du, am[hi], ee, dev);
 #pragma unroll
         for (int k = 0; k < 5; ++k) { df[k] = edf[k] - odf[k]; du[k] = edu[k] - odu[k]; }
-        T fminus = weno_field<T, LBL, WZ, FOLD>(ec - oc, df, du, am[lo], ee, dev);
+        T fminus = weno_field<T, LBL, WZ>(df, du, am[lo], ee, dev);
         S = fplus + fminus;
         D = fplus - fminus;
     };
@@ -541,27 +550,31 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
     G[5] += T(sr) * S;
     // entropy (field 3)
     {
-        T cc = kh * (C[0] - ke6 * C[6]), df[5], du[5];
+        T df[5], du[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
             df[k] = kh * (dY[k][0] - ke6 * dY[k][6]);
             du[k] = kh * (dZ[k][0] - ke6 * dZ[k][6]);
         }
-        G[0] += weno_field<T, LBL, WZ, FOLD>(cc, df, du, am[3], ee, dev);
+        G[0] += weno_field<T, LBL, WZ>(df, du, am[3], ee, dev);
     }
 
-    // back to (vt1, vt2), (Bt1, Bt2) and through dU/dW
+    // back to (vt1, vt2), (Bt1, Bt2) and through dU/dW, onto the mean flux
     T gv1 = e1 * G[2] + e2 * G[3], gv2 = e2 * G[2] - e1 * G[3];
     T gb1 = e1 * G[4] - e2 * G[5], gb2 = e2 * G[4] + e1 * G[5];
     const T trb = T(rb);
-    out[0] = G[0];
-    out[1] = tv * G[0] + trb * G[1];
-    out[2] = t1 * G[0] + trb * gv1;
-    out[3] = t2 * G[0] + trb * gv2;
-    out[4] = gb1;
-    out[5] = gb2;
-    out[6] = th * G[0] + trb * (tv * G[1] + t1 * gv1 + t2 * gv2) + tb1 * gb1 + tb2 * gb2
-           + G[6] * T(igm1);
+    if constexpr (STASH) {
+#pragma unroll
+        for (int c = 0; c < 7; ++c) Fs[c] = stash[c * TILE * ROWS];
+    }
+    out[0] = fma(T(0.5), Fs[0], G[0]);
+    out[1] = fma(T(0.5), Fs[1], tv * G[0] + trb * G[1]);
+    out[2] = fma(T(0.5), Fs[2], t1 * G[0] + trb * gv1);
+    out[3] = fma(T(0.5), Fs[3], t2 * G[0] + trb * gv2);
+    out[4] = fma(T(0.5), Fs[4], gb1);
+    out[5] = fma(T(0.5), Fs[5], gb2);
+    out[6] = fma(T(0.5), Fs[6], th * G[0] + trb * (tv * G[1] + t1 * gv1 + t2 * gv2) + tb1 * gb1 + tb2 * gb2
+                                    + G[6] * T(igm1));
 }
 
 // Linear fifth-order component-wise flux of the six staged cells (the cheap
@@ -988,7 +1001,7 @@ __device__ __forceinline__ void sweep_tile_xseg(const T *__restrict__ u, T *__re
     stage_end();
     if (tid < X.nface) {
         T out[7];
-        face_flux<T, false, WZ, GLF, true, PRE>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma, P.igm1,
+        face_flux<T, false, WZ, GLF, PRE>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma, P.igm1,
                                                 (T)P.eps, out, nullptr, P.ag);
         // faces are stored in the order of their numbers; the x frame is the grid's
         T *const fb = flux + X.g0;
@@ -1088,6 +1101,10 @@ __device__ __forceinline__ void fused_tile_store(const XFuse<T> &xf, const Fused
 // combination of rho, m, E.  Only the transverse-B fluxes (slots 4, 5) are
 // stored, once per face (the overlapping face by the next tile).
 constexpr int XFUSE_STRIDE = TILE * ROWS - 1;
+// The FP64 fused sweep keeps the mean flux (14 VGPRs) in hx during the fields:
+// it spilled 6 VGPRs without (6 % slower); the other FP64 sweeps fit.
+template <typename T> constexpr bool stash_x() { return sizeof(T) == 8; }
+template <typename T> constexpr int hx_slots() { return stash_x<T>() ? 7 : 5; }
 
 template <typename T, bool WZ = false, bool GLF = false, bool PRE = false>
 __device__ __forceinline__ void sweep_tile_xseg_fused(const T *__restrict__ u, T *__restrict__ flux,
@@ -1095,41 +1112,47 @@ __device__ __forceinline__ void sweep_tile_xseg_fused(const T *__restrict__ u, T
                                                       const XSegArgs &A, uint32_t tile, T *sq, T *hx,
                                                       const XFuse<T> &xf)
 {
-    stage_begin();
-    const int tid = threadIdx.x + TILE * threadIdx.y;
-    const XTile X = xtile(tile * XFUSE_STRIDE, A.total, A.nf, A.n1);
-    const long ubase = xseg_base(G, F, X);
-    const uint32_t jump = xseg_jump(G, F);
-    xseg_stage<T, PRE>(u + ubase, G.sv, jump, P.gamma, X, tid, sq);
-    __syncthreads();
-    stage_end();
     constexpr int NH = TILE * ROWS;
-    const bool valid = tid < X.nface;
-    if (valid) {
-        T out[7];
-        face_flux<T, false, WZ, GLF, true, PRE>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma, P.igm1,
-                                                (T)P.eps, out, nullptr, P.ag);
-        hx[0 * NH + tid] = out[0];
-        hx[1 * NH + tid] = out[1];
-        hx[2 * NH + tid] = out[2];
-        hx[3 * NH + tid] = out[3];
-        hx[4 * NH + tid] = out[6];
-        if (tid < XFUSE_STRIDE || X.g0 + tid == A.total - 1) {
-            st32<T>(flux + 4 * F.sc + X.g0, tid, out[4]);
-            st32<T>(flux + 5 * F.sc + X.g0, tid, out[5]);
+    stage_begin();
+    {
+        const int tid = threadIdx.x + TILE * threadIdx.y;
+        const XTile X = xtile(tile * XFUSE_STRIDE, A.total, A.nf, A.n1);
+        xseg_stage<T, PRE>(u + xseg_base(G, F, X), G.sv, xseg_jump(G, F), P.gamma, X, tid, sq);
+        __syncthreads();
+        stage_end();
+        if (tid < X.nface) {
+            T out[7];
+            face_flux<T, false, WZ, GLF, PRE, stash_x<T>()>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma,
+                                                            P.igm1, (T)P.eps, out, nullptr, P.ag, hx + tid);
+            hx[0 * NH + tid] = out[0];
+            hx[1 * NH + tid] = out[1];
+            hx[2 * NH + tid] = out[2];
+            hx[3 * NH + tid] = out[3];
+            hx[4 * NH + tid] = out[6];
+            if (tid < XFUSE_STRIDE || X.g0 + tid == A.total - 1) {
+                st32<T>(flux + 4 * F.sc + X.g0, tid, out[4]);
+                st32<T>(flux + 5 * F.sc + X.g0, tid, out[5]);
+            }
         }
     }
-    // the cell between faces tid and tid + 1 of one row (face f sits at f - 1/2);
-    // interior rows are 1..n of the face box's transverse numbering
-    const int s = X.row_of(tid), f = X.face_x(tid, s), jj = X.jj(s), kk = X.kk(s);
-    const bool cell = valid && tid < XFUSE_STRIDE && tid + 1 < X.nface && f + 1 < X.nf && jj >= 1 &&
-                      jj <= G.n[1] && kk >= 1 && kk <= G.n[2];
-    const uint32_t rel = X.state_rel(X.cell_of(tid, s) + 3, jump);
+    // The cell between faces t and t + 1 of one row (face f sits at f - 1/2);
+    // interior rows are 1..n of the face box's transverse numbering.  Tile
+    // and thread numbers are opaque to the compiler here: the tile's rows and
+    // bases are formed again instead of staying in registers through the
+    // flux, where the FP64 form has none left.
+    int t = threadIdx.x + TILE * threadIdx.y;
+    asm volatile("" : "+v"(t), "+s"(tile));
+    const XTile X = xtile(tile * XFUSE_STRIDE, A.total, A.nf, A.n1);
+    const long ubase = xseg_base(G, F, X);
+    const int s = X.row_of(t), f = X.face_x(t, s), jj = X.jj(s), kk = X.kk(s);
+    const bool cell = t + 1 < X.nface && t < XFUSE_STRIDE && f + 1 < X.nf && jj >= 1 && jj <= G.n[1] && kk >= 1 &&
+                      kk <= G.n[2];
+    const uint32_t rel = X.state_rel(X.cell_of(t, s) + 3, xseg_jump(G, F));
     const FusedTile<T> B = fused_tile(xf, ubase, X);
     FusedCell<T> fc;
     if (cell) fused_tile_load(xf, B, G.sv, f, s, s >= X.sw, rel, fc);
     __syncthreads();
-    if (cell) fused_tile_store(xf, B, G, hx, NH, tid, rel, fc);
+    if (cell) fused_tile_store(xf, B, G, hx, NH, t, rel, fc);
 }
 
 // y or z sweep with PW positions of the transverse plane (x fastest) per
