@@ -24,16 +24,35 @@ namespace {
 
 constexpr int RB = 256;
 
+// The patch number comes from a shared counter through LDS, so the compiler
+// takes everything read by it for per-lane data: geometry, strides and loop
+// bounds then sit in vector registers and every address is vector 64-bit
+// arithmetic.  The descriptor is read through the constant address space at a
+// scalar index instead (it never changes during the kernel).
+__device__ __forceinline__ PatchDesc load_desc(const PatchDesc *pd, int p)
+{
+    typedef const unsigned long long __attribute__((address_space(4))) *cptr;
+    constexpr int NW = sizeof(PatchDesc) / 8;
+    unsigned long long w[NW];
+    cptr q = (cptr)(pd + p);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) w[i] = q[i];
+    PatchDesc D;
+    __builtin_memcpy(&D, w, sizeof D);
+    return D;
+}
+
 // CFL time step of one patch (FP64 reduction in fixed order) and its count
 // of non-physical cells.
 template <typename T>
-__device__ __forceinline__ void patch_dt(const T *__restrict__ u, const Geom &G, double gamma,
+__device__ __forceinline__ void patch_dt(const T *__restrict__ u, const PatchDesc &D, const Geom &G, double gamma,
                                          double cfl, double *dt_out, int32_t *flag_out)
 {
     __shared__ double smx[sw::ROWS];
     __shared__ int sfl[sw::ROWS];
     const int tid = threadIdx.x + sw::TILE * threadIdx.y;
     const int ncell = G.n[0] * G.n[1] * G.n[2];     // < 2^31 for edges of at most 1024
+    const T *const ub = u + G.base;
     double mx = 0.0;
     int bad = 0;
     // DT_IT cells per thread and pass: all their loads first, then the
@@ -47,13 +66,10 @@ __device__ __forceinline__ void patch_dt(const T *__restrict__ u, const Geom &G,
         for (int it = 0; it < DT_IT; ++it) {
             const int c = c0 + it * RB;
             if (c < ncell) {
-                int p[3];
-                p[0] = c % G.n[0];
-                p[1] = (c / G.n[0]) % G.n[1];
-                p[2] = c / (G.n[0] * G.n[1]);
-                const long id = G.base + p[0] * G.s[0] + p[1] * G.s[1] + (long)p[2] * G.s[2];
+                const uint32_t jk = D.nx.div(c), k = D.ny.div(jk);
+                const uint32_t e = (c - jk * D.nx.d) + (jk - k * D.ny.d) * (uint32_t)G.s[1] + k * (uint32_t)G.s[2];
 #pragma unroll
-                for (int v = 0; v < 8; ++v) w[it][v] = u[id + v * G.sv];
+                for (int v = 0; v < 8; ++v) w[it][v] = sw::uniform(ub + v * G.sv)[e];
             }
         }
 #pragma unroll
@@ -98,107 +114,422 @@ __device__ __forceinline__ void patch_dt(const T *__restrict__ u, const Geom &G,
     __syncthreads();
 }
 
+// y or z sweep of a patch: tiles of 64 positions of the transverse plane (x
+// fastest) x FT faces, wave w taking rows and faces w, w + 4, ..: row and face
+// numbers are uniform, positions per lane.  Ghost cells are staged from their
+// periodic images.  Each 64-position column is walked along the sweep axis,
+// so that a tile's five halo rows are still in the L2.
+template <int DIR, int FT, typename T>
+__device__ __forceinline__ void sweep_yz_patch(const T *__restrict__ u, T *__restrict__ flux, const PatchDesc &D,
+                                               const Geom &G, const FaceBox &F, const Phys &P, T *sq)
+{
+    constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3, B = DIR == 1 ? 2 : 1;
+    constexpr int NC = sw::TILE * (FT + 5), IT = (FT + 5 + sw::ROWS - 1) / sw::ROWS;
+    const int cm[8] = { 0, 1 + N, 1 + T1, 1 + T2, 4 + N, 4 + T1, 4 + T2, 7 };
+    const int gc[7] = { 0, 1 + N, 1 + T1, 1 + T2, 4, 5, 6 };
+    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int npos = F.cnt[0] * F.cnt[B];
+    for (int p0 = 0; p0 < npos; p0 += sw::TILE) {
+        const bool ok = p0 + lane < npos;
+        // position - 1; lanes and rows beyond the end repeat the last one, so
+        // that the loads need no branches (values loaded under one were kept,
+        // and spilled, through the whole tile loop)
+        const uint32_t pp = ok ? p0 + lane : npos - 1, b = D.na.div(pp), a = pp - b * D.na.d;
+        const uint32_t es = sw::pwrap((int)a - 1, G.n[0]) + sw::pwrap((int)b - 1, G.n[B]) * (uint32_t)G.s[B];
+        const uint32_t ef = a + b * (uint32_t)F.s[B];
+        for (int f0 = 0; f0 < F.cnt[N]; f0 += FT) {
+            sw::stage_begin();
+            const int rows = min(FT + 5, G.n[N] + 6 - f0);       // cells f0 - 3 .. n + 2
+            T q[IT][8];
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int r = min(w + it * sw::ROWS, rows - 1);
+                const T *const ub = u + G.base + sw::pwrap(f0 - 3 + r, G.n[N]) * G.s[N];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) q[it][v] = sw::uniform(ub + cm[v] * G.sv)[es];
+            }
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int r = w + it * sw::ROWS;
+                if (r < rows) sw::stage_values<T>(q[it], P.gamma, sq + r * sw::TILE + lane, NC);
+            }
+            __syncthreads();
+            sw::stage_end();
+            if (ok) {
+                for (int r = w; r < FT && f0 + r < F.cnt[N]; r += sw::ROWS) {
+                    T out[7];
+                    sw::face_flux<T>(sq, NC, r * sw::TILE + lane, sw::TILE, P.gamma, P.igm1, (T)P.eps, out);
+                    T *const fb = flux + (f0 + r) * F.s[N];
+#pragma unroll
+                    for (int c = 0; c < 7; ++c) sw::uniform(fb + gc[c] * F.sc)[ef] = out[c];
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// The x sweep for short rows with the rho, m, E part of the update fused in
+// (the batched counterpart of sweep_tile_xseg_fused): tiles of XF_FACES faces
+// of the flattened (row, face) space overlapping by one (tile t starts at face
+// (XF_FACES - 1) t), one per thread (two faces per thread spill registers, and
+// the batched FP32 step measured 4% slower).  A tile stages every cell of the
+// rows it touches, at most xflat_cells(n, rows), ghost cells from their
+// periodic images; the fluxes' rho, m, E go to LDS (hx, 5 x XF_FACES) and
+// thread tid takes the cell right of its face when the next face is in the
+// same row and the row is interior.  Only the transverse-B fluxes of the x
+// faces are stored.  sq: NQ * XF_MAXC elements.  A flattened row holds at most
+// 266 cells and a patch edge 1024, so a variable is under 2^32 bytes and
+// every offset fits 32 bits.
+constexpr int XF_FACES = sw::TILE * sw::ROWS;
+constexpr int XF_MAXC = 544;     // 4-cell rows: at most 53 rows of 10 cells
+inline int xflat_cells(int nx, long nrows)
+{
+    long span = (XF_FACES + nx) / (nx + 1) + 1;
+    if (span > nrows) span = nrows;
+    return (int)(span * (nx + 6));
+}
+
+template <typename T>
+__device__ __forceinline__ void sweep_xflat_patch(const T *__restrict__ u, T *__restrict__ flux, const PatchDesc &D,
+                                                  const Geom &G, const FaceBox &F, const Phys &P, T *sq, T *hx,
+                                                  const XFuse<T> &xf)
+{
+    constexpr int STRIDE = XF_FACES - 1, IT = (XF_MAXC + RB - 1) / RB;
+    const int tid = threadIdx.x + sw::TILE * threadIdx.y;
+    const int total = (int)F.sc, nrows = F.cnt[1] * F.cnt[2];
+    // the patch's faces and RK arrays from its cell (0, 0, 0) on
+    sw::FusedTile<T> B;
+    B.nx2 = G.n[0] + 2;
+    B.fy = xf.fy + 1 + xf.by.s[2];
+    B.fz = xf.fz + 1 + B.nx2;
+    B.u0 = xf.u0 + G.base;
+    B.acc_in = xf.acc_in + G.base;
+    B.acc_out = xf.acc_out + G.base;
+    B.out = xf.out + G.base;
+    for (int g0 = 0; g0 < total - 1; g0 += STRIDE) {
+        sw::stage_begin();
+        const int r_lo = (int)D.nf.div(g0);
+        int r_hi = (int)D.nf.div(g0 + XF_FACES - 1);
+        if (r_hi > nrows - 1) r_hi = nrows - 1;
+        const int ncell = (r_hi - r_lo + 1) * (int)D.nxp.d;
+        T q[IT][8];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int c = min(tid + it * RB, ncell - 1);
+            const uint32_t rr = D.nxp.div(c), row = r_lo + rr, kk = D.n1f.div(row);
+            const int x = sw::pwrap((int)(c - rr * D.nxp.d) - 3, G.n[0]);
+            const int j = sw::pwrap((int)(row - kk * D.n1f.d) - 1, G.n[1]), k = sw::pwrap((int)kk - 1, G.n[2]);
+            const uint32_t e = x + j * (uint32_t)G.s[1] + k * (uint32_t)G.s[2];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) q[it][v] = sw::ld32(u + G.base + v * G.sv, e);
+        }
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int c = tid + it * RB;
+            if (c < ncell) sw::stage_values<T>(q[it], P.gamma, sq + c, XF_MAXC);
+        }
+        __syncthreads();
+        sw::stage_end();
+        const int g = g0 + tid;
+        const bool valid = g < total;
+        const uint32_t row = D.nf.div(g), kk = D.n1f.div(row);
+        const int i = (int)(g - row * D.nf.d), j = (int)(row - kk * D.n1f.d) - 1, k = (int)kk - 1;
+        if (valid) {
+            T out[7];
+            sw::face_flux<T>(sq, XF_MAXC, (int)((row - r_lo) * D.nxp.d) + i, 1, P.gamma, P.igm1, (T)P.eps, out);
+            hx[0 * XF_FACES + tid] = out[0];
+            hx[1 * XF_FACES + tid] = out[1];
+            hx[2 * XF_FACES + tid] = out[2];
+            hx[3 * XF_FACES + tid] = out[3];
+            hx[4 * XF_FACES + tid] = out[6];
+            if (tid < STRIDE || g == total - 1) {
+                sw::st32<T>(flux + 4 * F.sc + g0, tid, out[4]);
+                sw::st32<T>(flux + 5 * F.sc + g0, tid, out[5]);
+            }
+        }
+        // the cell's global loads in flight before the barrier
+        const bool cell = valid && tid < STRIDE && g + 1 < total && i < G.n[0] && j >= 0 && j < G.n[1] && k >= 0 &&
+                          k < G.n[2];
+        // (lanes without a cell load cell (0, 0, 0)'s values: no branch)
+        const uint32_t ci = cell ? i : 0, cj = cell ? j : 0, ck = cell ? k : 0;
+        const uint32_t rel = ci + cj * (uint32_t)G.s[1] + ck * (uint32_t)G.s[2], rj = ci + cj * (uint32_t)B.nx2;
+        sw::FusedCell<T> fc;
+        sw::fused_tile_load(xf, B, G.sv, rj + ck * (uint32_t)xf.by.s[2], rj + ck * (uint32_t)xf.bz.s[2], rel, fc);
+        __syncthreads();
+        if (cell) sw::fused_tile_store(xf, B, G, hx, XF_FACES, tid, rel, fc);
+        __syncthreads();
+    }
+}
+
+// Constrained transport and the B part of the RK stage of a patch whose x
+// sweep did the rho, m, E part: one thread per (i, j) column segment of up to
+// KSEG cells marching in k, the z-level EMFs carried (every EMF formed once
+// per column instead of once per adjacent cell, as in update_cell), the loads
+// of level k+1 issued before the arithmetic of level k (two waves per SIMD
+// hide little latency).  Operands, expressions and order of march_column.
+template <typename T>
+struct BLevel {
+    T x5h0, x5h1, y4h0, y4h1;          // FX5(i|i+1, j, k+1), FY4(i, j|j+1, k+1)
+    T z4m, z4c, z4p;                   // FZ4(i-1|i|i+1, j, k+1)
+    T z5m, z5c, z5p;                   // FZ5(i, j-1|j|j+1, k+1)
+    T x4[6];                           // FX4 at (i, j-1), (i, j), (i+1, j-1), (i+1, j), (i, j+1), (i+1, j+1), level k
+    T y5[6];                           // FY5 at (i-1, j), (i, j), (i+1, j), (i-1, j+1), (i, j+1), (i+1, j+1), level k
+    T w0[3], w1[3];                    // u0 and acc_in of B at the cell
+};
+
+// Bases of the face components and RK arrays at cell (0, 0, 0) and the plane
+// strides of the three face boxes and the state.
+template <typename T>
+struct BPatch {
+    const T *x4, *x5, *y4, *y5, *z4, *z5, *u0, *acc_in;
+    T *acc_out, *out;
+    int X0, X01, Y0, Y01, Z01, s2;     // rows and planes (rows of z faces as of y faces)
+    long sv;
+    bool ru0, rac;                     // the stage reads u0, acc_in
+};
+
+template <typename T>
+__device__ __forceinline__ void blevel_upper(const BPatch<T> &B, uint32_t ox, uint32_t oy, uint32_t oz, BLevel<T> &L)
+{
+    L.x5h0 = sw::ld32(B.x5 + B.X01, ox);
+    L.x5h1 = sw::ld32(B.x5 + B.X01 + 1, ox);
+    L.y4h0 = sw::ld32(B.y4 + B.Y01, oy);
+    L.y4h1 = sw::ld32(B.y4 + B.Y01 + B.Y0, oy);
+    L.z4m = sw::ld32(B.z4 + B.Z01 - 1, oz);
+    L.z4c = sw::ld32(B.z4 + B.Z01, oz);
+    L.z4p = sw::ld32(B.z4 + B.Z01 + 1, oz);
+    L.z5m = sw::ld32(B.z5 + B.Z01 - B.Y0, oz);
+    L.z5c = sw::ld32(B.z5 + B.Z01, oz);
+    L.z5p = sw::ld32(B.z5 + B.Z01 + B.Y0, oz);
+}
+template <typename T>
+__device__ __forceinline__ void blevel_load(const BPatch<T> &B, uint32_t ox, uint32_t oy, uint32_t oz, uint32_t os,
+                                            BLevel<T> &L)
+{
+    blevel_upper(B, ox, oy, oz, L);
+    L.x4[0] = sw::ld32(B.x4 - B.X0, ox);
+    L.x4[1] = sw::ld32(B.x4, ox);
+    L.x4[2] = sw::ld32(B.x4 - B.X0 + 1, ox);
+    L.x4[3] = sw::ld32(B.x4 + 1, ox);
+    L.x4[4] = sw::ld32(B.x4 + B.X0, ox);
+    L.x4[5] = sw::ld32(B.x4 + B.X0 + 1, ox);
+    L.y5[0] = sw::ld32(B.y5 - 1, oy);
+    L.y5[1] = sw::ld32(B.y5, oy);
+    L.y5[2] = sw::ld32(B.y5 + 1, oy);
+    L.y5[3] = sw::ld32(B.y5 + B.Y0 - 1, oy);
+    L.y5[4] = sw::ld32(B.y5 + B.Y0, oy);
+    L.y5[5] = sw::ld32(B.y5 + B.Y0 + 1, oy);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        L.w0[m] = B.ru0 ? sw::ld32(B.u0 + (4 + m) * B.sv, os) : T(0);
+        L.w1[m] = B.rac ? sw::ld32(B.acc_in + (4 + m) * B.sv, os) : T(0);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void update_b_patch(const T *fx, const T *fy, const T *fz, const PatchDesc &D,
+                                               const Geom &G, const FaceBox (&F)[3], const XFuse<T> &xf)
+{
+    constexpr int KSEG = 16;
+    BPatch<T> B;
+    B.X0 = G.n[0] + 1; B.X01 = (int)F[0].s[2];
+    B.Y0 = G.n[0] + 2; B.Y01 = (int)F[1].s[2]; B.Z01 = (int)F[2].s[2];
+    B.s2 = (int)G.s[2];
+    B.x4 = fx + 4 * F[0].sc + B.X0 + B.X01; B.x5 = fx + 5 * F[0].sc + B.X0 + B.X01;
+    B.y4 = fy + 4 * F[1].sc + 1 + B.Y01;    B.y5 = fy + 5 * F[1].sc + 1 + B.Y01;
+    B.z4 = fz + 4 * F[2].sc + 1 + B.Y0;     B.z5 = fz + 5 * F[2].sc + 1 + B.Y0;
+    B.u0 = xf.u0 + G.base; B.acc_in = xf.acc_in + G.base;
+    B.acc_out = xf.acc_out + G.base; B.out = xf.out + G.base;
+    B.sv = G.sv;
+    const StageCoef &c = xf.c;
+    B.ru0 = c.s < 3; B.rac = c.s > 0;
+    const T idx = T(G.idl[0]), idy = T(G.idl[1]), idz = T(G.idl[2]);
+    const T q = T(0.25), bdt = T(c.bdt), cdt = T(c.cdt);
+    const int tid = threadIdx.x + sw::TILE * threadIdx.y;
+    const int items = G.n[0] * G.n[1] * ((G.n[2] + KSEG - 1) / KSEG);
+    for (int it = tid; it < items; it += RB) {
+        const uint32_t col = D.nx.div(it), ks = D.ny.div(col);
+        const uint32_t i = it - col * D.nx.d, j = col - ks * D.ny.d, k0 = ks * KSEG;
+        const int k1 = min((int)k0 + KSEG, G.n[2]);
+        uint32_t ox = i + j * B.X0 + k0 * B.X01, oy = i + j * B.Y0 + k0 * B.Y01, oz = i + j * B.Y0 + k0 * B.Z01;
+        uint32_t os = i + j * (uint32_t)G.s[1] + k0 * (uint32_t)B.s2;
+        BLevel<T> cur, nxt;
+        // carried values at the lower z-level k0 (as march_column): the upper
+        // part of level k0 - 1
+        T x5c0, x5c1, y4c0, y4c1, Ey0, Ey1, Ex0, Ex1;
+        {
+            // level k0 - 1 through bases one plane lower (k0 may be 0)
+            BPatch<T> C = B;
+            C.x5 -= B.X01; C.y4 -= B.Y01; C.z4 -= B.Z01; C.z5 -= B.Z01;
+            BLevel<T> low;
+            blevel_upper(C, ox, oy, oz, low);
+            const T x5lo0 = sw::ld32(C.x5, ox), x5lo1 = sw::ld32(C.x5 + 1, ox);
+            const T y4lo0 = sw::ld32(C.y4, oy), y4lo1 = sw::ld32(C.y4 + B.Y0, oy);
+            blevel_load(B, ox, oy, oz, os, cur);
+            x5c0 = low.x5h0; x5c1 = low.x5h1; y4c0 = low.y4h0; y4c1 = low.y4h1;
+            T t;
+            t = -low.z4m; t -= low.z4c; t += x5lo0; t += x5c0; Ey0 = q * t;
+            t = -low.z4c; t -= low.z4p; t += x5lo1; t += x5c1; Ey1 = q * t;
+            t = -y4lo0; t -= y4c0; t += low.z5m; t += low.z5c; Ex0 = q * t;
+            t = -y4lo1; t -= y4c1; t += low.z5c; t += low.z5p; Ex1 = q * t;
+        }
+        for (int k = k0; k < k1; ++k) {
+            if (k + 1 < k1) blevel_load(B, ox + B.X01, oy + B.Y01, oz + B.Z01, os + B.s2, nxt);
+            T t;
+            t = -cur.z4m; t -= cur.z4c; t += x5c0; t += cur.x5h0; const T Ey2 = q * t;
+            t = -cur.z4c; t -= cur.z4p; t += x5c1; t += cur.x5h1; const T Ey3 = q * t;
+            t = -y4c0; t -= cur.y4h0; t += cur.z5m; t += cur.z5c; const T Ex2 = q * t;
+            t = -y4c1; t -= cur.y4h1; t += cur.z5c; t += cur.z5p; const T Ex3 = q * t;
+            t = -cur.x4[0]; t -= cur.x4[1]; t += cur.y5[0]; t += cur.y5[1]; const T Ez00 = q * t;
+            t = -cur.x4[2]; t -= cur.x4[3]; t += cur.y5[1]; t += cur.y5[2]; const T Ez10 = q * t;
+            t = -cur.x4[1]; t -= cur.x4[4]; t += cur.y5[3]; t += cur.y5[4]; const T Ez01 = q * t;
+            t = -cur.x4[3]; t -= cur.x4[5]; t += cur.y5[4]; t += cur.y5[5]; const T Ez11 = q * t;
+            T r, bxl, bxr, byl, byr, bzl, bzr;
+            r = T(0); r -= (Ez01 - Ez00) * idy; r += (Ey2 - Ey0) * idz; bxl = r;
+            r = T(0); r -= (Ez11 - Ez10) * idy; r += (Ey3 - Ey1) * idz; bxr = r;
+            r = T(0); r -= (Ex2 - Ex0) * idz; r += (Ez10 - Ez00) * idx; byl = r;
+            r = T(0); r -= (Ex3 - Ex1) * idz; r += (Ez11 - Ez01) * idx; byr = r;
+            r = T(0); r -= (Ey1 - Ey0) * idx; r += (Ex1 - Ex0) * idy; bzl = r;
+            r = T(0); r -= (Ey3 - Ey2) * idx; r += (Ex3 - Ex2) * idy; bzr = r;
+            const T Lb[3] = { T(0.5) * (bxl + bxr), T(0.5) * (byl + byr), T(0.5) * (bzl + bzr) };
+            // rk_store_vars's expressions on the preloaded u0 / acc_in values
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                T *const acc = B.acc_out + (4 + m) * B.sv, *const out = B.out + (4 + m) * B.sv;
+                if (c.s == 0) {
+                    sw::st32<T>(acc, os, cur.w0[m] + bdt * Lb[m]);
+                    sw::st32<T>(out, os, cur.w0[m] + cdt * Lb[m]);
+                } else if (c.s < 3) {
+                    sw::st32<T>(acc, os, cur.w1[m] + bdt * Lb[m]);
+                    sw::st32<T>(out, os, cur.w0[m] + cdt * Lb[m]);
+                } else {
+                    sw::st32<T>(out, os, cur.w1[m] + cdt * Lb[m]);
+                }
+            }
+            Ey0 = Ey2; Ey1 = Ey3; Ex0 = Ex2; Ex1 = Ex3;
+            x5c0 = cur.x5h0; x5c1 = cur.x5h1; y4c0 = cur.y4h0; y4c1 = cur.y4h1;
+            ox += B.X01; oy += B.Y01; oz += B.Z01; os += B.s2;
+            if (k + 1 < k1) cur = nxt;
+        }
+    }
+}
+
+// A patch's geometry and its block's face buffers, formed anew for each phase
+// (the patch number is made opaque): kept through all phases, the scalars of
+// one stood in the way of the next, with a thousand moves of spilled scalar
+// registers.
+template <typename T>
+struct Patch {
+    PatchDesc D;
+    Geom G;
+    FaceBox F[3];
+    T *fx, *fy, *fz;
+    __device__ __forceinline__ Patch(const BatchArgs<T> &a, int p, int block)
+    {
+        asm volatile("" : "+s"(p));
+        D = load_desc(a.pd, p);
+        patch_geom(D.n, a.dl, a.idl, G, F);
+        fx = a.scratch + (long)block * a.slot_elems;
+        fy = fx + NFC * F[0].sc;
+        fz = fy + NFC * F[1].sc;
+    }
+    // the RK stage of this patch, with its own dt
+    __device__ __forceinline__ StageCoef coef(const BatchArgs<T> &a, double dt) const
+    {
+        StageCoef c;
+        c.mode = 1;
+        c.s = a.s;
+        c.bdt = a.bw * dt;
+        c.cdt = a.cw * dt;
+        return c;
+    }
+    __device__ __forceinline__ XFuse<T> xfuse(const BatchArgs<T> &a, double dt) const
+    {
+        return XFuse<T>{ a.u0 + D.soff, a.acc + D.soff, a.acc + D.soff, a.out + D.soff, fy, fz, F[1], F[2],
+                         coef(a, dt) };
+    }
+};
+
 template <int FT, typename T>
 __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
 {
-    constexpr int C0 = sw::tile_cells<0, FT>(), C1 = sw::tile_cells<1, FT>();
-    constexpr int CMAX = (C0 > C1 ? C0 : C1) > sw::XF_MAXC ? (C0 > C1 ? C0 : C1) : sw::XF_MAXC;
+    constexpr int C0 = sw::XROWS_CELLS, C1 = sw::TILE * (FT + 5);
+    constexpr int CMAX = (C0 > C1 ? C0 : C1) > XF_MAXC ? (C0 > C1 ? C0 : C1) : XF_MAXC;
     __shared__ T sq[sw::NQ * CMAX];
-    __shared__ T hx[5 * sw::XF_FACES];     // rho, m, E fluxes of the fused x tile
+    __shared__ T hx[5 * XF_FACES];     // rho, m, E fluxes of the fused x tile
     __shared__ double sdt;
     const int b = blockIdx.x;
-    T *ff = a.scratch + (long)b * a.slot_elems;
-    const Phys P = a.P;
     __shared__ int next;
-    const int tid0 = threadIdx.x + sw::TILE * threadIdx.y;
+    const int tid = threadIdx.x + sw::TILE * threadIdx.y;
     for (;;) {
-        if (tid0 == 0) next = atomicAdd(a.counter, 1);
+        if (tid == 0) next = atomicAdd(a.counter, 1);
         __syncthreads();
-        const int q = next;
+        const int qn = __builtin_amdgcn_readfirstlane(next);
         __syncthreads();
-        if (q >= a.npatch) break;
-        const int p = a.order[q];
-        const PatchDesc &D = a.pd[p];
-        const Geom G = D.G;
-        T *us = a.us + D.soff;
-        if (a.s == 0) patch_dt<T>(a.u0 + D.soff, G, P.gamma, a.cfl, &a.dt[p], &a.flag[p]);
-        if (threadIdx.x == 0 && threadIdx.y == 0) sdt = a.dt[p];
+        if (qn >= a.npatch) break;
+        const int p = __builtin_amdgcn_readfirstlane(a.order[qn]);
+        if (a.s == 0) {
+            const Patch<T> Q(a, p, b);
+            patch_dt<T>(a.u0 + Q.D.soff, Q.D, Q.G, a.P.gamma, a.cfl, &a.dt[p], &a.flag[p]);
+        }
+        if (tid == 0) sdt = a.dt[p];
         __syncthreads();
-        const double dtp = sdt;
+        const double dtl = sdt;
+        const double dtp = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(dtl)),
+                                            __builtin_amdgcn_readfirstlane(__double2loint(dtl)));
         __syncthreads();
         if (dtp == 0.0) continue;        // non-physical patch: left unadvanced
         // no ghost fill: the sweep tiles stage ghost cells from their
-        // periodic images (WRAP)
-        T *fx = ff, *fy = ff + NFC * D.F[0].sc, *fz = fy + NFC * D.F[1].sc;
-        // the RK stage of this patch, with its own dt
-        StageCoef kc;
-        kc.mode = 1;
-        kc.s = a.s;
-        kc.bdt = a.bw * dtp;
-        kc.cdt = a.cw * dtp;
-        // y and z sweeps, then the x sweep: on the flattened x tiles it also
-        // differences every direction's rho, m, E fluxes and applies their RK
-        // update, and the update below is left with constrained transport
+        // periodic images.  y and z sweeps, then the x sweep: on the flattened
+        // x tiles it also differences every direction's rho, m, E fluxes and
+        // applies their RK update, and the update is left with constrained
+        // transport
         {
-            long na, nb;
-            sw::sweep_tiles<1, FT>(D.F[1], na, nb);
-            for (long tb = 0; tb < nb; ++tb)
-                for (long ta = 0; ta < na; ++ta) sw::sweep_tile<1, FT, T, false, false, true, true>(us, fy, G, D.F[1], P, ta, tb, sq);
-            sw::sweep_tiles<2, FT>(D.F[2], na, nb);
-            for (long tb = 0; tb < nb; ++tb)
-                for (long ta = 0; ta < na; ++ta) sw::sweep_tile<2, FT, T, false, false, true, true>(us, fz, G, D.F[2], P, ta, tb, sq);
+            const Patch<T> Q(a, p, b);
+            sweep_yz_patch<1, FT, T>(a.us + Q.D.soff, Q.fy, Q.D, Q.G, Q.F[1], a.P, sq);
         }
-        const bool fused = D.xflat != 0;
-        if (fused) {
-            const XFuse<T> xf{ a.u0 + D.soff, a.acc + D.soff, a.acc + D.soff, a.out + D.soff, fy, fz, D.F[1], D.F[2],
-                               kc };
-            const long total = (long)D.F[0].cnt[0] * D.F[0].cnt[1] * D.F[0].cnt[2];
-            const long nt = (total - 1 + sw::XF_FACES - 2) / (sw::XF_FACES - 1);
-            for (long t = 0; t < nt; ++t) sw::sweep_tile_xflat_fused<T, true>(us, fx, G, D.F[0], P, t, sq, hx, xf);
-        } else {
-            long na, nb;
-            sw::sweep_tiles<0, FT>(D.F[0], na, nb);
-            for (long tb = 0; tb < nb; ++tb)
-                for (long ta = 0; ta < na; ++ta) sw::sweep_tile<0, FT, T, false, false, true, true>(us, fx, G, D.F[0], P, ta, tb, sq);
+        {
+            const Patch<T> Q(a, p, b);
+            sweep_yz_patch<2, FT, T>(a.us + Q.D.soff, Q.fz, Q.D, Q.G, Q.F[2], a.P, sq);
         }
-        // flux differences (B only after the fused x sweep), CT, RK
-        up::UpdArgs<T> ua;
-        ua.u0 = a.u0 + D.soff;
-        ua.acc_in = a.acc + D.soff;
-        ua.acc_out = a.acc + D.soff;
-        ua.out = a.out + D.soff;
-        ua.ff[0] = fx; ua.ff[1] = fy; ua.ff[2] = fz;
-        ua.fb[0] = D.F[0]; ua.fb[1] = D.F[1]; ua.fb[2] = D.F[2];
-        ua.G = G;
-        ua.odelta = 0;
-        ua.osv = G.sv;
-        ua.c = kc;
-        ua.c.bonly = fused ? 1 : 0;
-        const int tid = threadIdx.x + sw::TILE * threadIdx.y;
-        if (fused) {
-            // CT and the B stage alone: one thread per (i, j) column segment
-            // of up to KSEG cells, marching in k with the z-level EMFs carried
-            // (every EMF formed once per column instead of once per adjacent
-            // cell, as in update_cell), the next level's loads in flight while
-            // a level is computed (two waves per SIMD hide little latency)
-            constexpr int KSEG = 16;
-            const int nseg = (G.n[2] + KSEG - 1) / KSEG;
-            const int ncol = G.n[0] * G.n[1], items = ncol * nseg;     // 32-bit: edges of at most 1024
-            for (int t = tid; t < items; t += RB) {
-                const int i = t % G.n[0], j = (t / G.n[0]) % G.n[1];
-                const int k0 = t / ncol * KSEG;
-                up::march_column_b_pipelined<T>(ua, i, j, k0, min(k0 + KSEG, G.n[2]));
+        if (load_desc(a.pd, p).xflat != 0) {
+            {
+                const Patch<T> Q(a, p, b);
+                sweep_xflat_patch<T>(a.us + Q.D.soff, Q.fx, Q.D, Q.G, Q.F[0], a.P, sq, hx, Q.xfuse(a, dtp));
             }
+            const Patch<T> Q(a, p, b);
+            update_b_patch<T>(Q.fx, Q.fy, Q.fz, Q.D, Q.G, Q.F, Q.xfuse(a, dtp));
         } else {
+            {
+                const Patch<T> Q(a, p, b);
+                long na, nb;
+                sw::xrows_tiles(Q.F[0], na, nb);
+                for (long tb = 0; tb < nb; ++tb)
+                    for (long ta = 0; ta < na; ++ta)
+                        sw::sweep_tile_xrows<T, false, false, true>(a.us + Q.D.soff, Q.fx, Q.G, Q.F[0], a.P, ta, tb, sq);
+            }
             // every variable: one thread per cell (marching with the hydro
             // fluxes carried too measured 1.5x slower here: more registers,
             // and whole passes of a small patch's columns half idle)
-            const int ncell = G.n[0] * G.n[1] * G.n[2];
+            const Patch<T> Q(a, p, b);
+            up::UpdArgs<T> ua;
+            ua.u0 = a.u0 + Q.D.soff;
+            ua.acc_in = a.acc + Q.D.soff;
+            ua.acc_out = a.acc + Q.D.soff;
+            ua.out = a.out + Q.D.soff;
+            ua.ff[0] = Q.fx; ua.ff[1] = Q.fy; ua.ff[2] = Q.fz;
+            ua.fb[0] = Q.F[0]; ua.fb[1] = Q.F[1]; ua.fb[2] = Q.F[2];
+            ua.G = Q.G;
+            ua.odelta = 0;
+            ua.osv = Q.G.sv;
+            ua.c = Q.coef(a, dtp);
+            const int ncell = Q.G.n[0] * Q.G.n[1] * Q.G.n[2];
             for (int c = tid; c < ncell; c += RB) {
                 int pos[3];
-                pos[0] = c % G.n[0];
-                pos[1] = (c / G.n[0]) % G.n[1];
-                pos[2] = c / (G.n[0] * G.n[1]);
+                pos[0] = c % Q.G.n[0];
+                pos[1] = (c / Q.G.n[0]) % Q.G.n[1];
+                pos[2] = c / (Q.G.n[0] * Q.G.n[1]);
                 up::update_cell(ua, pos);
             }
         }
@@ -206,18 +537,17 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
     }
 }
 
-// FP32: at least two waves per SIMD; left to itself the compiler gives the
-// 16-faces-per-tile kernel an AGPR past 256 registers and one wave per SIMD.
+// Waves per SIMD: FP32 three up to 8 faces per tile, as the 48 KB of LDS
+// allow, else two; FP64 two at 4 faces per tile (70 KB), else the LDS tile
+// leaves room for one block per CU anyway.
 template <int FT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void batch_stage_f32(BatchArgs<float> a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FT <= 8 ? 3 : 2))) void batch_stage_f32(BatchArgs<float> a)
 {
     batch_stage<FT, float>(a);
 }
 
-// FP64: from 8 faces per tile on the LDS tile leaves room for one block per
-// CU anyway, and at 4 two waves per SIMD would spill.
 template <int FT>
-__global__ __launch_bounds__(256) void batch_stage_f64(BatchArgs<double> a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FT <= 4 ? 2 : 1))) void batch_stage_f64(BatchArgs<double> a)
 {
     batch_stage<FT, double>(a);
 }
@@ -239,7 +569,7 @@ hipError_t launch_ft(const BatchArgs<T> &a, int nblocks, hipStream_t st)
 
 }  // namespace
 
-bool batch_xflat_ok(int nx, long nrows) { return nx >= 4 && sw::xflat_cells(nx, nrows) <= sw::XF_MAXC; }
+bool batch_xflat_ok(int nx, long nrows) { return nx >= 4 && xflat_cells(nx, nrows) <= XF_MAXC; }
 
 template <typename T>
 hipError_t launch_batch_stage(const BatchArgs<T> &a, int ft, int nblocks, hipStream_t st)

@@ -88,35 +88,6 @@ struct DevGuard {
     }
 };
 
-void patch_geom(const int n[3], double dl, Geom &G, FaceBox F[3])
-{
-    int N[3];
-    for (int d = 0; d < 3; ++d) {
-        G.n[d] = n[d];
-        G.act[d] = 1;
-        G.g[d] = 3;
-        G.dl[d] = dl;
-        G.idl[d] = 1.0 / dl;
-        N[d] = n[d] + 6;
-    }
-    G.s[0] = 1;
-    G.s[1] = N[0];
-    G.s[2] = (long)N[0] * N[1];
-    G.sv = (long)N[0] * N[1] * N[2];
-    G.base = 3 + 3 * G.s[1] + 3 * G.s[2];
-    for (int d = 0; d < 3; ++d) {
-        FaceBox &B = F[d];
-        for (int e = 0; e < 3; ++e) {
-            if (e == d) { B.lo[e] = 0; B.cnt[e] = n[e] + 1; }
-            else { B.lo[e] = -1; B.cnt[e] = n[e] + 2; }
-        }
-        B.s[0] = 1;
-        B.s[1] = B.cnt[0];
-        B.s[2] = (long)B.cnt[0] * B.cnt[1];
-        B.sc = (long)B.cnt[0] * B.cnt[1] * B.cnt[2];
-    }
-}
-
 double patch_cost(const int n[3])
 {
     double c = 0.0;
@@ -176,6 +147,8 @@ BatchArgs<T> stage_args(wombat_weno_batch_t *b, int s, T *u0, T *us, T *acc, T *
     a.dt = b->dt;
     a.flag = b->flag;
     a.cfl = b->cfg.cfl;
+    a.dl = b->cfg.dx;
+    a.idl = 1.0 / b->cfg.dx;
     a.s = s;
     a.bw = bw;
     a.cw = cw;
@@ -331,15 +304,24 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
     b->hpd.resize(npatch);
     b->soff.resize(npatch);
     for (int p = 0; p < npatch; ++p) {
-        const int *n = &b->dims[3 * p];
+        const int n[3] = { b->dims[3 * p], b->dims[3 * p + 1], b->dims[3 * p + 2] };
         PatchDesc &D = b->hpd[p];
         memset(&D, 0, sizeof D);
-        patch_geom(n, cfg->dx, D.G, D.F);
+        Geom G;
+        FaceBox F[3];
+        ww::patch_geom(n, cfg->dx, 1.0 / cfg->dx, G, F);
+        for (int d = 0; d < 3; ++d) D.n[d] = n[d];
         D.soff = off;
-        D.xflat = ww::batch_xflat_ok(n[0], (long)D.F[0].cnt[1] * D.F[0].cnt[2]) ? 1 : 0;
+        D.xflat = ww::batch_xflat_ok(n[0], (long)F[0].cnt[1] * F[0].cnt[2]) ? 1 : 0;
+        D.nx = ww::FastDiv(n[0]);
+        D.ny = ww::FastDiv(n[1]);
+        D.na = ww::FastDiv(n[0] + 2);
+        D.nf = ww::FastDiv(n[0] + 1);
+        D.n1f = ww::FastDiv(n[1] + 2);
+        D.nxp = ww::FastDiv(n[0] + 6);
         b->soff[p] = off;
-        off += (8 * D.G.sv + 63) / 64 * 64;
-        slot = std::max(slot, (long)ww::NFC * (D.F[0].sc + D.F[1].sc + D.F[2].sc));
+        off += (8 * G.sv + 63) / 64 * 64;
+        slot = std::max(slot, (long)ww::NFC * (F[0].sc + F[1].sc + F[2].sc));
     }
     b->arena = off;
     b->slot_elems = (slot + 63) / 64 * 64;

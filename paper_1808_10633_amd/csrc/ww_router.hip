@@ -933,7 +933,7 @@ static void routed_grid(int dir, const FaceBox &F, long &na, long &nb)
             na = (total + 255) / 256;
             nb = 1;
         } else {
-            sw::sweep_tiles<0, 4>(F, na, nb);
+            sw::xrows_tiles(F, na, nb);
         }
     } else {
         const long npos = (long)F.cnt[0] * F.cnt[dir == 1 ? 2 : 1];

@@ -43,8 +43,8 @@ template <typename T, bool WZ, bool GLF>
 __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xrows_kernel(const T *__restrict__ u,
                                                            T *__restrict__ flux, Geom G, FaceBox F, Phys P)
 {
-    __shared__ T sq[sw::NQ * sw::tile_cells<0, 4>()];
-    sw::sweep_tile<0, 4, T, WZ, GLF>(u, flux, G, F, P, blockIdx.x, blockIdx.y, sq);
+    __shared__ T sq[sw::NQ * sw::XROWS_CELLS];
+    sw::sweep_tile_xrows<T, WZ, GLF>(u, flux, G, F, P, blockIdx.x, blockIdx.y, sq);
 }
 
 template <typename T, bool WZ, bool GLF>
@@ -128,7 +128,7 @@ hipError_t launch_x(const T *u, T *flux, const Geom &G, const FaceBox &F, const 
         return hipGetLastError();
     }
     long na, nb;
-    sw::sweep_tiles<0, 4>(F, na, nb);
+    sw::xrows_tiles(F, na, nb);
     hipLaunchKernelGGL((sweep_xrows_kernel<T, WZ, GLF>), dim3((unsigned)na, (unsigned)nb),
                        dim3(sw::TILE, sw::ROWS), 0, st, u, flux, G, F, P);
     return hipGetLastError();

@@ -304,7 +304,7 @@ template <typename T>
 __device__ __forceinline__ GlobalPtr<T> uniform(T *p)
 {
     GlobalPtr<T> g = (GlobalPtr<T>)p;
-    asm("" : "+s"(g));
+    asm volatile("" : "+s"(g));
     return g;
 }
 // Load, store of the element at a 32-bit byte offset (per lane) from a uniform base.
@@ -635,102 +635,55 @@ __device__ __forceinline__ void store_face(T *__restrict__ flux, const FaceBox &
 // directly, so the patch needs no ghost fill.
 __device__ __forceinline__ int pwrap(int x, int n) { return x < 0 ? x + n : (x >= n ? x - n : x); }
 
-template <int DIR, int FT>
-__host__ __device__ constexpr int tile_cells() { return DIR == 0 ? ROWS * NCX : TILE * (FT + 5); }
+// Cells of an x tile of ROWS rows x TILE faces.
+constexpr int XROWS_CELLS = ROWS * NCX;
 
-// One tile of interfaces along axis DIR.  x sweep: ROWS rows (transverse
-// (j,k) pairs, tile index ta) x TILE consecutive faces (tile index tb).
-// y/z sweeps: TILE consecutive positions of the transverse plane (x fastest,
-// tile index ta) x FT consecutive faces (tile index tb); each of the ROWS
-// waves computes faces w, w+ROWS, ...  sq: LDS of NQ * tile_cells<DIR,FT>()
-// elements.  Ends with a block barrier, so consecutive tiles may reuse sq.
-// LF: stage with stage_tile (a thread's loads first: the batched kernel, at
-// two waves per SIMD, gains 4 %; the single-box FP32 y/z sweeps lose 1 %).
-template <int DIR, int FT, typename T, bool WZ = false, bool GLF = false, bool WRAP = false, bool LF = false>
-__device__ __forceinline__ void sweep_tile(const T *__restrict__ u, T *__restrict__ flux,
-                                           const Geom &G, const FaceBox &F, const Phys &P,
-                                           int ta, int tb, T *sq)
+// One x tile of ROWS rows (transverse (j,k) pairs, tile index ta) x TILE
+// consecutive faces (tile index tb), one face per thread.  sq: LDS of
+// NQ * XROWS_CELLS elements.  Ends with a block barrier, so consecutive tiles
+// may reuse sq.  WRAP: ghost cells from their periodic images, staged with a
+// thread's loads first (the batched kernel).
+template <typename T, bool WZ = false, bool GLF = false, bool WRAP = false>
+__device__ __forceinline__ void sweep_tile_xrows(const T *__restrict__ u, T *__restrict__ flux,
+                                                 const Geom &G, const FaceBox &F, const Phys &P,
+                                                 int ta, int tb, T *sq)
 {
-    constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3;
-    const int cm[8] = { 0, 1 + N, 1 + T1, 1 + T2, 4 + N, 4 + T1, 4 + T2, 7 };
-    constexpr int NC = tile_cells<DIR, FT>();
+    const int cm[8] = { 0, 1, 2, 3, 4, 5, 6, 7 };
+    constexpr int NC = XROWS_CELLS;
     const int lane = threadIdx.x, w = threadIdx.y, tid = lane + TILE * w;
-    const int nlast = G.n[N] + 2;   // last cell index along the sweep axis
-
+    const int nlast = G.n[0] + 2;   // last cell index along the sweep axis
+    const int nrows = F.cnt[1] * F.cnt[2];
+    const int r0 = ta * ROWS, f0 = tb * TILE;
     stage_begin();
-    if constexpr (DIR == 0) {
-        const int nrows = F.cnt[1] * F.cnt[2];
-        const int r0 = ta * ROWS;
-        const int f0 = tb * TILE;
-        auto cell_id = [&](int c, long &id) {
-            const int rr = c / NCX, xi = c - rr * NCX;
-            const int row = r0 + rr;
-            int x = f0 - 3 + xi;
-            if (row >= nrows || x > nlast) return false;
-            int j = F.lo[1] + row % F.cnt[1], k = F.lo[2] + row / F.cnt[1];
-            if (WRAP) { x = pwrap(x, G.n[0]); j = pwrap(j, G.n[1]); k = pwrap(k, G.n[2]); }
-            id = G.base + x * G.s[0] + j * G.s[1] + k * G.s[2];
-            return true;
-        };
-        if constexpr (LF) {
-            stage_tile<(ROWS * NCX + 255) / 256>(u, G.sv, cm, P.gamma, sq, NC, ROWS * NCX, cell_id);
-        } else {
-            for (int c = tid; c < ROWS * NCX; c += TILE * ROWS) {
-                long id;
-                if (cell_id(c, id)) stage_cell(u, id, G.sv, cm, P.gamma, sq + c, NC);
-            }
-        }
-        __syncthreads();
-        stage_end();
-        const int row = r0 + w;
-        int pos[3];
-        pos[0] = f0 + lane;
-        pos[1] = F.lo[1] + row % F.cnt[1];
-        pos[2] = F.lo[2] + row / F.cnt[1];
-        if (row < nrows && pos[0] < F.cnt[0]) {
-            T out[7];
-            face_flux<T, false, WZ, GLF>(sq, NC, w * NCX + lane, 1, P.gamma, P.igm1, (T)P.eps, out, nullptr,
-                                         P.ag);
-            store_face<N, T>(flux, F, pos, out);
-        }
+    auto cell_id = [&](int c, long &id) {
+        const int rr = c / NCX, xi = c - rr * NCX;
+        const int row = r0 + rr;
+        int x = f0 - 3 + xi;
+        if (row >= nrows || x > nlast) return false;
+        int j = F.lo[1] + row % F.cnt[1], k = F.lo[2] + row / F.cnt[1];
+        if (WRAP) { x = pwrap(x, G.n[0]); j = pwrap(j, G.n[1]); k = pwrap(k, G.n[2]); }
+        id = G.base + x * G.s[0] + j * G.s[1] + k * G.s[2];
+        return true;
+    };
+    if constexpr (WRAP) {
+        stage_tile<(NC + 255) / 256>(u, G.sv, cm, P.gamma, sq, NC, NC, cell_id);
     } else {
-        // positions in the transverse plane (x fastest, then the other axis)
-        constexpr int A = 0, B = (DIR == 1) ? 2 : 1;
-        const int npos = F.cnt[A] * F.cnt[B];
-        const int p = ta * TILE + lane;
-        const int f0 = tb * FT;
-        const int ca = F.lo[A] + p % F.cnt[A], cb = F.lo[B] + p / F.cnt[A];
-        const int wa = WRAP ? pwrap(ca, G.n[A]) : ca, wb = WRAP ? pwrap(cb, G.n[B]) : cb;
-        // cell c = rr * TILE + lane: row rr of the tile at this thread's position
-        auto cell_id = [&](int c, long &id) {
-            int y = f0 - 3 + c / TILE;
-            if (p >= npos || y > nlast) return false;
-            if (WRAP) y = pwrap(y, G.n[N]);
-            id = G.base + wa * G.s[A] + wb * G.s[B] + (long)y * G.s[N];
-            return true;
-        };
-        if constexpr (LF) {
-            stage_tile<(NC + 255) / 256>(u, G.sv, cm, P.gamma, sq, NC, NC, cell_id);
-        } else {
-            for (int c = tid; c < NC; c += TILE * ROWS) {
-                long id;
-                if (cell_id(c, id)) stage_cell(u, id, G.sv, cm, P.gamma, sq + c, NC);
-            }
+        for (int c = tid; c < NC; c += TILE * ROWS) {
+            long id;
+            if (cell_id(c, id)) stage_cell(u, id, G.sv, cm, P.gamma, sq + c, NC);
         }
-        __syncthreads();
-        stage_end();
-        for (int ff = w; ff < FT; ff += ROWS) {
-            int pos[3];
-            pos[A] = ca;
-            pos[B] = cb;
-            pos[N] = f0 + ff;
-            if (p < npos && pos[N] < F.cnt[N]) {
-                T out[7];
-                face_flux<T, false, WZ, GLF>(sq, NC, ff * TILE + lane, TILE, P.gamma, P.igm1, (T)P.eps, out,
-                                             nullptr, P.ag);
-                store_face<N, T>(flux, F, pos, out);
-            }
-        }
+    }
+    __syncthreads();
+    stage_end();
+    const int row = r0 + w;
+    int pos[3];
+    pos[0] = f0 + lane;
+    pos[1] = F.lo[1] + row % F.cnt[1];
+    pos[2] = F.lo[2] + row / F.cnt[1];
+    if (row < nrows && pos[0] < F.cnt[0]) {
+        T out[7];
+        face_flux<T, false, WZ, GLF>(sq, NC, w * NCX + lane, 1, P.gamma, P.igm1, (T)P.eps, out, nullptr, P.ag);
+        store_face<0, T>(flux, F, pos, out);
     }
     __syncthreads();
 }
@@ -818,116 +771,6 @@ __device__ __forceinline__ void fused_cell_store(const XFuse<T> &xf, const Geom 
     fused_cell_rk<T>(xf, G, xl, xr, c);
 }
 
-// x sweep for short rows (batched patches): the block takes XF_FACES
-// consecutive faces of the flattened (row, face) space, stages every cell of
-// the rows they touch (-3..n+2), and each thread computes XF_FPT faces (one:
-// two faces per thread spill registers at two waves per SIMD, and the
-// batched FP32 step measured 4% slower).  The rows touched hold at most
-// xflat_cells(n, rows) cells; sq needs NQ * XF_MAXC elements.  Face and row
-// numbers are 32-bit: a patch (edges of at most 1024 cells) has at most
-// 1025 * 1026^2 < 2^31 x faces, and 64-bit divisions are long software
-// sequences on the GPU.
-constexpr int XF_FPT = 1;
-constexpr int XF_FACES = TILE * ROWS * XF_FPT;
-constexpr int XF_MAXC = 544;     // 4-cell rows: at most 53 rows of 10 cells
-__host__ __device__ inline int xflat_cells(int nx, long nrows)
-{
-    long span = (XF_FACES + nx) / (nx + 1) + 1;
-    if (span > nrows) span = nrows;
-    return (int)(span * (nx + 6));
-}
-
-// Stage every cell of the rows that faces g0 .. g0+XF_FACES-1 touch; returns
-// the first row (sq with stride XF_MAXC).
-template <typename T, bool WRAP = false>
-__device__ __forceinline__ long xflat_stage(const T *__restrict__ u, const Geom &G, const FaceBox &F, const Phys &P,
-                                            long g0, T *sq)
-{
-    const int cm[8] = { 0, 1, 2, 3, 4, 5, 6, 7 };
-    const int nf = F.cnt[0], rowc = G.n[0] + 6;
-    const int nrows = F.cnt[1] * F.cnt[2];
-    const int r_lo = (int)g0 / nf;
-    int r_hi = ((int)g0 + XF_FACES - 1) / nf;
-    if (r_hi > nrows - 1) r_hi = nrows - 1;
-    const int ncell = (r_hi - r_lo + 1) * rowc;
-    stage_tile<(XF_MAXC + 255) / 256>(u, G.sv, cm, P.gamma, sq, XF_MAXC, ncell, [&](int c, long &id) {
-        const int row = r_lo + c / rowc;
-        int x = c % rowc - 3;
-        int j = F.lo[1] + row % F.cnt[1], k = F.lo[2] + row / F.cnt[1];
-        if (WRAP) { x = pwrap(x, G.n[0]); j = pwrap(j, G.n[1]); k = pwrap(k, G.n[2]); }
-        id = G.base + x * G.s[0] + j * G.s[1] + k * G.s[2];
-        return true;
-    });
-    return r_lo;
-}
-
-// The flattened x sweep with the rho, m, E part of the update fused in (the
-// batched form's counterpart of sweep_tile_xseg_fused): tiles of XF_FACES
-// faces overlapping by one (tile t starts at face (XF_FACES-1) t), the
-// fluxes' rho, m, E in LDS (hx, 5 x XF_FACES); thread tid takes faces
-// tid + q TILE ROWS (q < XF_FPT) and the cell right of each when the next
-// face is in the same row and the row is interior: x, y, z differences in
-// the update kernel's order and expressions, then the RK combination.  Only
-// the transverse-B fluxes of the x faces are stored.  Ends with a block
-// barrier.
-template <typename T, bool WRAP = false>
-__device__ __forceinline__ void sweep_tile_xflat_fused(const T *__restrict__ u, T *__restrict__ flux,
-                                                       const Geom &G, const FaceBox &F, const Phys &P,
-                                                       long tile, T *sq, T *hx, const XFuse<T> &xf)
-{
-    constexpr int NT = TILE * ROWS, STRIDE = XF_FACES - 1;
-    const int nf = F.cnt[0], rowc = G.n[0] + 6;
-    const int total = F.cnt[1] * F.cnt[2] * nf;
-    const int g0 = (int)tile * STRIDE;
-    const int tid = threadIdx.x + TILE * threadIdx.y;
-    stage_begin();
-    const int r_lo = (int)xflat_stage<T, WRAP>(u, G, F, P, g0, sq);
-    __syncthreads();
-    stage_end();
-    int pos[XF_FPT][3];
-    bool valid[XF_FPT];
-#pragma unroll
-    for (int q = 0; q < XF_FPT; ++q) {
-        const int f = tid + q * NT, g = g0 + f;
-        valid[q] = g < total;
-        pos[q][0] = pos[q][1] = pos[q][2] = 0;
-        if (valid[q]) {
-            const int row = g / nf;
-            pos[q][0] = g - row * nf;
-            pos[q][1] = F.lo[1] + row % F.cnt[1];
-            pos[q][2] = F.lo[2] + row / F.cnt[1];
-            T out[7];
-            face_flux<T>(sq, XF_MAXC, (row - r_lo) * rowc + pos[q][0], 1, P.gamma, P.igm1, (T)P.eps, out);
-            hx[0 * XF_FACES + f] = out[0];
-            hx[1 * XF_FACES + f] = out[1];
-            hx[2 * XF_FACES + f] = out[2];
-            hx[3 * XF_FACES + f] = out[3];
-            hx[4 * XF_FACES + f] = out[6];
-            if (f < STRIDE || g == total - 1) {
-                const long fi = F.idx(pos[q][0], pos[q][1], pos[q][2]);
-                flux[4 * F.sc + fi] = out[4];
-                flux[5 * F.sc + fi] = out[5];
-            }
-        }
-    }
-    // both cells' global loads in flight before the barrier
-    FusedCell<T> fc[XF_FPT];
-    bool cell[XF_FPT];
-#pragma unroll
-    for (int q = 0; q < XF_FPT; ++q) {
-        const int f = tid + q * NT, g = g0 + f;
-        const int i = pos[q][0], j = pos[q][1], k = pos[q][2];
-        cell[q] = valid[q] && f < STRIDE && g + 1 < total && i + 1 < nf && j >= 0 && j < G.n[1] && k >= 0 &&
-                  k < G.n[2];
-        if (cell[q]) fused_cell_load<T>(xf, G, i, j, k, fc[q]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < XF_FPT; ++q)
-        if (cell[q]) fused_cell_store<T>(xf, G, hx, XF_FACES, tid + q * NT, fc[q]);
-    __syncthreads();
-}
-
 // x sweep over the flattened (row, face) space, for rows of at least
 // XSEG_MIN faces: tile t takes the TILE*ROWS consecutive faces t*256 ..
 // of the row-major face sequence, which touch at most 4 rows (XTile); it
@@ -1011,15 +854,17 @@ __device__ __forceinline__ void sweep_tile_xseg(const T *__restrict__ u, T *__re
 }
 
 // The cell between tile faces t and t + 1 of row s (face x index f): its y
-// and z faces' fluxes and RK arrays, read at 32-bit offsets from the tile's
-// scalar bases (fused_cell_load's values, without its 64-bit products: those
-// and the row divisions were a fifth of the fused sweep's VALU time).  A row
-// of the x faces advances both face boxes by a row of n0 + 2 faces; passing
-// to the next plane, the y faces' rows (one fewer per plane) lag by one.
+// and z faces' fluxes (offsets ry, rz) and RK arrays (offset rel), read at
+// 32-bit offsets from the tile's scalar bases (fused_cell_load's values,
+// without its 64-bit products: those and the row divisions were a fifth of
+// the fused sweep's VALU time).  A row of the x faces advances both face
+// boxes by a row of n0 + 2 faces; passing to the next plane, the y faces' rows
+// (one fewer per plane) lag by one.
 template <typename T>
 struct FusedTile {
     const T *fy, *fz;          // y, z face fluxes at row 0 of the tile, x face 0's cell
     const T *u0, *acc_in;      // RK arrays at the tile's first staged cell
+                               // (the batched form: at the patch's cell (0, 0, 0))
     T *acc_out, *out;
     int nx2;                   // n0 + 2
 };
@@ -1038,11 +883,10 @@ __device__ __forceinline__ FusedTile<T> fused_tile(const XFuse<T> &xf, long ubas
 }
 
 template <typename T>
-__device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedTile<T> &B, long sv, int f, int s,
-                                                bool wrapped, uint32_t rel, FusedCell<T> &c)
+__device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedTile<T> &B, long sv, uint32_t ry,
+                                                uint32_t rz, uint32_t rel, FusedCell<T> &c)
 {
     const int hs[5] = { 0, 1, 2, 3, 6 }, hv[5] = { 0, 1, 2, 3, 7 };
-    const uint32_t ry = f + __umul24(s - (wrapped ? 1 : 0), B.nx2), rz = f + __umul24(s, B.nx2);
     const StageCoef &q = xf.c;
     const bool u0 = (q.mode == 1 && q.s < 3) || q.mode == 2;
     const bool ac = (q.mode == 1 && q.s > 0) || (q.mode == 2 && q.a1 != 0.0);
@@ -1150,7 +994,8 @@ __device__ __forceinline__ void sweep_tile_xseg_fused(const T *__restrict__ u, T
     const uint32_t rel = X.state_rel(X.cell_of(t, s) + 3, xseg_jump(G, F));
     const FusedTile<T> B = fused_tile(xf, ubase, X);
     FusedCell<T> fc;
-    if (cell) fused_tile_load(xf, B, G.sv, f, s, s >= X.sw, rel, fc);
+    if (cell)
+        fused_tile_load(xf, B, G.sv, f + __umul24(s - (s >= X.sw ? 1 : 0), B.nx2), f + __umul24(s, B.nx2), rel, fc);
     __syncthreads();
     if (cell) fused_tile_store(xf, B, G, hx, NH, t, rel, fc);
 }
@@ -1267,18 +1112,11 @@ __host__ inline YZArgs yz_args(const FaceBox &F, uint32_t nxcd)
     return Y;
 }
 
-// Number of tiles (ta, tb) of a sweep.
-template <int DIR, int FT>
-__host__ __device__ inline void sweep_tiles(const FaceBox &F, long &na, long &nb)
+// Number of tiles (ta, tb) of sweep_tile_xrows.
+__host__ __device__ inline void xrows_tiles(const FaceBox &F, long &na, long &nb)
 {
-    if (DIR == 0) {
-        na = ((long)F.cnt[1] * F.cnt[2] + ROWS - 1) / ROWS;
-        nb = (F.cnt[0] + TILE - 1) / TILE;
-    } else {
-        constexpr int B = (DIR == 1) ? 2 : 1;
-        na = ((long)F.cnt[0] * F.cnt[B] + TILE - 1) / TILE;
-        nb = (F.cnt[DIR] + FT - 1) / FT;
-    }
+    na = ((long)F.cnt[1] * F.cnt[2] + ROWS - 1) / ROWS;
+    nb = (F.cnt[0] + TILE - 1) / TILE;
 }
 
 }  // namespace sw
