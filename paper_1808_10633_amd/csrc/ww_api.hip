@@ -64,9 +64,9 @@ struct wombat_weno {
     void *ff[3];           // face fluxes per direction
     double *part;          // reduction partials (nblk x 8)
     int32_t *partflag;     // reduction flags (nblk)
-    double *dsmall;        // [0] dt, [1..8] sums / divb, flag at dflag
+    double *dsmall;        // [0] dt, flag at dflag
     int32_t *dflag;
-    double *hsmall;        // pinned host mirror of dsmall (16 doubles + flag)
+    double *hsmall;        // pinned, mapped host memory the reductions write: [0] dt, [1..8] sums / divb, flag at [16]
     int nblk;
     hipEvent_t ev[2];      // kernel timing
     int router;            // learned routing switched on
@@ -269,6 +269,11 @@ int precheck(wombat_weno_t *c)
 template <typename T>
 int fill_ghosts_t(wombat_weno_t *c, T *u)
 {
+    if (!ww::has_user_face(c->G, c->cfg.bc)) {
+        WW_CHECK(c, ww::launch_ghosts_all<T>(u, c->G, c->cfg.bc, c->st));
+        return WW_OK;
+    }
+    // a user hook runs after the built-in faces of its axis
     for (int ax = 0; ax < 3; ++ax) {
         if (!c->G.act[ax]) continue;
         WW_CHECK(c, ww::launch_ghosts<T>(u, c->G, ax, c->cfg.bc, c->st));
@@ -416,14 +421,15 @@ int operator_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *acc_out
 }
 
 template <typename T>
-int cfl_device_t(wombat_weno_t *c, const T *u, double *d_dt, int32_t *d_flag)
+int cfl_device_t(wombat_weno_t *c, const T *u, double *d_dt, int32_t *d_flag, double *h_dt = nullptr,
+                 int32_t *h_flag = nullptr)
 {
     if (c->cellst) {     // staggered storage: wave speeds of the cell-centred field
         WW_CHECK(c, ww::launch_face_to_cell<T>(u, (T *)c->cellst, c->G, c->st));
         u = (const T *)c->cellst;
     }
     WW_CHECK(c, ww::launch_cfl<T>(u, c->G, c->cfg.gamma, c->cfg.cfl, c->part, c->partflag,
-                                  c->nblk, d_dt, d_flag, c->st));
+                                  c->nblk, d_dt, d_flag, h_dt, h_flag, c->st));
     return WW_OK;
 }
 
@@ -474,6 +480,7 @@ int time_kernels_t(wombat_weno_t *c, T *u, int reps, double ms[7])
     for (int i = 0; i < 7; ++i) ms[i] = 0.0;
     auto chk = [&](hipError_t e) { return e == hipSuccess ? (int)WW_OK : hip_fail(c, e, "timed launch"); };
     if ((rc = time_launches(c, reps, [&] {
+             if (!ww::has_user_face(c->G, c->cfg.bc)) return chk(ww::launch_ghosts_all<T>(u, c->G, c->cfg.bc, c->st));
              for (int ax = 0; ax < 3; ++ax) {
                  int r2 = chk(ww::launch_ghosts<T>(u, c->G, ax, c->cfg.bc, c->st));
                  if (r2) return r2;
@@ -544,7 +551,7 @@ int time_kernels_t(wombat_weno_t *c, T *u, int reps, double ms[7])
     // the CFL reduction of a step (both passes)
     if ((rc = time_launches(c, reps, [&] {
              return chk(ww::launch_cfl<T>(u, c->G, c->cfg.gamma, c->cfg.cfl, c->part, c->partflag, c->nblk,
-                                          c->dsmall, c->dflag, c->st));
+                                          c->dsmall, c->dflag, nullptr, nullptr, c->st));
          }, ms[5])))
         return rc;
     // the update writing L(U) only (wombat_weno_rhs)
@@ -730,12 +737,13 @@ namespace {
 // CFL step and number of non-physical cells of d_u (synchronous).
 int cfl_and_count(wombat_weno_t *ctx, const void *d_u, double *dt, int32_t *bad)
 {
+    // the reduction writes its result to mapped host memory: no copy
+    double *h_dt = ctx->hsmall;
+    int32_t *h_flag = (int32_t *)(ctx->hsmall + 16);
     int rc = ctx->cfg.precision == WW_FP64
-                 ? cfl_device_t<double>(ctx, (const double *)d_u, ctx->dsmall, ctx->dflag)
-                 : cfl_device_t<float>(ctx, (const float *)d_u, ctx->dsmall, ctx->dflag);
+                 ? cfl_device_t<double>(ctx, (const double *)d_u, ctx->dsmall, ctx->dflag, h_dt, h_flag)
+                 : cfl_device_t<float>(ctx, (const float *)d_u, ctx->dsmall, ctx->dflag, h_dt, h_flag);
     if (rc) return rc;
-    WW_CHECK(ctx, hipMemcpyAsync(ctx->hsmall, ctx->dsmall, sizeof(double) * 20,
-                                 hipMemcpyDeviceToHost, ctx->st));
     WW_CHECK(ctx, hipStreamSynchronize(ctx->st));
     *bad = *(int32_t *)(ctx->hsmall + 16);
     *dt = ctx->hsmall[0];
@@ -907,12 +915,10 @@ int wombat_weno_sums(wombat_weno_t *ctx, const void *d_u, double out[8])
     DevGuard dg(ctx->cfg.device);
     if (ctx->cfg.precision == WW_FP64)
         WW_CHECK(ctx, ww::launch_sums<double>((const double *)d_u, ctx->G, ctx->part, ctx->nblk,
-                                              ctx->dsmall + 1, ctx->st));
+                                           ctx->hsmall + 1, ctx->st));
     else
         WW_CHECK(ctx, ww::launch_sums<float>((const float *)d_u, ctx->G, ctx->part, ctx->nblk,
-                                             ctx->dsmall + 1, ctx->st));
-    WW_CHECK(ctx, hipMemcpyAsync(ctx->hsmall, ctx->dsmall, sizeof(double) * 20,
-                                 hipMemcpyDeviceToHost, ctx->st));
+                                           ctx->hsmall + 1, ctx->st));
     WW_CHECK(ctx, hipStreamSynchronize(ctx->st));
     for (int v = 0; v < 8; ++v) out[v] = ctx->hsmall[1 + v];
     return WW_OK;
@@ -927,18 +933,16 @@ int wombat_weno_divb(wombat_weno_t *ctx, void *d_u, double *max_abs, double *l1)
     DevGuard dg(ctx->cfg.device);
     if (ctx->cellst && ctx->cfg.precision == WW_FP64)
         WW_CHECK(ctx, ww::launch_divb_face<double>((const double *)d_u, ctx->G, ctx->part, ctx->nblk,
-                                                   ctx->dsmall + 1, ctx->st));
+                                           ctx->hsmall + 1, ctx->st));
     else if (ctx->cellst)
         WW_CHECK(ctx, ww::launch_divb_face<float>((const float *)d_u, ctx->G, ctx->part, ctx->nblk,
-                                                  ctx->dsmall + 1, ctx->st));
+                                           ctx->hsmall + 1, ctx->st));
     else if (ctx->cfg.precision == WW_FP64)
         WW_CHECK(ctx, ww::launch_divb<double>((const double *)d_u, ctx->G, ctx->part, ctx->nblk,
-                                              ctx->dsmall + 1, ctx->st));
+                                           ctx->hsmall + 1, ctx->st));
     else
         WW_CHECK(ctx, ww::launch_divb<float>((const float *)d_u, ctx->G, ctx->part, ctx->nblk,
-                                             ctx->dsmall + 1, ctx->st));
-    WW_CHECK(ctx, hipMemcpyAsync(ctx->hsmall, ctx->dsmall, sizeof(double) * 20,
-                                 hipMemcpyDeviceToHost, ctx->st));
+                                           ctx->hsmall + 1, ctx->st));
     WW_CHECK(ctx, hipStreamSynchronize(ctx->st));
     *max_abs = ctx->hsmall[1];
     *l1 = ctx->hsmall[2];

@@ -12,6 +12,7 @@
 // assignment of cells to threads, wavefront butterflies and a fixed order
 // across the waves: results are bitwise reproducible.  No floating-point
 // atomics.
+#include "ww_index.h"
 #include "ww_internal.h"
 
 #include <math.h>
@@ -60,6 +61,63 @@ __global__ __launch_bounds__(256) void ghost_kernel(T *__restrict__ u, Geom G, i
     srp[ax] = src;
     const long di = G.base + dst[0] * G.s[0] + dst[1] * G.s[1] + (long)dst[2] * G.s[2];
     const long si = G.base + srp[0] * G.s[0] + srp[1] * G.s[1] + (long)srp[2] * G.s[2];
+#pragma unroll
+    for (int v = 0; v < 8; ++v) u[di + v * G.sv] = u[si + v * G.sv];
+}
+
+// Every ghost zone of the box in one launch, for boxes without user faces:
+// the zones of a later axis copy those of the earlier ones, so a ghost cell's
+// value is that of the interior cell its coordinates map to axis by axis
+// (periodic image or nearest interior cell), and no order is needed.  Three
+// shells, numbered x fastest: the z zones over the padded x and y ranges, the
+// y zones over the padded x and interior z range, the x zones over the
+// interior y and z ranges.
+constexpr long GHOST_ONE_LAUNCH = 1L << 18;    // ghost cells
+
+struct GhostArgs {
+    FastDiv px, py;            // padded x and y lengths
+    FastDiv nx6, ny;           // 2 gx, interior y length
+    FastDiv g6y;               // 2 gy
+    uint32_t nz_shell, ny_shell, total;
+    int per[6];                // face is periodic
+};
+
+__device__ __forceinline__ int ghost_image(int x, int n, int per_lo, int per_hi)
+{
+    if (x < 0) return per_lo ? x + n : 0;
+    if (x >= n) return per_hi ? x - n : n - 1;
+    return x;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void ghost_all_kernel(T *__restrict__ u, Geom G, GhostArgs A)
+{
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= A.total) return;
+    int p[3];
+    auto zone = [&](uint32_t g, int ax) { return (int)g < G.g[ax] ? (int)g - G.g[ax] : G.n[ax] + (int)g - G.g[ax]; };
+    if (t < A.nz_shell) {
+        const uint32_t r = A.px.div(t), g = A.py.div(r);
+        p[0] = (int)(t - r * A.px.d) - G.g[0];
+        p[1] = (int)(r - g * A.py.d) - G.g[1];
+        p[2] = zone(g, 2);
+    } else if (t < A.nz_shell + A.ny_shell) {
+        const uint32_t q = t - A.nz_shell, r = A.px.div(q), k = A.g6y.div(r);
+        p[0] = (int)(q - r * A.px.d) - G.g[0];
+        p[1] = zone(r - k * A.g6y.d, 1);
+        p[2] = (int)k;
+    } else {
+        const uint32_t q = t - A.nz_shell - A.ny_shell, r = A.nx6.div(q), k = A.ny.div(r);
+        p[0] = zone(q - r * A.nx6.d, 0);
+        p[1] = (int)(r - k * A.ny.d);
+        p[2] = (int)k;
+    }
+    long di = G.base, si = G.base;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        di += (long)p[e] * G.s[e];
+        si += (long)ghost_image(p[e], G.n[e], A.per[2 * e], A.per[2 * e + 1]) * G.s[e];
+    }
 #pragma unroll
     for (int v = 0; v < 8; ++v) u[di + v * G.sv] = u[si + v * G.sv];
 }
@@ -122,16 +180,29 @@ __device__ __forceinline__ void block_reduce_k(double (&v)[K])
             for (int i = 1; i < NW; ++i) v[k] = MAX ? fmax(v[k], sv[k][i]) : v[k] + sv[k][i];
 }
 
-// Cell c of the interior in row-major order.  32-bit arithmetic whenever the
-// box has fewer than 2^31 cells (every box that fits in memory: a 64-bit
-// division is a long software sequence on the GPU); the branch is uniform.
-__device__ __forceinline__ void cell_pos(const Geom &G, long c, int (&p)[3])
+// Cell c of the interior in row-major order: divisions by the launch
+// constants n0, n1 in boxes of fewer than 2^31 cells (every box that fits in
+// memory; a 64-bit division is a long software sequence on the GPU); the
+// branch is uniform.
+struct CellDiv {
+    FastDiv n0, n1;
+    int small;
+};
+CellDiv cell_div(const Geom &G)
 {
-    if ((long)G.n[0] * G.n[1] * G.n[2] <= 0x7fffffffL) {
-        const int ci = (int)c;
-        p[0] = ci % G.n[0];
-        p[1] = (ci / G.n[0]) % G.n[1];
-        p[2] = ci / (G.n[0] * G.n[1]);
+    CellDiv D;
+    D.n0 = FastDiv((uint32_t)G.n[0]);
+    D.n1 = FastDiv((uint32_t)G.n[1]);
+    D.small = (long)G.n[0] * G.n[1] * G.n[2] <= 0x7fffffffL;
+    return D;
+}
+__device__ __forceinline__ void cell_pos(const Geom &G, const CellDiv &D, long c, int (&p)[3])
+{
+    if (D.small) {
+        const uint32_t ci = (uint32_t)c, r = D.n0.div(ci), k = D.n1.div(r);
+        p[0] = (int)(ci - r * D.n0.d);
+        p[1] = (int)(r - k * D.n1.d);
+        p[2] = (int)k;
         return;
     }
     p[0] = (int)(c % G.n[0]);
@@ -140,15 +211,15 @@ __device__ __forceinline__ void cell_pos(const Geom &G, long c, int (&p)[3])
 }
 
 template <typename T>
-__global__ __launch_bounds__(RB) void cfl_partial(const T *__restrict__ u, Geom G, double gamma,
-                                                   double *part, int32_t *partflag)
+__global__ __launch_bounds__(RB) void cfl_partial(const T *__restrict__ u, Geom G, CellDiv D, double gamma,
+                                                  double *part, int32_t *partflag)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     double mx = 0.0, dummy = 0.0;
     int bad = 0;
     for (long c = (long)blockIdx.x * RB + threadIdx.x; c < ncell; c += (long)gridDim.x * RB) {
         int p[3];
-        cell_pos(G, c, p);
+        cell_pos(G, D, c, p);
         const long id = G.base + p[0] * G.s[0] + p[1] * G.s[1] + (long)p[2] * G.s[2];
         double q[8];
         bool fin = true;
@@ -178,15 +249,19 @@ __global__ __launch_bounds__(RB) void cfl_partial(const T *__restrict__ u, Geom 
 }
 
 __global__ __launch_bounds__(RB) void cfl_final(const double *part, const int32_t *partflag, int nblk,
-                                                 double cfl, double *d_dt, int32_t *d_flag)
+                                                double cfl, double *d_dt, int32_t *d_flag, double *h_dt,
+                                                int32_t *h_flag)
 {
     double mx = 0.0, dummy = 0.0;
     int bad = 0;
     for (int b = threadIdx.x; b < nblk; b += RB) { mx = fmax(mx, part[b]); bad += partflag[b]; }
     block_reduce2(mx, dummy, bad);
     if (threadIdx.x == 0) {
-        *d_dt = (mx > 0.0) ? cfl / mx : 0.0;
-        *d_flag = (mx > 0.0) ? bad : (bad > 0 ? bad : 1);
+        const double dt = (mx > 0.0) ? cfl / mx : 0.0;
+        const int32_t flag = (mx > 0.0) ? bad : (bad > 0 ? bad : 1);
+        *d_dt = dt;
+        *d_flag = flag;
+        if (h_dt) { *h_dt = dt; *h_flag = flag; }
     }
 }
 
@@ -252,13 +327,13 @@ __global__ __launch_bounds__(RB) void lf_final(const double *part, int nblk, dou
 }
 
 template <typename T>
-__global__ __launch_bounds__(RB) void sums_partial(const T *__restrict__ u, Geom G, double *part)
+__global__ __launch_bounds__(RB) void sums_partial(const T *__restrict__ u, Geom G, CellDiv D, double *part)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     double acc[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
     for (long c = (long)blockIdx.x * RB + threadIdx.x; c < ncell; c += (long)gridDim.x * RB) {
         int p[3];
-        cell_pos(G, c, p);
+        cell_pos(G, D, c, p);
         const long id = G.base + p[0] * G.s[0] + p[1] * G.s[1] + (long)p[2] * G.s[2];
         for (int v = 0; v < 8; ++v) acc[v] += (double)u[id + v * G.sv];
     }
@@ -279,14 +354,13 @@ __global__ __launch_bounds__(RB) void sums_final(const double *part, int nblk, d
 
 // Corner divergence at corners i+1/2 (i = 0..n-1) on active axes.
 template <typename T>
-__global__ __launch_bounds__(RB) void divb_partial(const T *__restrict__ u, Geom G, double *part)
+__global__ __launch_bounds__(RB) void divb_partial(const T *__restrict__ u, Geom G, CellDiv D, double *part)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     double mx = 0.0, sm = 0.0;
-    int dummy = 0;
     for (long c = (long)blockIdx.x * RB + threadIdx.x; c < ncell; c += (long)gridDim.x * RB) {
         int p[3];
-        cell_pos(G, c, p);
+        cell_pos(G, D, c, p);
         double div = 0.0;
         for (int d = 0; d < 3; ++d) {
             if (!G.act[d]) continue;
@@ -308,12 +382,12 @@ __global__ __launch_bounds__(RB) void divb_partial(const T *__restrict__ u, Geom
         mx = fmax(mx, fabs(div));
         sm += fabs(div);
     }
+    int dummy = 0;
     block_reduce2(mx, sm, dummy);
     if (threadIdx.x == 0) { part[2 * blockIdx.x] = mx; part[2 * blockIdx.x + 1] = sm; }
 }
 
-__global__ __launch_bounds__(RB) void divb_final(const double *part, int nblk, double ncell,
-                                                  double *out)
+__global__ __launch_bounds__(RB) void divb_final(const double *part, int nblk, double ncell, double *out)
 {
     double mx = 0.0, sm = 0.0;
     int dummy = 0;
@@ -324,13 +398,13 @@ __global__ __launch_bounds__(RB) void divb_final(const double *part, int nblk, d
 
 // Staggered storage (periodic boxes): cell-centred state of the interior cells.
 template <typename T>
-__global__ __launch_bounds__(RB) void face_to_cell_kernel(const T *__restrict__ u, T *__restrict__ uc, Geom G)
+__global__ __launch_bounds__(RB) void face_to_cell_kernel(const T *__restrict__ u, T *__restrict__ uc, Geom G, CellDiv D)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     const long c = (long)blockIdx.x * RB + threadIdx.x;
     if (c >= ncell) return;
     int p[3];
-    cell_pos(G, c, p);
+    cell_pos(G, D, c, p);
     const long id = G.base + p[0] * G.s[0] + p[1] * G.s[1] + (long)p[2] * G.s[2];
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
@@ -347,14 +421,13 @@ __global__ __launch_bounds__(RB) void face_to_cell_kernel(const T *__restrict__ 
 
 // Face divergence of a staggered state (periodic box).
 template <typename T>
-__global__ __launch_bounds__(RB) void divb_face_partial(const T *__restrict__ u, Geom G, double *part)
+__global__ __launch_bounds__(RB) void divb_face_partial(const T *__restrict__ u, Geom G, CellDiv D, double *part)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     double mx = 0.0, sm = 0.0;
-    int dummy = 0;
     for (long c = (long)blockIdx.x * RB + threadIdx.x; c < ncell; c += (long)gridDim.x * RB) {
         int p[3];
-        cell_pos(G, c, p);
+        cell_pos(G, D, c, p);
         const long id = G.base + p[0] * G.s[0] + p[1] * G.s[1] + (long)p[2] * G.s[2];
         double div = 0.0;
         for (int d = 0; d < 3; ++d)
@@ -365,6 +438,7 @@ __global__ __launch_bounds__(RB) void divb_face_partial(const T *__restrict__ u,
         mx = fmax(mx, fabs(div));
         sm += fabs(div);
     }
+    int dummy = 0;
     block_reduce2(mx, sm, dummy);
     if (threadIdx.x == 0) { part[2 * blockIdx.x] = mx; part[2 * blockIdx.x + 1] = sm; }
 }
@@ -425,13 +499,46 @@ hipError_t launch_ghosts(T *u, const Geom &G, int axis, const int bc[6], hipStre
 }
 
 template <typename T>
-hipError_t launch_cfl(const T *u, const Geom &G, double gamma, double cfl, double *part,
-                      int32_t *partflag, int nblk, double *d_dt, int32_t *d_flag, hipStream_t st)
+hipError_t launch_ghosts_all(T *u, const Geom &G, const int bc[6], hipStream_t st)
 {
-    hipLaunchKernelGGL((cfl_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, gamma, part, partflag);
+    const long px = G.n[0] + 2 * G.g[0], py = G.n[1] + 2 * G.g[1];
+    const long nz = 2L * G.g[2] * px * py, ny = 2L * G.g[1] * px * G.n[2], nx = 2L * G.g[0] * G.n[1] * G.n[2];
+    // One launch where the launches are the cost: at 32^3 (22 k ghost cells) it
+    // takes 5 us, one per axis 3 x 5; at 256^3 (1.2 M) the three, whose shells
+    // are each in one order, take 39 us, the one 57.
+    if (nx + ny + nz > GHOST_ONE_LAUNCH) {
+        for (int ax = 0; ax < 3; ++ax) {
+            hipError_t e = launch_ghosts<T>(u, G, ax, bc, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    GhostArgs A;
+    A.px = FastDiv((uint32_t)px);
+    A.py = FastDiv((uint32_t)py);
+    A.nx6 = FastDiv((uint32_t)(G.act[0] ? 2 * G.g[0] : 1));
+    A.g6y = FastDiv((uint32_t)(G.act[1] ? 2 * G.g[1] : 1));
+    A.ny = FastDiv((uint32_t)G.n[1]);
+    A.nz_shell = (uint32_t)nz;
+    A.ny_shell = (uint32_t)ny;
+    A.total = (uint32_t)(nx + ny + nz);
+    for (int f = 0; f < 6; ++f) A.per[f] = bc[f] == 0;
+    hipLaunchKernelGGL((ghost_all_kernel<T>), dim3((A.total + 255) / 256), dim3(256), 0, st, u, G, A);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_cfl(const T *u, const Geom &G, double gamma, double cfl, double *part,
+                      int32_t *partflag, int nblk, double *d_dt, int32_t *d_flag, double *h_dt, int32_t *h_flag,
+                      hipStream_t st)
+{
+    hipLaunchKernelGGL((cfl_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, cell_div(G), gamma, part, partflag);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cfl_final, dim3(1), dim3(RB), 0, st, part, partflag, nblk, cfl, d_dt, d_flag);
+    // (letting the last block of the first pass do this measured slower: its
+    // fences write back and invalidate the L2s while the others still read,
+    // 283 us against 205 + 5 at 256^3)
+    hipLaunchKernelGGL(cfl_final, dim3(1), dim3(RB), 0, st, part, partflag, nblk, cfl, d_dt, d_flag, h_dt, h_flag);
     return hipGetLastError();
 }
 
@@ -453,25 +560,22 @@ hipError_t launch_lf_global(const T *u, const Geom &G, int d, double gamma, doub
 }
 
 template <typename T>
-hipError_t launch_sums(const T *u, const Geom &G, double *part, int nblk, double *d_out,
-                       hipStream_t st)
+hipError_t launch_sums(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL((sums_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, part);
+    hipLaunchKernelGGL((sums_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, cell_div(G), part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sums_final, dim3(1), dim3(RB), 0, st, part, nblk, d_out);
+    hipLaunchKernelGGL(sums_final, dim3(1), dim3(RB), 0, st, part, nblk, out);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_divb(const T *u, const Geom &G, double *part, int nblk, double *d_out,
-                       hipStream_t st)
+hipError_t launch_divb(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL((divb_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, part);
+    hipLaunchKernelGGL((divb_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, cell_div(G), part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    double ncell = (double)G.n[0] * G.n[1] * G.n[2];
-    hipLaunchKernelGGL(divb_final, dim3(1), dim3(RB), 0, st, part, nblk, ncell, d_out);
+    hipLaunchKernelGGL(divb_final, dim3(1), dim3(RB), 0, st, part, nblk, (double)G.n[0] * G.n[1] * G.n[2], out);
     return hipGetLastError();
 }
 
@@ -479,25 +583,27 @@ template <typename T>
 hipError_t launch_face_to_cell(const T *u, T *uc, const Geom &G, hipStream_t st)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
-    hipLaunchKernelGGL((face_to_cell_kernel<T>), dim3((unsigned)((ncell + RB - 1) / RB)), dim3(RB), 0, st, u, uc, G);
+    hipLaunchKernelGGL((face_to_cell_kernel<T>), dim3((unsigned)((ncell + RB - 1) / RB)), dim3(RB), 0, st, u, uc, G,
+                       cell_div(G));
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_divb_face(const T *u, const Geom &G, double *part, int nblk, double *d_out, hipStream_t st)
+hipError_t launch_divb_face(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL((divb_face_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, part);
+    hipLaunchKernelGGL((divb_face_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, cell_div(G), part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    double ncell = (double)G.n[0] * G.n[1] * G.n[2];
-    hipLaunchKernelGGL(divb_final, dim3(1), dim3(RB), 0, st, part, nblk, ncell, d_out);
+    hipLaunchKernelGGL(divb_final, dim3(1), dim3(RB), 0, st, part, nblk, (double)G.n[0] * G.n[1] * G.n[2], out);
     return hipGetLastError();
 }
 
 #define WW_INST(T)                                                                           \
     template hipError_t launch_ghosts<T>(T *, const Geom &, int, const int *, hipStream_t);  \
+    template hipError_t launch_ghosts_all<T>(T *, const Geom &, const int *, hipStream_t);   \
     template hipError_t launch_cfl<T>(const T *, const Geom &, double, double, double *,      \
-                                      int32_t *, int, double *, int32_t *, hipStream_t);     \
+                                      int32_t *, int, double *, int32_t *,                   \
+                                      double *, int32_t *, hipStream_t);                     \
     template hipError_t launch_sums<T>(const T *, const Geom &, double *, int, double *,      \
                                        hipStream_t);                                         \
     template hipError_t launch_divb<T>(const T *, const Geom &, double *, int, double *,      \

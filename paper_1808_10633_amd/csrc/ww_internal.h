@@ -114,11 +114,23 @@ int sweep_x_fused_min_faces();
 template <typename T>
 hipError_t launch_ghosts(T *u, const Geom &G, int axis, const int bc[6], hipStream_t st);
 
-// CFL reduction: writes partial maxima / flags to scratch, then dt to d_dt.
+// All axes in one launch (no user faces; the same values as axis by axis).
+template <typename T>
+hipError_t launch_ghosts_all(T *u, const Geom &G, const int bc[6], hipStream_t st);
+inline bool has_user_face(const Geom &G, const int bc[6])
+{
+    for (int f = 0; f < 6; ++f)
+        if (G.act[f / 2] && bc[f] == 2) return true;
+    return false;
+}
+
+// CFL reduction: partial maxima / flags to scratch, then dt to d_dt and the
+// count of non-physical cells to d_flag, and both to mapped host memory h_dt,
+// h_flag unless NULL.
 template <typename T>
 hipError_t launch_cfl(const T *u, const Geom &G, double gamma, double cfl, double *part,
-                      int32_t *partflag, int nblk, double *d_dt, int32_t *d_flag,
-                      hipStream_t st);
+                      int32_t *partflag, int nblk, double *d_dt, int32_t *d_flag, double *h_dt,
+                      int32_t *h_flag, hipStream_t st);
 int cfl_blocks(const Geom &G);
 
 // Global LF speeds of the d-sweep (the LF-speed ablation): per field, the
@@ -133,22 +145,20 @@ hipError_t launch_lf_global(const T *u, const Geom &G, int d, double gamma, doub
                             hipStream_t st);
 
 template <typename T>
-hipError_t launch_sums(const T *u, const Geom &G, double *part, int nblk, double *d_out,
-                       hipStream_t st);
+hipError_t launch_sums(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st);
 
 // Staggered storage (periodic boxes): the cell-centred state uc of u
 // (interior; B_d the mean of a cell's two d-faces on an active axis, the
 // slot itself on an inactive one), and the face divergence
-// sum_d (b_d(i+1/2) - b_d(i-1/2))/dx_d of u (max, mean of |.|) into d_out[0..1].
+// sum_d (b_d(i+1/2) - b_d(i-1/2))/dx_d of u (max, mean of |.|) into out[0..1].
+// out of the sums and divergences may be mapped host memory.
 template <typename T>
 hipError_t launch_face_to_cell(const T *u, T *uc, const Geom &G, hipStream_t st);
 template <typename T>
-hipError_t launch_divb_face(const T *u, const Geom &G, double *part, int nblk, double *d_out,
-                            hipStream_t st);
+hipError_t launch_divb_face(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st);
 int sums_blocks(const Geom &G);
 
 template <typename T>
-hipError_t launch_divb(const T *u, const Geom &G, double *part, int nblk, double *d_out,
-                       hipStream_t st);
+hipError_t launch_divb(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st);
 
 }  // namespace ww

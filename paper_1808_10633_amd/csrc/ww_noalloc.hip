@@ -55,7 +55,12 @@ int rhs_t(const wombat_weno_config *cfg, const ww::Geom &G, const ww::FaceBox (&
 {
     hipStream_t st = (hipStream_t)cfg->stream;
     // ghost zones, axis by axis, then the user faces of that axis (Sec. 2.2)
-    for (int ax = 0; ax < 3; ++ax) {
+    const bool user = ww::has_user_face(G, cfg->bc);
+    if (!user) {
+        hipError_t e = ww::launch_ghosts_all<T>(u, G, cfg->bc, st);
+        if (e != hipSuccess) return hipfail(e, "ghost fill");
+    }
+    for (int ax = 0; ax < 3 && user; ++ax) {
         if (!G.act[ax]) continue;
         hipError_t e = ww::launch_ghosts<T>(u, G, ax, cfg->bc, st);
         if (e != hipSuccess) return hipfail(e, "ghost fill");

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xfused_kernel(const T 
                                                            uint32_t per_xcd)
 {
     __shared__ T sq[sw::nq<pre_x<T>()>() * sw::XSEG_CELLS];
-    __shared__ T hx[sw::hx_slots<T>() * sw::TILE * sw::ROWS];
+    __shared__ T hx[5 * sw::TILE * sw::ROWS];
     const uint32_t tile = (blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;
     if (tile >= ntile) return;
     sw::sweep_tile_xseg_fused<T, WZ, GLF, pre_x<T>()>(u, flux, G, F, P, A, tile, sq, hx, xf);

@@ -138,6 +138,7 @@ constexpr double SQ18 = 4.2426406871192851464, SQ12 = 3.4641016151377545870;
 template <typename T>
 __device__ __forceinline__ void phi_fold(T a, T b, T c, T d, const T (&ee)[3], T &num, T &inv)
 {
+#pragma clang fp contract(off)
     const T b2 = b * b, c2 = c * c;
     T r0 = fma(a, fma(T(4 * SQ18), a, T(-11 * SQ18) * b), fma(T(10 * SQ18), b2, ee[1]));
     T r1 = fma(T(4), b2 + c2, fma(T(-5), b * c, ee[0]));
@@ -215,6 +216,7 @@ __device__ __forceinline__ T phi_n(T a, T b, T c, T d, const T (&ee)[3], T *dev)
 template <typename T, bool LBL = false, bool WZ = false>
 __device__ __forceinline__ T weno_field(const T (&df)[5], const T (&du)[5], T al, const T (&ee)[3], T *dev = nullptr)
 {
+#pragma clang fp contract(off)
     T dp[5], dm[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
@@ -263,18 +265,20 @@ __device__ __forceinline__ T cell_flux(const T (&w)[8], T p, T ir, T (&F)[7])
 template <typename T, bool PRE = false, bool LIN = false>
 __device__ __forceinline__ void stage_values(const T (&w)[8], double gamma, T *q, int qs)
 {
+#pragma clang fp contract(off)
     const T r = w[0], mn = w[1], m1 = w[2], m2 = w[3], bn = w[4], b1 = w[5], b2 = w[6], e = w[7];
     // pressure recovery (kept in FP64 for every storage type)
-    double ird = frcp((double)r);
-    double pd = (gamma - 1.0) * ((double)e - 0.5 * ((double)mn * mn + (double)m1 * m1 + (double)m2 * m2) * ird
-                                 - 0.5 * ((double)bn * bn + (double)b1 * b1 + (double)b2 * b2));
+    const double ird = frcp((double)r);
+    const double mm = fma((double)m2, (double)m2, fma((double)m1, (double)m1, (double)mn * mn));
+    const double bb = fma((double)b2, (double)b2, fma((double)b1, (double)b1, (double)bn * bn));
+    const double pd = (gamma - 1.0) * fma(-0.5, bb, fma(-0.5 * mm, ird, (double)e));
     T p = (T)pd;
     T ir = (T)ird;
     T a2 = T(gamma) * p * ir;
     T bn2 = bn * bn * ir;
-    T bt2 = (b1 * b1 + b2 * b2) * ir;
+    T bt2 = fma(b1, b1, b2 * b2) * ir;
     T dd = a2 - bn2;
-    T disc = dd * dd + bt2 * (T(2) * a2 + T(2) * bn2 + bt2);
+    T disc = fma(dd, dd, bt2 * fma(T(2), a2, fma(T(2), bn2, bt2)));
     T cf2 = T(0.5) * (a2 + bn2 + bt2 + fsqrt(disc));
     T cs2 = a2 * bn2 * frcp(cf2);       // (unused, and not computed, with LIN)
     q[0 * qs] = r;  q[1 * qs] = mn; q[2 * qs] = m1; q[3 * qs] = m2;
@@ -366,18 +370,21 @@ __device__ __forceinline__ void stage_tile(const T *__restrict__ u, long sv, con
 // GLF: the LF speed of field s is ag[s] (global speeds of the sweep, an
 // ablation) instead of the largest |lambda^s| over the six cells.
 // PRE: the cells were staged with their fluxes and v_n (NQ_PRE quantities).
-// STASH: the mean flux waits in LDS (the thread's own 7 values, a block apart).
-template <typename T, bool LBL = false, bool WZ = false, bool GLF = false, bool PRE = false, bool STASH = false>
+// REREAD: the mean mass flux is read from the tile again at the end instead of
+// waiting in registers: with it the FP64 fused x sweep fits 256 VGPRs (without,
+// it spills 4; the FP64 y/z tiles fit without and spill 7 with it).
+template <typename T, bool LBL = false, bool WZ = false, bool GLF = false, bool PRE = false, bool REREAD = false>
 __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int off, int cstr,
                                           double gamma, double igm1, T eps, T (&out)[7],
-                                          T *dev = nullptr, const double *ag = nullptr, T *stash = nullptr)
+                                          T *dev = nullptr, const double *ag = nullptr)
 {
+    // every fused operation is written out (see cell_flux)
+#pragma clang fp contract(off)
 #define QQ(q, j) sq[(q) * qs + off + (j) * cstr]
     T Fs[7], dY[5][7], dZ[5][7], am[7];
     T Fp[7], Up[7];
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-#pragma clang fp contract(off)
         T vn, Fj[7];
         const T w[8] = { QQ(0, j), QQ(1, j), QQ(2, j), QQ(3, j), QQ(4, j), QQ(5, j), QQ(6, j), QQ(7, j) };
         if constexpr (PRE) {
@@ -395,11 +402,7 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
 #pragma unroll
         for (int c = 0; c < 7; ++c) {
             am[c] = (j == 0) ? lam[c] : fmax(am[c], lam[c]);
-            if (j == 3) {                                  // twice the mean flux
-                const T sum = Fp[c] + Fj[c];
-                if constexpr (STASH) stash[c * TILE * ROWS] = sum;
-                else Fs[c] = sum;
-            }
+            if (j == 3) Fs[c] = Fp[c] + Fj[c];             // twice the mean flux
             if (j > 0) { dY[j - 1][c] = Fj[c] - Fp[c]; dZ[j - 1][c] = Uj[c] - Up[c]; }
             Fp[c] = Fj[c];
             Up[c] = Uj[c];
@@ -412,16 +415,15 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
 
     // Interface state: mean of the primitive variables of cells i and i+1.
     // Eigen-system normalisation in FP64 for every storage type.
-    double r2 = QQ(0, 2), r3 = QQ(0, 3), i2 = QQ(9, 2), i3 = QQ(9, 3);
-    double rb = 0.5 * (r2 + r3);
-    double vnb = 0.5 * ((double)QQ(1, 2) * i2 + (double)QQ(1, 3) * i3);
-    double v1b = 0.5 * ((double)QQ(2, 2) * i2 + (double)QQ(2, 3) * i3);
-    double v2b = 0.5 * ((double)QQ(3, 2) * i2 + (double)QQ(3, 3) * i3);
-    double bnb = 0.5 * ((double)QQ(4, 2) + (double)QQ(4, 3));
-    double b1b = 0.5 * ((double)QQ(5, 2) + (double)QQ(5, 3));
-    double b2b = 0.5 * ((double)QQ(6, 2) + (double)QQ(6, 3));
-    double pb = 0.5 * ((double)QQ(8, 2) + (double)QQ(8, 3));
-#undef QQ
+    const double r2 = QQ(0, 2), r3 = QQ(0, 3), i2 = QQ(9, 2), i3 = QQ(9, 3);
+    const double rb = 0.5 * (r2 + r3);
+    const double vnb = 0.5 * fma((double)QQ(1, 3), i3, (double)QQ(1, 2) * i2);
+    const double v1b = 0.5 * fma((double)QQ(2, 3), i3, (double)QQ(2, 2) * i2);
+    const double v2b = 0.5 * fma((double)QQ(3, 3), i3, (double)QQ(3, 2) * i2);
+    const double bnb = 0.5 * ((double)QQ(4, 2) + (double)QQ(4, 3));
+    const double b1b = 0.5 * ((double)QQ(5, 2) + (double)QQ(5, 3));
+    const double b2b = 0.5 * ((double)QQ(6, 2) + (double)QQ(6, 3));
+    const double pb = 0.5 * ((double)QQ(8, 2) + (double)QQ(8, 3));
     // 1/rho, a and 1/a^2, c_f and 1/c_f^2 from one reciprocal square root
     // each, and c_s = a c_A / c_f with c_A = |B_n| rho^-1/2 (four fewer roots
     // and reciprocals, 1 % of the FP64 y sweep).  The FP64 WENO-Z kernels have
@@ -431,12 +433,13 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
     double irb, isr = 0.0;
     if constexpr (LEAN) { isr = frsq(rb); irb = isr * isr; }
     else irb = frcp(rb);
-    double a2 = gamma * pb * irb;
-    double bn2 = bnb * bnb * irb;
-    double bt2 = (b1b * b1b + b2b * b2b) * irb;
-    double dd = a2 - bn2;
-    double sqD = fsqrt(dd * dd + bt2 * (2.0 * a2 + 2.0 * bn2 + bt2));
-    double cf2 = 0.5 * (a2 + bn2 + bt2 + sqD);
+    const double a2 = gamma * pb * irb;
+    const double bn2 = bnb * bnb * irb;
+    const double btt = fma(b1b, b1b, b2b * b2b);
+    const double bt2 = btt * irb;
+    const double dd = a2 - bn2;
+    const double sqD = fsqrt(fma(dd, dd, bt2 * fma(2.0, a2, fma(2.0, bn2, bt2))));
+    const double cf2 = 0.5 * (a2 + bn2 + bt2 + sqD);
     double icf2, rcf = 0.0, cs2 = 0.0;
     if constexpr (LEAN) { rcf = frsq(cf2); icf2 = rcf * rcf; }
     else { icf2 = frcp(cf2); cs2 = a2 * bn2 * icf2; }
@@ -448,14 +451,14 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
         double P, Q;
         if (dd >= 0.0) { P = 0.5 * (dd + bt2 + sqD); Q = bt2 * cf2 * frcp(P); }
         else           { Q = 0.5 * (-dd + bt2 + sqD); P = bt2 * cf2 * frcp(Q); }
-        double isq = frcp(sqD);
-        double af2 = fmin(fmax(a2 * P * icf2 * isq, 0.0), 1.0);
-        double as2 = fmin(fmax(Q * isq, 0.0), 1.0);
+        const double isq = frcp(sqD);
+        const double af2 = fmin(fmax(a2 * P * icf2 * isq, 0.0), 1.0);
+        const double as2 = fmin(fmax(Q * isq, 0.0), 1.0);
         af = fsqrt(af2); as = fsqrt(as2);
     }
     double be1, be2;
     if (bt2 > 1e-24 * (a2 + bn2)) {
-        double ibt = frsq(b1b * b1b + b2b * b2b);
+        const double ibt = frsq(btt);
         be1 = b1b * ibt; be2 = b2b * ibt;
     } else {
         // B_t ~ 0: any unit vector spans the degenerate wave pairs; the first
@@ -464,7 +467,7 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
         // along one transverse axis) stays planar
         be1 = 1.0; be2 = 0.0;
     }
-    double sg = (bnb >= 0.0) ? 1.0 : -1.0;
+    const double sg = (bnb >= 0.0) ? 1.0 : -1.0;
     double cfm, csm, am_, ia2;
     if constexpr (LEAN) {
         const double ra = frsq(a2);
@@ -475,8 +478,8 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
         isr = frsq(rb); ia2 = frcp(a2);
     }
     const double sr = rb * isr;
-    double gm1 = gamma - 1.0;
-    double hv2 = 0.5 * (vnb * vnb + v1b * v1b + v2b * v2b);
+    const double gm1 = gamma - 1.0;
+    const double hv2 = 0.5 * fma(v2b, v2b, fma(v1b, v1b, vnb * vnb));
 
     // rows of L_W, per wave pair: odd (sign-flipping) and even parts, with
     // the 1/2 of the Lax-Friedrichs split folded in (exact power-of-two scale)
@@ -495,19 +498,19 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
     const T tv = T(vnb), t1 = T(v1b), t2 = T(v2b), th = T(hv2);
     const T tb1 = T(b1b), tb2 = T(b2b), e1 = T(be1), e2 = T(be2);
     auto xf = [&](T (&X)[7]) {
-        T w1 = X[1] - tv * X[0];
-        T w2 = X[2] - t1 * X[0];
-        T w3 = X[3] - t2 * X[0];
-        T w6 = th * X[0] - tv * X[1] - t1 * X[2] - t2 * X[3] - tb1 * X[4] - tb2 * X[5] + X[6];
-        T pv = e1 * w2 + e2 * w3, qv = e2 * w2 - e1 * w3;
-        T pB = e1 * X[4] + e2 * X[5], qB = e1 * X[5] - e2 * X[4];
+        const T w1 = fma(-tv, X[0], X[1]);
+        const T w2 = fma(-t1, X[0], X[2]);
+        const T w3 = fma(-t2, X[0], X[3]);
+        const T w6 = fma(-tb2, X[5], fma(-tb1, X[4], fma(-t2, X[3], fma(-t1, X[2], fma(-tv, X[1], fma(th, X[0], X[6]))))));
+        const T pv = fma(e1, w2, e2 * w3), qv = fma(e2, w2, -(e1 * w3));
+        const T pB = fma(e1, X[4], e2 * X[5]), qB = fma(e1, X[5], -(e2 * X[4]));
         X[1] = w1; X[2] = pv; X[3] = qv; X[4] = pB; X[5] = qB; X[6] = w6;
     };
 #pragma unroll
     for (int k = 0; k < 5; ++k) { xf(dY[k]); xf(dZ[k]); }
 
-    T G[7] = { T(0), T(0), T(0), T(0), T(0), T(0), T(0) };
-    const T teps = T(0.25) * eps;     // epsilon / 4 for phi_n
+    T G[7];
+    const T teps = T(0.25) * eps;     // epsilon / 4 for the weights
     const T ee[3] = { teps, teps * T(SQ18), teps * T(SQ12) };
 
     // One wave pair (sigma = -1 field index lo, sigma = +1 field index hi).
@@ -529,52 +532,53 @@ __device__ __forceinline__ void face_flux(const T *__restrict__ sq, int qs, int 
 
     T S, D;
     // fast pair (fields 0 and 6)
-    pair([&](const T (&X)[7], T &o, T &e) { o = kf1 * X[1] - kf2 * X[2]; e = kf4 * X[4] + kf6 * X[6]; },
+    pair([&](const T (&X)[7], T &o, T &e) { o = fma(kf1, X[1], -(kf2 * X[2])); e = fma(kf4, X[4], kf6 * X[6]); },
          0, 6, S, D);
     {
         const T c0 = T(rb * af), c1 = T(af * cfm), c2 = T(-as * csm * sg), c4 = T(as * sr * am_),
                 c6 = T(rb * af * a2);
-        G[0] += c0 * S; G[1] += c1 * D; G[2] += c2 * D; G[4] += c4 * S; G[6] += c6 * S;
+        G[0] = c0 * S; G[1] = c1 * D; G[2] = c2 * D; G[4] = c4 * S; G[6] = c6 * S;
     }
     // slow pair (fields 2 and 4)
-    pair([&](const T (&X)[7], T &o, T &e) { o = ks1 * X[1] + ks2 * X[2]; e = ks6 * X[6] - ks4 * X[4]; },
+    pair([&](const T (&X)[7], T &o, T &e) { o = fma(ks1, X[1], ks2 * X[2]); e = fma(ks6, X[6], -(ks4 * X[4])); },
          2, 4, S, D);
     {
         const T c0 = T(rb * as), c1 = T(as * csm), c2 = T(af * cfm * sg), c4 = T(-af * sr * am_),
                 c6 = T(rb * as * a2);
-        G[0] += c0 * S; G[1] += c1 * D; G[2] += c2 * D; G[4] += c4 * S; G[6] += c6 * S;
+        G[0] = fma(c0, S, G[0]); G[1] = fma(c1, D, G[1]); G[2] = fma(c2, D, G[2]); G[4] = fma(c4, S, G[4]);
+        G[6] = fma(c6, S, G[6]);
     }
     // Alfven pair (fields 1 and 5)
     pair([&](const T (&X)[7], T &o, T &e) { o = ka3 * X[3]; e = ka5 * X[5]; }, 1, 5, S, D);
-    G[3] += T(sg) * D;
-    G[5] += T(sr) * S;
+    G[3] = T(sg) * D;
+    G[5] = T(sr) * S;
     // entropy (field 3)
     {
         T df[5], du[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
-            df[k] = kh * (dY[k][0] - ke6 * dY[k][6]);
-            du[k] = kh * (dZ[k][0] - ke6 * dZ[k][6]);
+            df[k] = kh * fma(-ke6, dY[k][6], dY[k][0]);
+            du[k] = kh * fma(-ke6, dZ[k][6], dZ[k][0]);
         }
         G[0] += weno_field<T, LBL, WZ>(df, du, am[3], ee, dev);
     }
 
     // back to (vt1, vt2), (Bt1, Bt2) and through dU/dW, onto the mean flux
-    T gv1 = e1 * G[2] + e2 * G[3], gv2 = e2 * G[2] - e1 * G[3];
-    T gb1 = e1 * G[4] - e2 * G[5], gb2 = e2 * G[4] + e1 * G[5];
+    const T gv1 = fma(e1, G[2], e2 * G[3]), gv2 = fma(e2, G[2], -(e1 * G[3]));
+    const T gb1 = fma(e1, G[4], -(e2 * G[5])), gb2 = fma(e2, G[4], e1 * G[5]);
     const T trb = T(rb);
-    if constexpr (STASH) {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) Fs[c] = stash[c * TILE * ROWS];
+    if constexpr (REREAD) {
+        Fs[0] = *(const volatile T *)&QQ(1, 2) + *(const volatile T *)&QQ(1, 3);
     }
+#undef QQ
     out[0] = fma(T(0.5), Fs[0], G[0]);
-    out[1] = fma(T(0.5), Fs[1], tv * G[0] + trb * G[1]);
-    out[2] = fma(T(0.5), Fs[2], t1 * G[0] + trb * gv1);
-    out[3] = fma(T(0.5), Fs[3], t2 * G[0] + trb * gv2);
+    out[1] = fma(T(0.5), Fs[1], fma(trb, G[1], tv * G[0]));
+    out[2] = fma(T(0.5), Fs[2], fma(trb, gv1, t1 * G[0]));
+    out[3] = fma(T(0.5), Fs[3], fma(trb, gv2, t2 * G[0]));
     out[4] = fma(T(0.5), Fs[4], gb1);
     out[5] = fma(T(0.5), Fs[5], gb2);
-    out[6] = fma(T(0.5), Fs[6], th * G[0] + trb * (tv * G[1] + t1 * gv1 + t2 * gv2) + tb1 * gb1 + tb2 * gb2
-                                    + G[6] * T(igm1));
+    const T kin = fma(t2, gv2, fma(t1, gv1, tv * G[1]));
+    out[6] = fma(T(0.5), Fs[6], fma(G[6], T(igm1), fma(tb2, gb2, fma(tb1, gb1, fma(trb, kin, th * G[0])))));
 }
 
 // Linear fifth-order component-wise flux of the six staged cells (the cheap
@@ -945,10 +949,6 @@ __device__ __forceinline__ void fused_tile_store(const XFuse<T> &xf, const Fused
 // combination of rho, m, E.  Only the transverse-B fluxes (slots 4, 5) are
 // stored, once per face (the overlapping face by the next tile).
 constexpr int XFUSE_STRIDE = TILE * ROWS - 1;
-// The FP64 fused sweep keeps the mean flux (14 VGPRs) in hx during the fields:
-// it spilled 6 VGPRs without (6 % slower); the other FP64 sweeps fit.
-template <typename T> constexpr bool stash_x() { return sizeof(T) == 8; }
-template <typename T> constexpr int hx_slots() { return stash_x<T>() ? 7 : 5; }
 
 template <typename T, bool WZ = false, bool GLF = false, bool PRE = false>
 __device__ __forceinline__ void sweep_tile_xseg_fused(const T *__restrict__ u, T *__restrict__ flux,
@@ -966,8 +966,8 @@ __device__ __forceinline__ void sweep_tile_xseg_fused(const T *__restrict__ u, T
         stage_end();
         if (tid < X.nface) {
             T out[7];
-            face_flux<T, false, WZ, GLF, PRE, stash_x<T>()>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1, P.gamma,
-                                                            P.igm1, (T)P.eps, out, nullptr, P.ag, hx + tid);
+            face_flux<T, false, WZ, GLF, PRE, sizeof(T) == 8>(sq, XSEG_CELLS, X.cell_of(tid, X.row_of(tid)), 1,
+                                                              P.gamma, P.igm1, (T)P.eps, out, nullptr, P.ag);
             hx[0 * NH + tid] = out[0];
             hx[1 * NH + tid] = out[1];
             hx[2 * NH + tid] = out[2];

@@ -1,5 +1,6 @@
 // ww_update.hip -- launchers of the flux-difference / CT / RK update kernels
 // (device code in ww_update_dev.h).
+#include "ww_index.h"
 #include "ww_update_dev.h"
 
 namespace ww {
@@ -9,16 +10,12 @@ using up::UpdArgs;
 using up::rk_store;
 
 template <typename T>
-__global__ __launch_bounds__(256) void update_kernel(UpdArgs<T> a)
+__global__ __launch_bounds__(256) void update_kernel(UpdArgs<T> a, FastDiv n0, FastDiv n1, uint32_t ncell)
 {
-    const Geom &G = a.G;
-    const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
     if (t >= ncell) return;
-    int pos[3];
-    pos[0] = (int)(t % G.n[0]);
-    pos[1] = (int)((t / G.n[0]) % G.n[1]);
-    pos[2] = (int)(t / ((long)G.n[0] * G.n[1]));
+    const uint32_t r = n0.div(t), k = n1.div(r);
+    const int pos[3] = { (int)(t - r * n0.d), (int)(r - k * n1.d), (int)k };
     up::update_cell(a, pos);
 }
 
@@ -83,8 +80,10 @@ hipError_t launch_update(const T *u0, const T *acc_in, T *acc_out, T *out, const
         return hipGetLastError();
     }
     long ncell = (long)G.n[0] * G.n[1] * G.n[2];
-    dim3 grd((unsigned)((ncell + 255) / 256));
-    hipLaunchKernelGGL((update_kernel<T>), grd, dim3(256), 0, st, a);
+    // fewer than 2^24 blocks of 256 threads per launch: cell numbers fit 32 bits
+    if ((ncell + 255) / 256 >= (1L << 24)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((update_kernel<T>), dim3((unsigned)((ncell + 255) / 256)), dim3(256), 0, st, a,
+                       FastDiv((uint32_t)G.n[0]), FastDiv((uint32_t)G.n[1]), (uint32_t)ncell);
     return hipGetLastError();
 }
 
