@@ -84,6 +84,7 @@ struct wombat_weno {
     double *lfg;           // global LF speeds: partials, then 7 per direction (WW_LF_GLOBAL only)
     int slab;              // z-slab mode: planes per slab (0: whole box)
     int fuse;              // the x sweep does the rho, m, E update (3-D, long rows, no slabs, no router)
+    int small;             // the three sweeps run in one launch (boxes of few tiles)
     void *delay;           // slab mode: the last 3 output planes of a slab (8 vars x 3 planes)
     void *cellst;          // WW_B_FACE: the cell-centred state the sweeps read
     hipStream_t st;
@@ -356,6 +357,15 @@ int operator_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *acc_out
 {
     if (c->slab) return operator_slabs_t<T>(c, us, u0, acc_in, acc_out, out, k);
     int rc;
+    if (c->small && !c->router) {
+        // ghosts of the context's own stage arrays are read by nobody
+        const bool own = us == c->work[0] || us == c->work[1] || us == c->work[2];
+        T *const ff[3] = { (T *)c->ff[0], (T *)c->ff[1], (T *)c->ff[2] };
+        const ww::Phys P{ c->cfg.gamma, c->cfg.eps, 1.0 / (c->cfg.gamma - 1.0) };
+        WW_CHECK(c, ww::launch_small_sweeps<T>(us, ff, c->G, c->F, P, c->cfg.bc, !own, c->st));
+        WW_CHECK(c, ww::launch_update<T>(u0, acc_in, acc_out, out, ff[0], ff[1], ff[2], c->F, c->G, k, c->st));
+        return WW_OK;
+    }
     const bool stag = c->cellst != nullptr;
     if (stag) {
         // staggered storage: the sweeps read the cell-centred state (its
@@ -638,6 +648,7 @@ int wombat_weno_init(const wombat_weno_config *cfg, wombat_weno_t **out)
     c->st = (hipStream_t)cfg->stream;
     c->nblk = ww::cfl_blocks(c->G);
     c->fuse = !c->slab && c->G.act[0] && c->G.act[1] && c->G.act[2] && c->F[0].cnt[0] >= ww::sweep_x_fused_min_faces();
+    c->small = ww::small_box(*cfg, c->G, c->F);
     DevGuard dg(cfg->device);
     if (!dg.ok) { delete c; return fail_ctx(nullptr, WW_ERR_HIP, "hipSetDevice failed"); }
     ww::alloc_hook_reset();

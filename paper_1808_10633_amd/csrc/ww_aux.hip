@@ -12,6 +12,7 @@
 // assignment of cells to threads, wavefront butterflies and a fixed order
 // across the waves: results are bitwise reproducible.  No floating-point
 // atomics.
+#include "ww_ghost_dev.h"
 #include "ww_index.h"
 #include "ww_internal.h"
 
@@ -65,61 +66,14 @@ __global__ __launch_bounds__(256) void ghost_kernel(T *__restrict__ u, Geom G, i
     for (int v = 0; v < 8; ++v) u[di + v * G.sv] = u[si + v * G.sv];
 }
 
-// Every ghost zone of the box in one launch, for boxes without user faces:
-// the zones of a later axis copy those of the earlier ones, so a ghost cell's
-// value is that of the interior cell its coordinates map to axis by axis
-// (periodic image or nearest interior cell), and no order is needed.  Three
-// shells, numbered x fastest: the z zones over the padded x and y ranges, the
-// y zones over the padded x and interior z range, the x zones over the
-// interior y and z ranges.
+// Every ghost zone of the box in one launch, for boxes without user faces.
 constexpr long GHOST_ONE_LAUNCH = 1L << 18;    // ghost cells
 
-struct GhostArgs {
-    FastDiv px, py;            // padded x and y lengths
-    FastDiv nx6, ny;           // 2 gx, interior y length
-    FastDiv g6y;               // 2 gy
-    uint32_t nz_shell, ny_shell, total;
-    int per[6];                // face is periodic
-};
-
-__device__ __forceinline__ int ghost_image(int x, int n, int per_lo, int per_hi)
-{
-    if (x < 0) return per_lo ? x + n : 0;
-    if (x >= n) return per_hi ? x - n : n - 1;
-    return x;
-}
-
 template <typename T>
-__global__ __launch_bounds__(256) void ghost_all_kernel(T *__restrict__ u, Geom G, GhostArgs A)
+__global__ __launch_bounds__(256) void ghost_all_kernel(T *u, Geom G, GhostArgs A)
 {
     const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-    if (t >= A.total) return;
-    int p[3];
-    auto zone = [&](uint32_t g, int ax) { return (int)g < G.g[ax] ? (int)g - G.g[ax] : G.n[ax] + (int)g - G.g[ax]; };
-    if (t < A.nz_shell) {
-        const uint32_t r = A.px.div(t), g = A.py.div(r);
-        p[0] = (int)(t - r * A.px.d) - G.g[0];
-        p[1] = (int)(r - g * A.py.d) - G.g[1];
-        p[2] = zone(g, 2);
-    } else if (t < A.nz_shell + A.ny_shell) {
-        const uint32_t q = t - A.nz_shell, r = A.px.div(q), k = A.g6y.div(r);
-        p[0] = (int)(q - r * A.px.d) - G.g[0];
-        p[1] = zone(r - k * A.g6y.d, 1);
-        p[2] = (int)k;
-    } else {
-        const uint32_t q = t - A.nz_shell - A.ny_shell, r = A.nx6.div(q), k = A.ny.div(r);
-        p[0] = zone(q - r * A.nx6.d, 0);
-        p[1] = (int)(r - k * A.ny.d);
-        p[2] = (int)k;
-    }
-    long di = G.base, si = G.base;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-        di += (long)p[e] * G.s[e];
-        si += (long)ghost_image(p[e], G.n[e], A.per[2 * e], A.per[2 * e + 1]) * G.s[e];
-    }
-#pragma unroll
-    for (int v = 0; v < 8; ++v) u[di + v * G.sv] = u[si + v * G.sv];
+    if (t < A.total) ghost_fill(u, G, A, t);
 }
 
 // Reductions: a butterfly over the 64 lanes of each wavefront (__shfl_xor,
@@ -203,6 +157,23 @@ __device__ __forceinline__ void cell_pos(const Geom &G, const CellDiv &D, long c
         p[0] = (int)(ci - r * D.n0.d);
         p[1] = (int)(r - k * D.n1.d);
         p[2] = (int)k;
+        return;
+    }
+    p[0] = (int)(c % G.n[0]);
+    p[1] = (int)((c / G.n[0]) % G.n[1]);
+    p[2] = (int)(c / ((long)G.n[0] * G.n[1]));
+}
+
+// The same by the processor's division (the divergence kernel: with the form
+// above it took 358 us at 256^3 instead of 246, the copies and the CFL and sum
+// reductions being a little faster with it).
+__device__ __forceinline__ void cell_pos_plain(const Geom &G, long c, int (&p)[3])
+{
+    if ((long)G.n[0] * G.n[1] * G.n[2] <= 0x7fffffffL) {
+        const int ci = (int)c;
+        p[0] = ci % G.n[0];
+        p[1] = (ci / G.n[0]) % G.n[1];
+        p[2] = ci / (G.n[0] * G.n[1]);
         return;
     }
     p[0] = (int)(c % G.n[0]);
@@ -354,13 +325,13 @@ __global__ __launch_bounds__(RB) void sums_final(const double *part, int nblk, d
 
 // Corner divergence at corners i+1/2 (i = 0..n-1) on active axes.
 template <typename T>
-__global__ __launch_bounds__(RB) void divb_partial(const T *__restrict__ u, Geom G, CellDiv D, double *part)
+__global__ __launch_bounds__(RB) void divb_partial(const T *__restrict__ u, Geom G, double *part)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     double mx = 0.0, sm = 0.0;
     for (long c = (long)blockIdx.x * RB + threadIdx.x; c < ncell; c += (long)gridDim.x * RB) {
         int p[3];
-        cell_pos(G, D, c, p);
+        cell_pos_plain(G, c, p);
         double div = 0.0;
         for (int d = 0; d < 3; ++d) {
             if (!G.act[d]) continue;
@@ -421,13 +392,13 @@ __global__ __launch_bounds__(RB) void face_to_cell_kernel(const T *__restrict__ 
 
 // Face divergence of a staggered state (periodic box).
 template <typename T>
-__global__ __launch_bounds__(RB) void divb_face_partial(const T *__restrict__ u, Geom G, CellDiv D, double *part)
+__global__ __launch_bounds__(RB) void divb_face_partial(const T *__restrict__ u, Geom G, double *part)
 {
     const long ncell = (long)G.n[0] * G.n[1] * G.n[2];
     double mx = 0.0, sm = 0.0;
     for (long c = (long)blockIdx.x * RB + threadIdx.x; c < ncell; c += (long)gridDim.x * RB) {
         int p[3];
-        cell_pos(G, D, c, p);
+        cell_pos_plain(G, c, p);
         const long id = G.base + p[0] * G.s[0] + p[1] * G.s[1] + (long)p[2] * G.s[2];
         double div = 0.0;
         for (int d = 0; d < 3; ++d)
@@ -501,28 +472,17 @@ hipError_t launch_ghosts(T *u, const Geom &G, int axis, const int bc[6], hipStre
 template <typename T>
 hipError_t launch_ghosts_all(T *u, const Geom &G, const int bc[6], hipStream_t st)
 {
-    const long px = G.n[0] + 2 * G.g[0], py = G.n[1] + 2 * G.g[1];
-    const long nz = 2L * G.g[2] * px * py, ny = 2L * G.g[1] * px * G.n[2], nx = 2L * G.g[0] * G.n[1] * G.n[2];
     // One launch where the launches are the cost: at 32^3 (22 k ghost cells) it
     // takes 5 us, one per axis 3 x 5; at 256^3 (1.2 M) the three, whose shells
     // are each in one order, take 39 us, the one 57.
-    if (nx + ny + nz > GHOST_ONE_LAUNCH) {
+    if (ghost_cells(G) > GHOST_ONE_LAUNCH) {
         for (int ax = 0; ax < 3; ++ax) {
             hipError_t e = launch_ghosts<T>(u, G, ax, bc, st);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
     }
-    GhostArgs A;
-    A.px = FastDiv((uint32_t)px);
-    A.py = FastDiv((uint32_t)py);
-    A.nx6 = FastDiv((uint32_t)(G.act[0] ? 2 * G.g[0] : 1));
-    A.g6y = FastDiv((uint32_t)(G.act[1] ? 2 * G.g[1] : 1));
-    A.ny = FastDiv((uint32_t)G.n[1]);
-    A.nz_shell = (uint32_t)nz;
-    A.ny_shell = (uint32_t)ny;
-    A.total = (uint32_t)(nx + ny + nz);
-    for (int f = 0; f < 6; ++f) A.per[f] = bc[f] == 0;
+    const GhostArgs A = ghost_args(G, bc);
     hipLaunchKernelGGL((ghost_all_kernel<T>), dim3((A.total + 255) / 256), dim3(256), 0, st, u, G, A);
     return hipGetLastError();
 }
@@ -572,7 +532,7 @@ hipError_t launch_sums(const T *u, const Geom &G, double *part, int nblk, double
 template <typename T>
 hipError_t launch_divb(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL((divb_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, cell_div(G), part);
+    hipLaunchKernelGGL((divb_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(divb_final, dim3(1), dim3(RB), 0, st, part, nblk, (double)G.n[0] * G.n[1] * G.n[2], out);
@@ -591,7 +551,7 @@ hipError_t launch_face_to_cell(const T *u, T *uc, const Geom &G, hipStream_t st)
 template <typename T>
 hipError_t launch_divb_face(const T *u, const Geom &G, double *part, int nblk, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL((divb_face_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, cell_div(G), part);
+    hipLaunchKernelGGL((divb_face_partial<T>), dim3(nblk), dim3(RB), 0, st, u, G, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(divb_final, dim3(1), dim3(RB), 0, st, part, nblk, (double)G.n[0] * G.n[1] * G.n[2], out);

@@ -64,6 +64,11 @@ struct XTile {
         const int b1 = nf - fa0;
         return (t >= b1) + (t >= b1 + nf) + (t >= b1 + 2 * nf);
     }
+    WW_HD int row_of_cell(int c) const
+    {
+        const int o1 = nf + 5 - fa0;
+        return (c >= o1) + (c >= o1 + nf + 5) + (c >= o1 + 2 * (nf + 5));
+    }
     WW_HD int face_x(int t, int s) const { return t + fa0 - s * nf; }
     WW_HD int cell_of(int t, int s) const { return t + 5 * s; }      // of the face's first stencil cell
     // a plane holds one row (inactive axis) or at least five: at most one

@@ -124,6 +124,28 @@ inline bool has_user_face(const Geom &G, const int bc[6])
     return false;
 }
 
+// The sweeps of a small box in one launch, ghost cells taken from their
+// interior images; with ghosts set the ghost zones of u are filled too, by the
+// same launch.  No user faces, JS weights, per-stencil LF speeds.
+// A box is small up to SMALL_TILES tiles of 256 faces, 3-D boxes without the
+// fused x sweep (rows under 86 faces) up to twice as many.  Steps with one
+// launch and with three: FP64 64^3 (3.3 k tiles) 356 us, 495; FP32 254, 510;
+// FP64 80^3 (6.4 k) 763, 822; FP32 484, 640; 900^2 (6.4 k) 680, 635; 96^3
+// (11 k; fused x sweep) 1390, 950.
+constexpr long SMALL_TILES = 4096;
+long small_sweep_tiles(const Geom &G, const FaceBox F[3]);
+int sweep_x_fused_min_faces();
+template <typename T>
+hipError_t launch_small_sweeps(T *u, T *const flux[3], const Geom &G, const FaceBox F[3], const Phys &P,
+                               const int bc[6], bool ghosts, hipStream_t st);
+inline bool small_box(const wombat_weno_config &c, const Geom &G, const FaceBox F[3])
+{
+    return c.slab_planes == 0 && c.b_storage == WW_B_CELL && c.weights == WW_WEIGHTS_JS &&
+           c.lf_speed == WW_LF_LOCAL && !has_user_face(G, c.bc) &&
+           small_sweep_tiles(G, F) <=
+               (G.act[0] && G.act[1] && G.act[2] && F[0].cnt[0] < sweep_x_fused_min_faces() ? 2 : 1) * SMALL_TILES;
+}
+
 // CFL reduction: partial maxima / flags to scratch, then dt to d_dt and the
 // count of non-physical cells to d_flag, and both to mapped host memory h_dt,
 // h_flag unless NULL.

@@ -54,6 +54,21 @@ int rhs_t(const wombat_weno_config *cfg, const ww::Geom &G, const ww::FaceBox (&
           T *dudt)
 {
     hipStream_t st = (hipStream_t)cfg->stream;
+    T *ff[3] = { nullptr, nullptr, nullptr };
+    size_t off = 0;
+    for (int d = 0; d < 3; ++d) {
+        if (!G.act[d]) continue;
+        ff[d] = (T *)(buf + off);
+        off += align256(sizeof(T) * ww::NFC * F[d].sc);
+    }
+    if (ww::small_box(*cfg, G, F)) {
+        const ww::Phys P{ cfg->gamma, cfg->eps, 1.0 / (cfg->gamma - 1.0) };
+        hipError_t e = ww::launch_small_sweeps<T>(u, ff, G, F, P, cfg->bc, true, st);
+        if (e != hipSuccess) return hipfail(e, "sweeps");
+        const ww::StageCoef k{ 0, 0, 0.0, 0.0 };
+        e = ww::launch_update<T>(nullptr, nullptr, nullptr, dudt, ff[0], ff[1], ff[2], F, G, k, st);
+        return e == hipSuccess ? (int)WW_OK : hipfail(e, "update");
+    }
     // ghost zones, axis by axis, then the user faces of that axis (Sec. 2.2)
     const bool user = ww::has_user_face(G, cfg->bc);
     if (!user) {
@@ -72,13 +87,6 @@ int rhs_t(const wombat_weno_config *cfg, const ww::Geom &G, const ww::FaceBox (&
                 return fail(WW_ERR_USER_BC, "user boundary hook returned " + std::to_string(rc) + " on face " +
                                                 std::to_string(face));
         }
-    }
-    T *ff[3] = { nullptr, nullptr, nullptr };
-    size_t off = 0;
-    for (int d = 0; d < 3; ++d) {
-        if (!G.act[d]) continue;
-        ff[d] = (T *)(buf + off);
-        off += align256(sizeof(T) * ww::NFC * F[d].sc);
     }
     double *lfg = cfg->lf_speed == WW_LF_GLOBAL ? (double *)(buf + off) : nullptr;
     ww::Phys P{ cfg->gamma, cfg->eps, 1.0 / (cfg->gamma - 1.0) };

@@ -87,6 +87,8 @@ static int xtiles(const int (&n)[3], int slab)
                     CHECK(tc < X.ncell);
                     const long id = ub + X.state_rel(tc, jump);
                     CHECK(id == sidx(B, i - 3 + c, j, k) && id >= 0 && id < B.sv);
+                    const int sc = X.row_of_cell(tc);
+                    CHECK(sc == s && tc + X.fa0 - 3 - sc * (X.nf + 5) == i - 3 + c);
                 }
                 if (B.act[0] && B.act[1] && B.act[2] && i < B.n[0] && j >= 0 && j < B.n[1] && k >= 0 && k < B.n[2]) {
                     const long x2 = X.nf + 1, w = s >= X.sw;
