@@ -1,5 +1,6 @@
 // ww_batch.h -- internal types of the batched (many-patch) stage.
 #pragma once
+#include "ww_batch_plan.h"
 #include "ww_index.h"
 #include "ww_internal.h"
 
@@ -50,18 +51,33 @@ WW_HD void patch_geom(const int (&n)[3], double dl, double idl, Geom &G, FaceBox
     }
 }
 
+// Counts of a stage: the next item, then per split patch the items done per phase.
+inline int stage_counters(int nsplit) { return 1 + 3 * nsplit; }
+// Stage 0's CFL maximum (bit pattern of a positive double) and bad-cell count
+// of a split patch.
+struct SplitDt {
+    unsigned long long mx;
+    int bad;
+    int pad_;
+};
+
 template <typename T>
 struct BatchArgs {
     const PatchDesc *pd;
-    const int *order;          // patches by decreasing cost
-    int npatch;
-    int32_t *counter;          // next position in order (cleared before the stage)
+    const BatchItem *items;
+    const SplitDesc *split;
+    int nitem, nwhole;
+    int32_t *counter;          // the stage's counters (cleared before the stage)
+    SplitDt *sdt;              // cleared before stage 0
     const T *u0;               // arena of the step's initial state
-    T *us;                     // arena of the stage input (ghosts filled here)
+    T *us;                     // arena of the stage input
     T *acc;                    // arena of the RK accumulator
     T *out;                    // arena of the stage output
-    T *scratch;                // face fluxes, slot_elems per block
+    T *scratch;                // face fluxes of whole patches, slot_elems per block (or per patch if fewer)
     long slot_elems;
+    int nslot;
+    T *split_scratch;          // face fluxes of split patches
+    long split_elems;
     double *dt;                // per-patch time step (written in stage 0)
     int32_t *flag;             // per-patch count of non-physical cells
     double cfl;
@@ -79,8 +95,7 @@ hipError_t launch_batch_stage(const BatchArgs<T> &a, int ft, int nblocks, hipStr
 template <typename T>
 hipError_t batch_occupancy(int ft, int *blocks_per_cu);
 
-// Clear the n per-stage work counters of a step (a kernel, so that it can be
-// captured in a graph).
+// Clear n counters (a kernel, so that it can be captured in a graph).
 hipError_t launch_batch_reset(int32_t *counters, int n, hipStream_t st);
 
 }  // namespace ww

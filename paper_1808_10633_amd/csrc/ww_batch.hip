@@ -3,13 +3,16 @@
 //
 // The patches (arXiv:1808.10633, Sec. 2.2: the domain is cut into patches of
 // 18^3-32^3 zones with ghost zones, each computed independently once its
-// boundary zones are present) live in one arena.  Resident blocks take whole
-// patches, largest first, from a shared counter (one atomic per patch), so a
-// block that finishes early takes the next patch and the stage ends when the
-// work runs out, not when the unluckiest block does.  A block takes
-// each of its patches through the full stage: (stage 0 only) the patch's CFL
+// boundary zones are present) live in one arena.  Resident blocks take work
+// items from a shared counter (one atomic per item), so a block that finishes
+// early takes the next one and the stage ends when the work runs out, not when
+// the unluckiest block does.  An item is a whole patch, or a share of a patch
+// that would keep one block busy beyond the others' end (ww_batch_plan.h; 1024
+// FP32 patches of 16-64 cells per axis were bound by one block's 64^3 patch:
+// 71.5 ms a step as whole patches, 45.2 ms split).  A patch is taken through
+// the full stage: (stage 0 only) the patch's CFL
 // time step (0, and the patch left unadvanced, if any cell is non-physical),
-// x/y/z characteristic WENO sweeps into the block's own face-flux scratch
+// x/y/z characteristic WENO sweeps into the patch's face-flux scratch
 // (y and z first; the flattened x tiles also apply the rho, m, E update),
 // then CT and the B part of the RK update -- the same device functions as
 // the single-box kernels.  The patches are periodic, and the sweep tiles
@@ -22,7 +25,7 @@
 namespace ww {
 namespace {
 
-constexpr int RB = 256;
+constexpr int RB = BATCH_THREADS;
 
 // The patch number comes from a shared counter through LDS, so the compiler
 // takes everything read by it for per-lane data: geometry, strides and loop
@@ -41,17 +44,34 @@ __device__ __forceinline__ PatchDesc load_desc(const PatchDesc *pd, int p)
     __builtin_memcpy(&D, w, sizeof D);
     return D;
 }
+// One 32-bit word of a table that does not change during the kernel.
+__device__ __forceinline__ int load_word(const int *p)
+{
+    return *(const int __attribute__((address_space(4))) *)p;
+}
+__device__ __forceinline__ BatchItem load_item(const BatchItem *items, int i)
+{
+    const int *q = (const int *)(items + i);
+    return BatchItem{ load_word(q), load_word(q + 1), load_word(q + 2), load_word(q + 3),
+                      load_word(q + 4), load_word(q + 5), load_word(q + 6), load_word(q + 7) };
+}
+__device__ __forceinline__ SplitDesc load_split(const SplitDesc *split, int i)
+{
+    const int *q = (const int *)(split + i);
+    return SplitDesc{ { load_word(q), load_word(q + 1), load_word(q + 2) }, 0 };
+}
 
-// CFL time step of one patch (FP64 reduction in fixed order) and its count
-// of non-physical cells.
+// Largest signal speed sum and count of non-physical cells of cells c_lo ..
+// c_hi - 1 of a patch, in FP64 (valid in thread 0; neither depends on the
+// order).
 template <typename T>
-__device__ __forceinline__ void patch_dt(const T *__restrict__ u, const PatchDesc &D, const Geom &G, double gamma,
-                                         double cfl, double *dt_out, int32_t *flag_out)
+__device__ __forceinline__ void patch_speed(const T *__restrict__ u, const PatchDesc &D, const Geom &G, double gamma,
+                                            int c_lo, int c_hi, double &mx_out, int &bad_out)
 {
     __shared__ double smx[sw::ROWS];
     __shared__ int sfl[sw::ROWS];
     const int tid = threadIdx.x + sw::TILE * threadIdx.y;
-    const int ncell = G.n[0] * G.n[1] * G.n[2];     // < 2^31 for edges of at most 1024
+    const int ncell = c_hi;     // < 2^31 for edges of at most 1024
     const T *const ub = u + G.base;
     double mx = 0.0;
     int bad = 0;
@@ -60,7 +80,7 @@ __device__ __forceinline__ void patch_dt(const T *__restrict__ u, const PatchDes
     // memory latency per cell); the maximum and the count do not depend on
     // the order
     constexpr int DT_IT = 4;
-    for (int c0 = tid; c0 < ncell; c0 += DT_IT * RB) {
+    for (int c0 = c_lo + tid; c0 < ncell; c0 += DT_IT * RB) {
         T w[DT_IT][8];
 #pragma unroll
         for (int it = 0; it < DT_IT; ++it) {
@@ -105,13 +125,44 @@ __device__ __forceinline__ void patch_dt(const T *__restrict__ u, const PatchDes
     }
     if (threadIdx.x == 0) { smx[threadIdx.y] = mx; sfl[threadIdx.y] = bad; }
     __syncthreads();
-    if (tid == 0) {
+    if (tid == 0)
         for (int w = 1; w < sw::ROWS; ++w) { mx = fmax(mx, smx[w]); bad += sfl[w]; }
-        const bool ok = mx > 0.0 && bad == 0;
-        *dt_out = ok ? cfl / mx : 0.0;
-        *flag_out = bad > 0 ? bad : (ok ? 0 : 1);
+    mx_out = mx;
+    bad_out = bad;
+    __syncthreads();
+}
+__device__ __forceinline__ void store_dt(double mx, int bad, double cfl, double *dt_out, int32_t *flag_out)
+{
+    const bool ok = mx > 0.0 && bad == 0;
+    *dt_out = ok ? cfl / mx : 0.0;
+    *flag_out = bad > 0 ? bad : (ok ? 0 : 1);
+}
+
+// Waits and counts between the blocks of a split patch.  Every wave of the
+// counting block waits until its stores are in the L2, then one wave writes
+// the L2 back and counts; in the waiting block one wave drops the CU's and the
+// L2's stale lines before the others go on (a fence per wave costs four of
+// each).
+__device__ __forceinline__ void wait_count(const int32_t *count, int target)
+{
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target)
+            __builtin_amdgcn_s_sleep(16);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
+}
+// Returns the count after this item (in thread 0).
+__device__ __forceinline__ int count_done(int32_t *count)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    int n = 0;
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        n = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    }
+    return n;
 }
 
 // y or z sweep of a patch: tiles of 64 positions of the transverse plane (x
@@ -121,7 +172,8 @@ __device__ __forceinline__ void patch_dt(const T *__restrict__ u, const PatchDes
 // so that a tile's five halo rows are still in the L2.
 template <int DIR, int FT, typename T>
 __device__ __forceinline__ void sweep_yz_patch(const T *__restrict__ u, T *__restrict__ flux, const PatchDesc &D,
-                                               const Geom &G, const FaceBox &F, const Phys &P, T *sq)
+                                               const Geom &G, const FaceBox &F, const Phys &P, int t_lo, int t_hi,
+                                               T *sq)
 {
     constexpr int N = DIR, T1 = (DIR + 1) % 3, T2 = (DIR + 2) % 3, B = DIR == 1 ? 2 : 1;
     constexpr int NC = sw::TILE * (FT + 5), IT = (FT + 5 + sw::ROWS - 1) / sw::ROWS;
@@ -129,7 +181,8 @@ __device__ __forceinline__ void sweep_yz_patch(const T *__restrict__ u, T *__res
     const int gc[7] = { 0, 1 + N, 1 + T1, 1 + T2, 4, 5, 6 };
     const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int npos = F.cnt[0] * F.cnt[B];
-    for (int p0 = 0; p0 < npos; p0 += sw::TILE) {
+    for (int t = t_lo; t < t_hi; ++t) {
+        const int p0 = t * sw::TILE;
         const bool ok = p0 + lane < npos;
         // position - 1; lanes and rows beyond the end repeat the last one, so
         // that the loads need no branches (values loaded under one were kept,
@@ -180,7 +233,7 @@ __device__ __forceinline__ void sweep_yz_patch(const T *__restrict__ u, T *__res
 // same row and the row is interior.  Only the transverse-B fluxes of the x
 // faces are stored.  sq: NQ * XF_MAXC elements.  A flattened row holds at most
 // 266 cells and a patch edge 1024, so a variable is under 2^32 bytes and
-// every offset fits 32 bits.
+// every offset fits 32 bits.  Tiles t_lo .. t_hi - 1.
 constexpr int XF_FACES = sw::TILE * sw::ROWS;
 constexpr int XF_MAXC = 544;     // 4-cell rows: at most 53 rows of 10 cells
 inline int xflat_cells(int nx, long nrows)
@@ -192,8 +245,8 @@ inline int xflat_cells(int nx, long nrows)
 
 template <typename T>
 __device__ __forceinline__ void sweep_xflat_patch(const T *__restrict__ u, T *__restrict__ flux, const PatchDesc &D,
-                                                  const Geom &G, const FaceBox &F, const Phys &P, T *sq, T *hx,
-                                                  const XFuse<T> &xf)
+                                                  const Geom &G, const FaceBox &F, const Phys &P, int t_lo, int t_hi,
+                                                  T *sq, T *hx, const XFuse<T> &xf)
 {
     constexpr int STRIDE = XF_FACES - 1, IT = (XF_MAXC + RB - 1) / RB;
     const int tid = threadIdx.x + sw::TILE * threadIdx.y;
@@ -207,7 +260,8 @@ __device__ __forceinline__ void sweep_xflat_patch(const T *__restrict__ u, T *__
     B.acc_in = xf.acc_in + G.base;
     B.acc_out = xf.acc_out + G.base;
     B.out = xf.out + G.base;
-    for (int g0 = 0; g0 < total - 1; g0 += STRIDE) {
+    for (int t = t_lo; t < t_hi; ++t) {
+        const int g0 = t * STRIDE;
         sw::stage_begin();
         const int r_lo = (int)D.nf.div(g0);
         int r_hi = (int)D.nf.div(g0 + XF_FACES - 1);
@@ -268,6 +322,7 @@ __device__ __forceinline__ void sweep_xflat_patch(const T *__restrict__ u, T *__
 // per column instead of once per adjacent cell, as in update_cell), the loads
 // of level k+1 issued before the arithmetic of level k (two waves per SIMD
 // hide little latency).  Operands, expressions and order of march_column.
+// Shares t_lo .. t_hi - 1 of RB segments.
 template <typename T>
 struct BLevel {
     T x5h0, x5h1, y4h0, y4h1;          // FX5(i|i+1, j, k+1), FY4(i, j|j+1, k+1)
@@ -329,7 +384,8 @@ __device__ __forceinline__ void blevel_load(const BPatch<T> &B, uint32_t ox, uin
 
 template <typename T>
 __device__ __forceinline__ void update_b_patch(const T *fx, const T *fy, const T *fz, const PatchDesc &D,
-                                               const Geom &G, const FaceBox (&F)[3], const XFuse<T> &xf)
+                                               const Geom &G, const FaceBox (&F)[3], const XFuse<T> &xf, int t_lo,
+                                               int t_hi)
 {
     constexpr int KSEG = 16;
     BPatch<T> B;
@@ -347,8 +403,8 @@ __device__ __forceinline__ void update_b_patch(const T *fx, const T *fy, const T
     const T idx = T(G.idl[0]), idy = T(G.idl[1]), idz = T(G.idl[2]);
     const T q = T(0.25), bdt = T(c.bdt), cdt = T(c.cdt);
     const int tid = threadIdx.x + sw::TILE * threadIdx.y;
-    const int items = G.n[0] * G.n[1] * ((G.n[2] + KSEG - 1) / KSEG);
-    for (int it = tid; it < items; it += RB) {
+    const int items = min(G.n[0] * G.n[1] * ((G.n[2] + KSEG - 1) / KSEG), t_hi * RB);
+    for (int it = t_lo * RB + tid; it < items; it += RB) {
         const uint32_t col = D.nx.div(it), ks = D.ny.div(col);
         const uint32_t i = it - col * D.nx.d, j = col - ks * D.ny.d, k0 = ks * KSEG;
         const int k1 = min((int)k0 + KSEG, G.n[2]);
@@ -415,7 +471,7 @@ __device__ __forceinline__ void update_b_patch(const T *fx, const T *fy, const T
     }
 }
 
-// A patch's geometry and its block's face buffers, formed anew for each phase
+// A patch's geometry and its face buffers, formed anew for each phase
 // (the patch number is made opaque): kept through all phases, the scalars of
 // one stood in the way of the next, with a thousand moves of spilled scalar
 // registers.
@@ -425,12 +481,12 @@ struct Patch {
     Geom G;
     FaceBox F[3];
     T *fx, *fy, *fz;
-    __device__ __forceinline__ Patch(const BatchArgs<T> &a, int p, int block)
+    __device__ __forceinline__ Patch(const BatchArgs<T> &a, int p, T *ff)
     {
         asm volatile("" : "+s"(p));
         D = load_desc(a.pd, p);
         patch_geom(D.n, a.dl, a.idl, G, F);
-        fx = a.scratch + (long)block * a.slot_elems;
+        fx = ff;
         fy = fx + NFC * F[0].sc;
         fz = fy + NFC * F[1].sc;
     }
@@ -459,7 +515,6 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
     __shared__ T sq[sw::NQ * CMAX];
     __shared__ T hx[5 * XF_FACES];     // rho, m, E fluxes of the fused x tile
     __shared__ double sdt;
-    const int b = blockIdx.x;
     __shared__ int next;
     const int tid = threadIdx.x + sw::TILE * threadIdx.y;
     for (;;) {
@@ -467,42 +522,74 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
         __syncthreads();
         const int qn = __builtin_amdgcn_readfirstlane(next);
         __syncthreads();
-        if (qn >= a.npatch) break;
-        const int p = __builtin_amdgcn_readfirstlane(a.order[qn]);
-        if (a.s == 0) {
-            const Patch<T> Q(a, p, b);
-            patch_dt<T>(a.u0 + Q.D.soff, Q.D, Q.G, a.P.gamma, a.cfl, &a.dt[p], &a.flag[p]);
+        if (qn >= a.nitem) break;
+        const BatchItem I = load_item(a.items, qn);
+        const int p = I.patch;
+        const bool whole = I.split < 0;
+        int32_t *const done = a.counter + 1 + 3 * I.split;      // items done per phase (split patches)
+        T *ff;
+        if (whole) {
+            ff = a.scratch + (long)(a.nwhole <= a.nslot ? I.slot : (int)blockIdx.x) * a.slot_elems;
+            if (a.s == 0) {
+                const Patch<T> Q(a, p, ff);
+                double mx;
+                int bad;
+                patch_speed<T>(a.u0 + Q.D.soff, Q.D, Q.G, a.P.gamma, 0, Q.G.n[0] * Q.G.n[1] * Q.G.n[2], mx, bad);
+                if (tid == 0) store_dt(mx, bad, a.cfl, &a.dt[p], &a.flag[p]);
+            }
+        } else {
+            ff = a.split_scratch + (long)I.slot * a.split_elems;
+            // the slot's last patch done; the phases before this one done
+            // (stage 0: and the time step stored, counted as one more)
+            if (I.mask == ITEM_YZ && I.prev >= 0)
+                wait_count(a.counter + 1 + 3 * I.prev + 2, load_split(a.split, I.prev).n[2]);
+            if (I.mask == ITEM_X) wait_count(done, load_split(a.split, I.split).n[0] + (a.s == 0 ? 1 : 0));
+            if (I.mask == ITEM_B) wait_count(done + 1, load_split(a.split, I.split).n[1]);
         }
-        if (tid == 0) sdt = a.dt[p];
+        if (tid == 0) sdt = __hip_atomic_load(&a.dt[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         const double dtl = sdt;
-        const double dtp = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(dtl)),
-                                            __builtin_amdgcn_readfirstlane(__double2loint(dtl)));
+        double dtp = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(dtl)),
+                                      __builtin_amdgcn_readfirstlane(__double2loint(dtl)));
         __syncthreads();
-        if (dtp == 0.0) continue;        // non-physical patch: left unadvanced
-        // no ghost fill: the sweep tiles stage ghost cells from their
-        // periodic images.  y and z sweeps, then the x sweep: on the flattened
-        // x tiles it also differences every direction's rho, m, E fluxes and
-        // applies their RK update, and the update is left with constrained
-        // transport
-        {
-            const Patch<T> Q(a, p, b);
-            sweep_yz_patch<1, FT, T>(a.us + Q.D.soff, Q.fy, Q.D, Q.G, Q.F[1], a.P, sq);
-        }
-        {
-            const Patch<T> Q(a, p, b);
-            sweep_yz_patch<2, FT, T>(a.us + Q.D.soff, Q.fz, Q.D, Q.G, Q.F[2], a.P, sq);
-        }
-        if (load_desc(a.pd, p).xflat != 0) {
+        // a non-physical patch has dt = 0 and is left unadvanced; the y and z
+        // phase of a split patch in stage 0 runs before its dt is known
+        const bool live = dtp != 0.0 || (!whole && I.mask == ITEM_YZ && a.s == 0);
+        if (live && (I.mask & ITEM_YZ)) {
+            // no ghost fill: the sweep tiles stage ghost cells from their
+            // periodic images
+            int lo = I.lo, hi = I.hi, ny;
             {
-                const Patch<T> Q(a, p, b);
-                sweep_xflat_patch<T>(a.us + Q.D.soff, Q.fx, Q.D, Q.G, Q.F[0], a.P, sq, hx, Q.xfuse(a, dtp));
+                const Patch<T> Q(a, p, ff);
+                ny = (Q.F[1].cnt[0] * Q.F[1].cnt[2] + sw::TILE - 1) / sw::TILE;
+                if (whole) { lo = 0; hi = ny; }
+                sweep_yz_patch<1, FT, T>(a.us + Q.D.soff, Q.fy, Q.D, Q.G, Q.F[1], a.P, lo, min(hi, ny), sq);
             }
-            const Patch<T> Q(a, p, b);
-            update_b_patch<T>(Q.fx, Q.fy, Q.fz, Q.D, Q.G, Q.F, Q.xfuse(a, dtp));
-        } else {
             {
-                const Patch<T> Q(a, p, b);
+                const Patch<T> Q(a, p, ff);
+                const int nz = (Q.F[2].cnt[0] * Q.F[2].cnt[1] + sw::TILE - 1) / sw::TILE;
+                sweep_yz_patch<2, FT, T>(a.us + Q.D.soff, Q.fz, Q.D, Q.G, Q.F[2], a.P, whole ? 0 : max(lo - ny, 0),
+                                         whole ? nz : hi - ny, sq);
+            }
+        }
+        // the x sweep: on the flattened x tiles it also differences every
+        // direction's rho, m, E fluxes and applies their RK update, and the
+        // update is left with constrained transport
+        const bool flat = load_desc(a.pd, p).xflat != 0;
+        if (live && flat && (I.mask & ITEM_X)) {
+            const Patch<T> Q(a, p, ff);
+            const int nt = ((int)Q.F[0].sc - 1 + XF_FACES - 2) / (XF_FACES - 1);
+            sweep_xflat_patch<T>(a.us + Q.D.soff, Q.fx, Q.D, Q.G, Q.F[0], a.P, whole ? 0 : I.lo, whole ? nt : I.hi, sq,
+                                 hx, Q.xfuse(a, dtp));
+        }
+        if (live && flat && (I.mask & ITEM_B)) {
+            const Patch<T> Q(a, p, ff);
+            update_b_patch<T>(Q.fx, Q.fy, Q.fz, Q.D, Q.G, Q.F, Q.xfuse(a, dtp), whole ? 0 : I.lo,
+                              whole ? 0x7fffffff / RB : I.hi);
+        }
+        if (live && !flat) {         // whole patches only
+            {
+                const Patch<T> Q(a, p, ff);
                 long na, nb;
                 sw::xrows_tiles(Q.F[0], na, nb);
                 for (long tb = 0; tb < nb; ++tb)
@@ -512,7 +599,7 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
             // every variable: one thread per cell (marching with the hydro
             // fluxes carried too measured 1.5x slower here: more registers,
             // and whole passes of a small patch's columns half idle)
-            const Patch<T> Q(a, p, b);
+            const Patch<T> Q(a, p, ff);
             up::UpdArgs<T> ua;
             ua.u0 = a.u0 + Q.D.soff;
             ua.acc_in = a.acc + Q.D.soff;
@@ -531,6 +618,36 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
                 pos[1] = (c / Q.G.n[0]) % Q.G.n[1];
                 pos[2] = c / (Q.G.n[0] * Q.G.n[1]);
                 up::update_cell(ua, pos);
+            }
+        }
+        if (!whole) {
+            const int phase = I.mask == ITEM_YZ ? 0 : I.mask == ITEM_X ? 1 : 2;
+            if (phase == 0 && a.s == 0) {
+                // this item's share of the patch's cells for the CFL maximum
+                // (order-independent: a maximum and an integer sum)
+                const Patch<T> Q(a, p, ff);
+                const SplitDesc S = load_split(a.split, I.split);
+                const int ncell = Q.G.n[0] * Q.G.n[1] * Q.G.n[2];
+                const int c_lo = (int)((long)ncell * I.part / S.n[0]), c_hi = (int)((long)ncell * (I.part + 1) / S.n[0]);
+                double mx;
+                int bad;
+                patch_speed<T>(a.u0 + Q.D.soff, Q.D, Q.G, a.P.gamma, c_lo, c_hi, mx, bad);
+                SplitDt *const dt = a.sdt + I.split;
+                if (tid == 0) {
+                    __hip_atomic_fetch_max(&dt->mx, (unsigned long long)__double_as_longlong(mx), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(&dt->bad, bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (count_done(done) == S.n[0]) {                 // thread 0 of the last item
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    const unsigned long long m = __hip_atomic_load(&dt->mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int nbad = __hip_atomic_load(&dt->bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    store_dt(__longlong_as_double((long long)m), nbad, a.cfl, &a.dt[p], &a.flag[p]);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            } else {
+                count_done(done + phase);
             }
         }
         __syncthreads();     // the scratch is reused by the next patch
@@ -584,12 +701,13 @@ hipError_t launch_batch_stage(const BatchArgs<T> &a, int ft, int nblocks, hipStr
 
 __global__ void batch_reset_kernel(int32_t *c, int n)
 {
-    if ((int)threadIdx.x < n) c[threadIdx.x] = 0;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) c[i] = 0;
 }
 
 hipError_t launch_batch_reset(int32_t *counters, int n, hipStream_t st)
 {
-    hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(64), 0, st, counters, n);
+    hipLaunchKernelGGL(batch_reset_kernel, dim3((n + 255) / 256), dim3(256), 0, st, counters, n);
     return hipGetLastError();
 }
 

@@ -1,7 +1,6 @@
-// ww_batch_api.hip -- C ABI of the batched form: arena layout, the
-// largest-first patch order the resident blocks take their work from, graph
-// capture and replay of whole RK4 steps, and the autotuner of the launch
-// shape.
+// ww_batch_api.hip -- C ABI of the batched form: arena layout, the list of
+// work items the resident blocks take their work from, graph capture and
+// replay of whole RK4 steps, and the autotuner of the launch shape.
 #include "../../include/wombat_weno.h"
 #include "ww_batch.h"
 
@@ -11,8 +10,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
-#include <numeric>
-#include <queue>
 #include <string>
 #include <vector>
 
@@ -29,15 +26,17 @@ struct wombat_weno_batch {
     std::vector<PatchDesc> hpd;
     long arena;                     // elements per arena
     size_t esize;
-    long slot_elems;
+    ww::BatchPlan plan;
     int ncu;
     int ft, bpc, nblocks;           // launch shape: faces per y/z tile, blocks per CU
     int maxblocks;
     PatchDesc *pd;
-    int *order;            // patches by decreasing cost
-    int32_t *counters;     // work counters of the 4 stages of a step
+    ww::BatchItem *items;           // work items of a stage
+    ww::SplitDesc *split;
+    ww::SplitDt *sdt;               // stage 0's CFL maxima of the split patches, then ..
+    int32_t *counters;              // .. the counters of the 4 stages of a step
     void *work[3];                  // A, B, acc arenas
-    void *scratch;
+    void *scratch, *split_scratch;  // face fluxes of whole and of split patches
     double *dt;
     int32_t *flag;
     hipStream_t st, cap;            // user stream, capture stream
@@ -88,27 +87,9 @@ struct DevGuard {
     }
 };
 
-double patch_cost(const int n[3])
-{
-    double c = 0.0;
-    for (int d = 0; d < 3; ++d) {
-        double f = n[d] + 1.0;
-        for (int e = 0; e < 3; ++e) if (e != d) f *= n[e] + 2.0;
-        c += f;
-    }
-    return c;
-}
-
-// Patches by decreasing estimated cost (ties by index).
-void make_order(const std::vector<int> &dims, std::vector<int> &order)
-{
-    const int np = (int)dims.size() / 3;
-    order.resize(np);
-    std::iota(order.begin(), order.end(), 0);
-    std::vector<double> cost(np);
-    for (int p = 0; p < np; ++p) cost[p] = patch_cost(&dims[3 * p]);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-}
+// 32-bit words of the CFL maxima and of a step's counters, which follow them.
+int sdt_words(const wombat_weno_batch_t *b) { return (int)(b->plan.split.size() * (sizeof(ww::SplitDt) / 4)); }
+int stage_words(const wombat_weno_batch_t *b) { return ww::stage_counters((int)b->plan.split.size()); }
 
 int set_shape(wombat_weno_batch_t *b, int ft, int bpc)
 {
@@ -135,15 +116,21 @@ BatchArgs<T> stage_args(wombat_weno_batch_t *b, int s, T *u0, T *us, T *acc, T *
 {
     BatchArgs<T> a;
     a.pd = b->pd;
-    a.order = b->order;
-    a.npatch = (int)(b->dims.size() / 3);
-    a.counter = b->counters + s;
+    a.items = b->items;
+    a.split = b->split;
+    a.nitem = (int)b->plan.items.size();
+    a.nwhole = b->plan.nwhole;
+    a.counter = b->counters + s * stage_words(b);
+    a.sdt = b->sdt;
     a.u0 = u0;
     a.us = us;
     a.acc = acc;
     a.out = out;
     a.scratch = (T *)b->scratch;
-    a.slot_elems = b->slot_elems;
+    a.slot_elems = b->plan.whole_elems;
+    a.nslot = b->maxblocks;
+    a.split_scratch = (T *)b->split_scratch;
+    a.split_elems = b->plan.split_elems;
     a.dt = b->dt;
     a.flag = b->flag;
     a.cfl = b->cfg.cfl;
@@ -164,7 +151,7 @@ int launch_step_t(wombat_weno_batch_t *b, T *u, hipStream_t st)
     T *A = (T *)b->work[0], *B = (T *)b->work[1], *acc = (T *)b->work[2];
     T *in[4] = { u, A, B, A };
     T *out[4] = { A, B, A, u };
-    WB_CHECK(b, ww::launch_batch_reset(b->counters, 4, st));
+    WB_CHECK(b, ww::launch_batch_reset((int32_t *)b->sdt, sdt_words(b) + 4 * stage_words(b), st));
     for (int s = 0; s < 4; ++s)
         WB_CHECK(b, ww::launch_batch_stage<T>(stage_args<T>(b, s, u, in[s], acc, out[s], bw[s], cw[s]), b->ft,
                                               b->nblocks, st));
@@ -178,7 +165,7 @@ int tune_prepare_t(wombat_weno_batch_t *b, const T *u)
 {
     T *A = (T *)b->work[0], *B = (T *)b->work[1], *acc = (T *)b->work[2];
     WB_CHECK(b, hipMemcpyAsync(A, u, b->esize * b->arena, hipMemcpyDeviceToDevice, b->st));
-    WB_CHECK(b, ww::launch_batch_reset(b->counters, 4, b->st));
+    WB_CHECK(b, ww::launch_batch_reset((int32_t *)b->sdt, sdt_words(b) + 4 * stage_words(b), b->st));
     WB_CHECK(b, ww::launch_batch_stage<T>(stage_args<T>(b, 0, A, A, acc, B, 1.0 / 6.0, 0.5), b->ft, b->nblocks,
                                           b->st));
     return WW_OK;
@@ -191,7 +178,7 @@ template <typename T>
 int tune_stage_t(wombat_weno_batch_t *b, float *ms)
 {
     T *A = (T *)b->work[0], *B = (T *)b->work[1], *acc = (T *)b->work[2];
-    WB_CHECK(b, ww::launch_batch_reset(b->counters + 1, 1, b->st));
+    WB_CHECK(b, ww::launch_batch_reset(b->counters + stage_words(b), stage_words(b), b->st));
     WB_CHECK(b, hipEventRecord(b->ev[0], b->st));
     WB_CHECK(b, ww::launch_batch_stage<T>(stage_args<T>(b, 1, A, B, acc, A, 0.0, 0.0), b->ft, b->nblocks, b->st));
     WB_CHECK(b, hipEventRecord(b->ev[1], b->st));
@@ -219,9 +206,11 @@ void release(wombat_weno_batch_t *b)
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (int i = 0; i < 3; ++i) if (b->work[i]) (void)hipFree(b->work[i]);
     if (b->scratch) (void)hipFree(b->scratch);
+    if (b->split_scratch) (void)hipFree(b->split_scratch);
     if (b->pd) (void)hipFree(b->pd);
-    if (b->order) (void)hipFree(b->order);
-    if (b->counters) (void)hipFree(b->counters);
+    if (b->items) (void)hipFree(b->items);
+    if (b->split) (void)hipFree(b->split);
+    if (b->sdt) (void)hipFree(b->sdt);
     if (b->dt) (void)hipFree(b->dt);
     if (b->flag) (void)hipFree(b->flag);
     if (b->cap) (void)hipStreamDestroy(b->cap);
@@ -301,6 +290,7 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
     if (!dg.ok) { delete b; return bfail(nullptr, WW_ERR_HIP, "hipSetDevice failed"); }
     // arena layout (each patch aligned to 64 elements) and patch table
     long off = 0, slot = 0;
+    std::vector<long> felems(npatch);
     b->hpd.resize(npatch);
     b->soff.resize(npatch);
     for (int p = 0; p < npatch; ++p) {
@@ -321,15 +311,21 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
         D.nxp = ww::FastDiv(n[0] + 6);
         b->soff[p] = off;
         off += (8 * G.sv + 63) / 64 * 64;
-        slot = std::max(slot, (long)ww::NFC * (F[0].sc + F[1].sc + F[2].sc));
+        felems[p] = ((long)ww::NFC * (F[0].sc + F[1].sc + F[2].sc) + 63) / 64 * 64;
+        slot = std::max(slot, felems[p]);
     }
     b->arena = off;
-    b->slot_elems = (slot + 63) / 64 * 64;
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, cfg->device) != hipSuccess || ncu < 1)
         ncu = 256;
     b->ncu = ncu;
     b->maxblocks = 4 * ncu;
+    // For the resident blocks of the usual shapes (FP32 three blocks per CU,
+    // FP64 two), with no more face scratch than the largest patch's per block.
+    // Split x sweeps take the flattened tiles.
+    b->plan = ww::batch_plan(
+        npatch, dims, (cfg->precision == WW_FP64 ? 2 : 3) * ncu, b->maxblocks, slot * b->maxblocks,
+        [&](int p) { return felems[p]; }, [&](int p) { return b->hpd[p].xflat != 0; });
     auto fail_oom = [&](const char *what) {
         release(b);
         delete b;
@@ -338,16 +334,26 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
     ww::alloc_hook_reset();
     for (int i = 0; i < 3; ++i)
         if (ww::dev_alloc(&b->work[i], b->esize * b->arena) != hipSuccess) return fail_oom("work arenas");
-    if (ww::dev_alloc(&b->scratch, b->esize * b->slot_elems * b->maxblocks) != hipSuccess) return fail_oom("face scratch");
+    const ww::BatchPlan &P = b->plan;
+    if (P.nwhole > 0 &&
+        ww::dev_alloc(&b->scratch, b->esize * P.whole_elems * std::min(P.nwhole, b->maxblocks)) != hipSuccess)
+        return fail_oom("face scratch");
+    if (P.nslot > 0 && ww::dev_alloc(&b->split_scratch, b->esize * P.split_elems * P.nslot) != hipSuccess)
+        return fail_oom("face scratch");
     if (ww::dev_alloc((void **)&b->pd, sizeof(PatchDesc) * npatch) != hipSuccess) return fail_oom("patch table");
-    if (ww::dev_alloc((void **)&b->order, sizeof(int) * npatch) != hipSuccess) return fail_oom("patch order");
-    if (ww::dev_alloc((void **)&b->counters, sizeof(int32_t) * 4) != hipSuccess) return fail_oom("work counters");
+    if (ww::dev_alloc((void **)&b->items, sizeof(ww::BatchItem) * P.items.size()) != hipSuccess)
+        return fail_oom("work items");
+    if (!P.split.empty() && ww::dev_alloc((void **)&b->split, sizeof(ww::SplitDesc) * P.split.size()) != hipSuccess)
+        return fail_oom("work items");
+    if (ww::dev_alloc((void **)&b->sdt, sizeof(int32_t) * (sdt_words(b) + 4 * stage_words(b))) != hipSuccess)
+        return fail_oom("work counters");
+    b->counters = (int32_t *)b->sdt + sdt_words(b);
     if (ww::dev_alloc((void **)&b->dt, sizeof(double) * npatch) != hipSuccess) return fail_oom("dt");
     if (ww::dev_alloc((void **)&b->flag, sizeof(int32_t) * npatch) != hipSuccess) return fail_oom("flags");
-    std::vector<int> order;
-    make_order(b->dims, order);
     if (hipMemcpy(b->pd, b->hpd.data(), sizeof(PatchDesc) * npatch, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(b->order, order.data(), sizeof(int) * npatch, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(b->items, P.items.data(), sizeof(ww::BatchItem) * P.items.size(), hipMemcpyHostToDevice) != hipSuccess ||
+        (!P.split.empty() && hipMemcpy(b->split, P.split.data(), sizeof(ww::SplitDesc) * P.split.size(),
+                                       hipMemcpyHostToDevice) != hipSuccess) ||
         hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreate(&b->ev[0]) != hipSuccess || hipEventCreate(&b->ev[1]) != hipSuccess) {
         release(b);
