@@ -83,7 +83,7 @@ struct wombat_weno {
     int64_t fallbacks;     // routed steps redone with full WENO
     double *lfg;           // global LF speeds: partials, then 7 per direction (WW_LF_GLOBAL only)
     int slab;              // z-slab mode: planes per slab (0: whole box)
-    int fuse;              // the x sweep does the rho, m, E update (3-D, long rows, no slabs, no router)
+    int fuse;              // the x sweep does the rho, m, E update (3-D, long rows; in slabs: stages with out != us)
     int small;             // the three sweeps run in one launch (boxes of few tiles)
     void *delay;           // slab mode: the last 3 output planes of a slab (8 vars x 3 planes)
     void *cellst;          // WW_B_FACE: the cell-centred state the sweeps read
@@ -300,6 +300,9 @@ int fill_ghosts_t(wombat_weno_t *c, T *u)
 // delay buffer and are copied over the input after the next slab's sweeps.
 // Each face flux and cell update is computed by the same kernels and code as
 // in the whole-box stage, so the results are identical bit for bit.
+// The fused x sweep writes cells that its neighbouring tiles still read as
+// halo, so it serves the stages that write another array (the first and last
+// of a step, L(U)): 256^3 FP64 in slabs of 64 planes, 21.4 -> 19.7 ms a step.
 template <typename T>
 int operator_slabs_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *acc_out, T *out,
                      const ww::StageCoef &k)
@@ -308,7 +311,9 @@ int operator_slabs_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *a
     if (rc) return rc;
     const ww::Geom &G = c->G;
     const int nz = G.n[2], kz = c->slab;
-    const bool inplace = out == us;
+    const bool inplace = out == us, fuse = c->fuse && !inplace;
+    ww::StageCoef kb = k;
+    kb.bonly = fuse ? 1 : 0;
     ww::Phys P{ c->cfg.gamma, c->cfg.eps, 1.0 / (c->cfg.gamma - 1.0) };
     T *D = (T *)c->delay;
     const long dsv = 3 * G.s[2];                          // variable stride of the delay buffer
@@ -319,8 +324,17 @@ int operator_slabs_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *a
         ww::Geom S;
         ww::FaceBox F[3];
         slab_geom(G, k0, nk, S, F);
-        for (int d = 0; d < 3; ++d)
-            if (G.act[d]) WW_CHECK(c, ww::launch_sweep<T>(d, us, (T *)c->ff[d], S, F[d], P, c->cfg.weights, c->st));
+        for (int m = 0; m < 3; ++m) {
+            const int d = fuse ? (m + 1) % 3 : m;
+            if (!G.act[d]) continue;
+            if (fuse && d == 0) {
+                const ww::XFuse<T> xf{ u0, acc_in, acc_out, out, (const T *)c->ff[1], (const T *)c->ff[2],
+                                       F[1], F[2], k };
+                WW_CHECK(c, ww::launch_sweep_x_fused<T>(us, (T *)c->ff[0], S, F[0], P, c->cfg.weights, xf, c->st));
+                continue;
+            }
+            WW_CHECK(c, ww::launch_sweep<T>(d, us, (T *)c->ff[d], S, F[d], P, c->cfg.weights, c->st));
+        }
         if (pending >= 0) {
             // the previous slab's last three planes: their input has been read
             for (int v = 0; v < 8; ++v)
@@ -344,7 +358,7 @@ int operator_slabs_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *a
                                              dbase - S2.base, dsv));
             pending = k1 - 3;
         } else {
-            WW_CHECK(c, ww::launch_update<T>(u0, acc_in, acc_out, out, f0, f1, f2, F, S, k, c->st));
+            WW_CHECK(c, ww::launch_update<T>(u0, acc_in, acc_out, out, f0, f1, f2, F, S, kb, c->st));
         }
     }
     return WW_OK;
@@ -502,7 +516,8 @@ int time_kernels_t(wombat_weno_t *c, T *u, int reps, double ms[7])
     // SSP-RK3 stages), u0 = u, acc and out in the work arrays, dt = 0 so that
     // repeated launches leave acc and out unchanged; the mean of the forms.
     // With the fused x sweep, the x sweep is timed in those forms too (the y
-    // and z fluxes it reads are those of u), and the update in its B-only form.
+    // and z fluxes it reads are those of u), and the update in its B-only form;
+    // in slabs the second and third stage work in place, with separate sweeps.
     const bool fuse = c->fuse && !c->router;
     const T *fx = (const T *)c->ff[0], *fy = (const T *)c->ff[1], *fz = (const T *)c->ff[2];
     T *acc = (T *)c->work[c->slab ? 1 : 2], *out = (T *)c->work[0];
@@ -511,7 +526,7 @@ int time_kernels_t(wombat_weno_t *c, T *u, int reps, double ms[7])
     auto form = [&](int s) {
         ww::StageCoef k = ssp ? ww::StageCoef{ 2, s, 0.0, 0.0, 1.0, s == 0 ? 0.0 : 0.5 }
                               : ww::StageCoef{ 1, s, 0.0, 0.0 };
-        k.bonly = fuse ? 1 : 0;
+        k.bonly = fuse && !(c->slab && (s == 1 || s == 2)) ? 1 : 0;
         return k;
     };
     auto form_acc_in = [&](int s) {
@@ -525,11 +540,16 @@ int time_kernels_t(wombat_weno_t *c, T *u, int reps, double ms[7])
         if (fuse && d == 0) {
             double sum = 0.0;
             for (int s = 0; s < nform; ++s) {
-                const ww::XFuse<T> xf{ u, form_acc_in(s), acc, out, fy, fz, c->F[1], c->F[2], form(s) };
                 double t = 0.0;
                 if ((rc = time_launches(c, reps, [&] {
-                         return chk(ww::launch_sweep_x_fused<T>(u, (T *)c->ff[0], c->G, c->F[0], P, c->cfg.weights,
-                                                                xf, c->st));
+                         return for_slabs(c, [&](const ww::Geom &S, const ww::FaceBox *F) {
+                             const ww::StageCoef k = form(s);
+                             if (!k.bonly)
+                                 return chk(ww::launch_sweep<T>(0, u, (T *)c->ff[0], S, F[0], P, c->cfg.weights, c->st));
+                             const ww::XFuse<T> xf{ u, form_acc_in(s), acc, out, fy, fz, F[1], F[2], k };
+                             return chk(ww::launch_sweep_x_fused<T>(u, (T *)c->ff[0], S, F[0], P, c->cfg.weights, xf,
+                                                                    c->st));
+                         });
                      }, t)))
                     return rc;
                 sum += t;
@@ -647,7 +667,7 @@ int wombat_weno_init(const wombat_weno_config *cfg, wombat_weno_t **out)
     c->elems = state_elems(cfg);
     c->st = (hipStream_t)cfg->stream;
     c->nblk = ww::cfl_blocks(c->G);
-    c->fuse = !c->slab && c->G.act[0] && c->G.act[1] && c->G.act[2] && c->F[0].cnt[0] >= ww::sweep_x_fused_min_faces();
+    c->fuse = c->G.act[0] && c->G.act[1] && c->G.act[2] && c->F[0].cnt[0] >= ww::sweep_x_fused_min_faces();
     c->small = ww::small_box(*cfg, c->G, c->F);
     DevGuard dg(cfg->device);
     if (!dg.ok) { delete c; return fail_ctx(nullptr, WW_ERR_HIP, "hipSetDevice failed"); }
