@@ -604,11 +604,18 @@ __global__ __launch_bounds__(64) void router_sample_kernel(const T *__restrict__
 // take the decisions stored in mask (one byte per face, 1 = troubled) by an
 // earlier evaluation instead of evaluating the network; otherwise store them.
 // Queue entries pack the face position (x+1, y+1, z+1) in 21 bits each.
-// FUSED (x sweep, flattened 256-face tiles, after the y and z sweeps): the
-// tile also applies the rho, m, E update (RK stage xf.c) to every cell whose
-// two x faces lie in the tile and are both smooth, with their fluxes from
-// LDS (the fused x sweep's tail); the other cells are left to
-// xfix_queue_kernel and xfix_bound_kernel.
+// Tiles as the plain sweeps': x in flattened segments of 256 faces that overlap
+// by one (rows of XSEG_MIN faces or more; the shared face belongs to the later
+// tile) or 4 rows x 64 faces, y/z 32 positions x 8 faces, each XCD walking
+// columns (y/z) or consecutive tiles (long x rows) so that halo rows and the
+// faces that neighbouring cells share come from its L2.
+// FUSED (x sweep in flattened tiles, after the y and z sweeps): the tile also
+// applies the rho, m, E update (RK stage xf.c) to every cell whose two x faces
+// are both smooth, with their fluxes from LDS (the fused x sweep's tail); the
+// cells next to troubled faces are left to xfix_queue_kernel, and only the
+// faces it reads get their rho, m, E fluxes stored.  Both kinds of sweep are
+// bound by memory: 256^3, per RK stage, y 460 -> 373 us, z 433 -> 357, x with its
+// cells 812 -> 636 (column order, overlapping tiles, faces nobody reads left out).
 template <int DIR, bool FUSED = false>
 __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restrict__ u,
                                                            float *__restrict__ flux, Geom G,
@@ -619,11 +626,10 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
                                                            unsigned long long *__restrict__ queue,
                                                            int32_t *__restrict__ qcount, long qcap,
                                                            unsigned char *__restrict__ mask, int reuse,
-                                                           XFuse<float> xf, sw::XSegArgs XA, sw::YZArgs YA)
+                                                           XFuse<float> xf, sw::XSegArgs XA, sw::YZArgs YA,
+                                                           uint32_t ntile)
 {
     static_assert(!FUSED || DIR == 0, "the fused tail belongs to the x sweep");
-    // tiles as the plain sweeps: x in flattened 256-face segments (rows of
-    // XSEG_MIN faces or more) or 4 rows x 64 faces; y/z 32 positions x 8 faces
     constexpr int NC = DIR == 0 ? sw::XSEG_CELLS : sw::yz_cells<YZ_PW, YZ_FT>();
     __shared__ float sq[sw::NQ * NC];
     __shared__ __align__(16) short xs[4 * 32 * XS];     // 32 feature rows per wave
@@ -634,20 +640,26 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
     constexpr int N = DIR;
     const int lane = threadIdx.x, w = threadIdx.y, tid = lane + 64 * w;
     int pos[3], off, cstr;
-    bool act;
-    int nface = 0;
+    bool act, own;                     // own: the tile stores and counts the face
+    uint32_t fo;                       // the face's offset in the flux box
+    XTile X;
+    uint32_t lb;                       // number of the tile
     sw::stage_begin();
     if constexpr (DIR == 0) {
         cstr = 1;
         if (FUSED || F.cnt[0] >= sw::XSEG_MIN) {
-            const XTile X = xtile(blockIdx.x * 256u, XA.total, XA.nf, XA.n1);
+            const uint32_t per = gridDim.x / sw::NXCD;
+            lb = (blockIdx.x % sw::NXCD) * per + blockIdx.x / sw::NXCD;
+            if (lb >= ntile) return;
+            X = xtile(lb * sw::XFUSE_STRIDE, XA.total, XA.nf, XA.n1);
             sw::xseg_stage<float, false, true>(u + sw::xseg_base(G, F, X), G.sv, sw::xseg_jump(G, F), P.gamma, X, tid,
                                                sq);
             __syncthreads();
             sw::stage_end();
-            nface = X.nface;
-            act = tid < nface;
-            const int t = act ? tid : nface - 1, s = X.row_of(t);
+            act = tid < X.nface;
+            const int t = act ? tid : X.nface - 1, s = X.row_of(t);
+            fo = X.g0 + t;
+            own = act && (tid < sw::XFUSE_STRIDE || fo == XA.total - 1);
             pos[0] = X.face_x(t, s);
             pos[1] = F.lo[1] + X.jj(s);
             pos[2] = F.lo[2] + X.kk(s);
@@ -656,6 +668,7 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
             const int cm[8] = { 0, 1, 2, 3, 4, 5, 6, 7 };
             const int ta = blockIdx.x, tb = blockIdx.y, nlast = G.n[0] + 2;
             const int nrows = F.cnt[1] * F.cnt[2];
+            lb = blockIdx.y * gridDim.x + blockIdx.x;
             for (int c = tid; c < sw::ROWS * sw::NCX; c += 256) {
                 int rr = c / sw::NCX, xi = c - rr * sw::NCX;
                 int row = ta * sw::ROWS + rr, x = tb * sw::TILE - 3 + xi;
@@ -672,12 +685,15 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
             pos[1] = F.lo[1] + row % F.cnt[1];
             pos[2] = F.lo[2] + row / F.cnt[1];
             off = w * sw::NCX + lane;
-            act = row < nrows && pos[0] < F.cnt[0];
+            act = own = row < nrows && pos[0] < F.cnt[0];
+            fo = (uint32_t)F.idx(pos[0], pos[1], pos[2]);
         }
     } else {
         cstr = YZ_PW;
         constexpr int A = 0, B = DIR == 1 ? 2 : 1;
-        const sw::YZTile<DIR == 0 ? 1 : DIR, YZ_PW, YZ_FT> t(YA, blockIdx.x, blockIdx.y, tid);
+        uint32_t ta, tb;
+        if (!sw::column_tile(YA, ta, tb, lb)) return;
+        const sw::YZTile<DIR == 0 ? 1 : DIR, YZ_PW, YZ_FT> t(YA, ta, tb, tid);
         sw::yz_stage<DIR == 0 ? 1 : DIR, YZ_PW, YZ_FT, float, true>(u, G, F, P.gamma, YA, t, sq);
         __syncthreads();
         sw::stage_end();
@@ -685,12 +701,13 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
         pos[B] = t.pos_b(F);
         pos[N] = t.f0 + t.fr;
         off = t.fr * YZ_PW + t.pl;
-        act = t.pl < t.np && pos[N] < F.cnt[N];
+        act = own = t.pl < t.np && pos[N] < F.cnt[N];
+        fo = (uint32_t)t.face_base(F) + t.face_rel(F, YA, t.fr);
     }
     // --- features and the MLP
     bool troubled = false;
     if (force == 0 && reuse) {
-        troubled = act && mask[F.idx(pos[0], pos[1], pos[2])] != 0;
+        troubled = act && mask[fo] != 0;
     } else if (force == 0) {
         bf4 xb[12];
         {
@@ -724,7 +741,7 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
         troubled = !(lg <= thr);                // NaN features count as troubled
-        if (act) mask[F.idx(pos[0], pos[1], pos[2])] = troubled ? 1 : 0;
+        if (own) mask[fo] = troubled ? 1 : 0;
     }
     // smooth interfaces: the linear flux (stored below)
     float lin[7];
@@ -741,57 +758,83 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
         }
     }
     // --- troubled interfaces: one queue reservation per block
-    const unsigned long long bt = __ballot(act && troubled), ba = __ballot(act);
+    const unsigned long long bt = __ballot(own && troubled), ba = __ballot(own);
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     if (lane == 0) { wcnt[w] = __popcll(bt); wact[w] = __popcll(ba); }
     __syncthreads();
     const int ntr = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
     if (tid == 0) {
         const int nact = wact[0] + wact[1] + wact[2] + wact[3];
-        if (nsmooth) nsmooth[(long)blockIdx.y * gridDim.x + blockIdx.x] = nact - ntr;
-        const long b = (long)blockIdx.y * gridDim.x + blockIdx.x;
-        const int reg = (int)(b % QREG);
+        if (nsmooth) nsmooth[lb] = nact - ntr;
+        const int reg = (int)(lb % QREG);
         qbase = ntr > 0 ? (long)reg * qcap + atomicAdd(qcount + reg, ntr) : 0;
     }
     __syncthreads();
-    if (act && troubled) {
+    if (own && troubled) {
         long o = qbase;
         for (int i = 0; i < w; ++i) o += wcnt[i];
         o += __popcll(bt & below);
         queue[o] = (unsigned long long)(pos[0] + 1) | ((unsigned long long)(pos[1] + 1) << 21) |
                    ((unsigned long long)(pos[2] + 1) << 42);
     }
-    if (act && !troubled) sw::store_face<N, float>(flux, F, pos, lin);
+    // hx and tfl were published by the barriers above
+    if (own && !troubled) {
+        bool hydro = true;             // rho, m, E of this face are read back
+        if constexpr (FUSED)
+            hydro = tid == 0 || tfl[tid - 1] != 0 || (tid + 1 < X.nface && tfl[tid + 1] != 0);
+        const int gc[7] = { 0, 1 + N, 1 + (N + 1) % 3, 1 + (N + 2) % 3, 4, 5, 6 };
+        sw::st32<float>(flux + gc[4] * F.sc, fo, lin[4]);
+        sw::st32<float>(flux + gc[5] * F.sc, fo, lin[5]);
+        if (hydro) {
+#pragma unroll
+            for (int c = 0; c < 7; ++c)
+                if (c != 4 && c != 5) sw::st32<float>(flux + gc[c] * F.sc, fo, lin[c]);
+        }
+    }
     if constexpr (FUSED) {
         // the cell between faces tid and tid + 1 (same row, interior), both
-        // smooth; hx and tfl were published by the barrier above
+        // smooth
         const int i = pos[0], j = pos[1], k = pos[2];
-        const bool cell = act && tid + 1 < nface && i + 1 < F.cnt[0] && j >= 0 && j < G.n[1] && k >= 0 &&
-                          k < G.n[2] && tfl[tid] == 0 && tfl[tid + 1] == 0;
+        const bool cell = act && tid < sw::XFUSE_STRIDE && tid + 1 < X.nface && i + 1 < F.cnt[0] && j >= 0 &&
+                          j < G.n[1] && k >= 0 && k < G.n[2] && tfl[tid] == 0 && tfl[tid + 1] == 0;
+        const sw::FusedTile<float> B = sw::fused_tile(xf, sw::xseg_base(G, F, X), X);
         if (cell) {
+            const int s = X.row_of(tid);
+            const uint32_t rel = X.state_rel(off + 3, sw::xseg_jump(G, F));
             sw::FusedCell<float> fc;
-            sw::fused_cell_load<float>(xf, G, i, j, k, fc);
-            sw::fused_cell_store<float>(xf, G, hx, 256, tid, fc);
+            sw::fused_tile_load(xf, B, G.sv, i + __umul24(s - (s >= X.sw ? 1 : 0), B.nx2), i + __umul24(s, B.nx2), rel,
+                                fc);
+            sw::fused_tile_store(xf, B, G, hx, 256, tid, rel, fc);
         }
     }
 }
 
 // The rho, m, E update of one cell left by the fused routed x sweep, its x
-// fluxes read back from the flux buffer (every x face stored by then).
+// fluxes read back from the flux buffer.
 __device__ __forceinline__ void xfix_cell(const float *__restrict__ flux, const Geom &G, const FaceBox &F,
                                           const XFuse<float> &xf, int i, int j, int k)
 {
+    // the faces and RK arrays from cell (0, 0, 0) on
+    sw::FusedTile<float> B;
+    B.nx2 = G.n[0] + 2;
+    B.fy = xf.fy + 1 + xf.by.s[2];
+    B.fz = xf.fz + 1 + B.nx2;
+    B.u0 = xf.u0 + G.base;
+    B.acc_in = xf.acc_in + G.base;
+    B.acc_out = xf.acc_out + G.base;
+    B.out = xf.out + G.base;
+    const uint32_t rj = i + j * (uint32_t)B.nx2, fl = (uint32_t)F.idx(i, j, k);
+    const uint32_t rel = i + j * (uint32_t)G.s[1] + k * (uint32_t)G.s[2];
     const int hs[5] = { 0, 1, 2, 3, 6 };
-    float xl[5], xr[5];
-    const long fl = F.idx(i, j, k), fr = F.idx(i + 1, j, k);
+    float x[10];
 #pragma unroll
     for (int h = 0; h < 5; ++h) {
-        xl[h] = flux[hs[h] * F.sc + fl];
-        xr[h] = flux[hs[h] * F.sc + fr];
+        x[2 * h] = sw::ld32(flux + hs[h] * F.sc, fl);
+        x[2 * h + 1] = sw::ld32(flux + hs[h] * F.sc + 1, fl);
     }
     sw::FusedCell<float> fc;
-    sw::fused_cell_load<float>(xf, G, i, j, k, fc);
-    sw::fused_cell_rk<float>(xf, G, xl, xr, fc);
+    sw::fused_tile_load(xf, B, G.sv, rj + k * (uint32_t)xf.by.s[2], rj + k * (uint32_t)xf.bz.s[2], rel, fc);
+    sw::fused_tile_store(xf, B, G, x, 2, 0, rel, fc);
 }
 
 // After the troubled pass: the cells next to the troubled x faces of queue
@@ -813,25 +856,6 @@ __global__ __launch_bounds__(128) void xfix_queue_kernel(const float *__restrict
         if (i < G.n[0]) xfix_cell(flux, G, F, xf, i, j, k);
         if (i > 0 && mask[F.idx(i - 1, j, k)] == 0) xfix_cell(flux, G, F, xf, i - 1, j, k);
     }
-}
-
-// The cells whose two x faces are smooth but lie in consecutive tiles (tile
-// t ends with face 256 t + 255), one thread per tile boundary.  Decisions
-// from mask (force -1: every face smooth).
-__global__ __launch_bounds__(256) void xfix_bound_kernel(const float *__restrict__ flux, Geom G, FaceBox F,
-                                                         XFuse<float> xf, const unsigned char *__restrict__ mask,
-                                                         int force, long ntile)
-{
-    const long t = (long)blockIdx.x * 256 + threadIdx.x;
-    if (t + 1 >= ntile) return;
-    const int nf = F.cnt[0];
-    const long g = 256 * t + 255, row = g / nf;
-    const int i = (int)(g - row * nf);
-    if (i + 1 >= nf) return;                                 // the row ends there: no cell
-    const int j = F.lo[1] + (int)(row % F.cnt[1]), k = F.lo[2] + (int)(row / F.cnt[1]);
-    if (j < 0 || j >= G.n[1] || k < 0 || k >= G.n[2]) return;
-    if (force == 0 && (mask[F.idx(i, j, k)] != 0 || mask[F.idx(i + 1, j, k)] != 0)) return;
-    xfix_cell(flux, G, F, xf, i, j, k);
 }
 
 // Full characteristic WENO at the queued troubled interfaces: each thread
@@ -856,14 +880,17 @@ __global__ __launch_bounds__(128) void troubled_kernel(const float *__restrict__
         if (e >= n) continue;
         const unsigned long long q = qr[e];
         int pos[3] = { (int)(q & 0x1fffff) - 1, (int)((q >> 21) & 0x1fffff) - 1, (int)(q >> 42) - 1 };
-        for (int j = 0; j < 6; ++j) {
-            int c[3] = { pos[0], pos[1], pos[2] };
-            c[N] = pos[N] - 3 + j;
-            const long id = G.base + c[0] * G.s[0] + c[1] * G.s[1] + (long)c[2] * G.s[2];
-            sw::stage_cell(u, id, G.sv, cm, P.gamma, sq + t * 6 + j, 128 * 6);
-        }
+        // all loads of the six cells before the arithmetic
+        const uint32_t id = (uint32_t)(G.base + pos[0] * G.s[0] + pos[1] * G.s[1] + pos[2] * G.s[2] - 3 * G.s[N]);
+        float q6[6][8];
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+#pragma unroll
+            for (int v = 0; v < 8; ++v) q6[j][v] = sw::ld32(u + cm[v] * G.sv, id + j * (uint32_t)G.s[N]);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) sw::stage_values<float>(q6[j], P.gamma, sq + j * 128 + t, 128 * 6);
         float out[7];
-        sw::face_flux<float>(sq, 128 * 6, t * 6, 1, P.gamma, P.igm1, (float)P.eps, out);
+        sw::face_flux<float>(sq, 128 * 6, t, 128, P.gamma, P.igm1, (float)P.eps, out);
         sw::store_face<N, float>(flux, F, pos, out);
     }
 }
@@ -930,7 +957,7 @@ static void routed_grid(int dir, const FaceBox &F, long &na, long &nb)
     if (dir == 0) {
         if (F.cnt[0] >= sw::XSEG_MIN) {
             const long total = (long)F.cnt[0] * F.cnt[1] * F.cnt[2];
-            na = (total + 255) / 256;
+            na = (total - 1 + sw::XFUSE_STRIDE - 1) / sw::XFUSE_STRIDE;
             nb = 1;
         } else {
             sw::xrows_tiles(F, na, nb);
@@ -967,37 +994,39 @@ hipError_t launch_routed_sweep(int dir, const float *u, float *flux, const Geom 
     long na, nb;
     routed_grid(dir, F, na, nb);
     const long cap = routed_queue_capacity(dir, F);
-    const dim3 grid((unsigned)na, (unsigned)nb), blk(64, 4), qgrid(32, rt::QREG), qblk(128);
+    // one axis, whole tiles per XCD, except for short x rows
+    const bool linear = dir != 0 || F.cnt[0] >= sw::XSEG_MIN;
+    const uint32_t ntile = (uint32_t)(na * nb), per = (ntile + sw::NXCD - 1) / sw::NXCD;
+    if (linear && na * nb + sw::NXCD >= 1L << 24) return hipErrorInvalidConfiguration;     // 2^32 threads
+    const dim3 grid = linear ? dim3(per * sw::NXCD) : dim3((unsigned)na, (unsigned)nb);
+    const dim3 blk(64, 4), qgrid(32, rt::QREG), qblk(128);
     const XFuse<float> nofuse{};
     const sw::XSegArgs XA = sw::xseg_args(F);
-    const sw::YZArgs YA = dir == 2 ? sw::yz_args<2, rt::YZ_PW, rt::YZ_FT>(F, 1)
-                                   : sw::yz_args<1, rt::YZ_PW, rt::YZ_FT>(F, 1);
+    const sw::YZArgs YA = dir == 2 ? sw::yz_args<2, rt::YZ_PW, rt::YZ_FT>(F, sw::NXCD)
+                                   : sw::yz_args<1, rt::YZ_PW, rt::YZ_FT>(F, sw::NXCD);
     switch (dir) {
     case 0:
         if (fused)
             hipLaunchKernelGGL((rt::routed_sweep_kernel<0, true>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
-                               force, nsmooth, queue, qcount, cap, mask, reuse, *xf, XA, YA);
+                               force, nsmooth, queue, qcount, cap, mask, reuse, *xf, XA, YA, ntile);
         else
             hipLaunchKernelGGL((rt::routed_sweep_kernel<0, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
-                               force, nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA);
+                               force, nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA, ntile);
         if (force == 0)
             hipLaunchKernelGGL(rt::troubled_kernel<0>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
         if (fused && force == 0)
             hipLaunchKernelGGL(rt::xfix_queue_kernel, qgrid, qblk, 0, st, flux, G, F, *xf, queue, qcount, cap,
                                mask);
-        if (fused && na > 1)
-            hipLaunchKernelGGL(rt::xfix_bound_kernel, dim3((unsigned)((na - 1 + 255) / 256)), dim3(256), 0, st,
-                               flux, G, F, *xf, mask, force, na);
         break;
     case 1:
         hipLaunchKernelGGL((rt::routed_sweep_kernel<1, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr, force,
-                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA);
+                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA, ntile);
         if (force == 0)
             hipLaunchKernelGGL(rt::troubled_kernel<1>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
         break;
     default:
         hipLaunchKernelGGL((rt::routed_sweep_kernel<2, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr, force,
-                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA);
+                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA, ntile);
         if (force == 0)
             hipLaunchKernelGGL(rt::troubled_kernel<2>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
         break;

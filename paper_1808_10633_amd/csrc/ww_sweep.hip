@@ -12,9 +12,6 @@ namespace {
 // by it.
 #define WW_TWO_WAVES __attribute__((amdgpu_waves_per_eu(2)))
 
-// Hardware block b runs on XCD b % 8 (blocks are dealt round-robin to the
-// eight XCDs, each with its own L2).
-constexpr int NXCD = 8;
 // 256-thread blocks of a launch: HIP takes fewer than 2^32 threads per axis.
 // Tile and face numbers therefore fit 32 bits.
 constexpr long MAX_BLOCKS = 1L << 24;
@@ -24,19 +21,6 @@ constexpr long MAX_BLOCKS = 1L << 24;
 // slower with them (the larger live set spilled at 256 VGPRs), and the FP32
 // y/z tiles lost a block per CU to the larger LDS footprint and ran 5 % slower.
 template <typename T> constexpr bool pre_x() { return sizeof(T) == 4; }
-
-// y/z sweeps: tiles (ta: positions of the transverse plane, tb: faces along
-// the sweep axis) are renumbered so that each XCD walks whole columns of
-// tiles, tb fastest.  A tile's 5 halo rows along the sweep axis were staged
-// by the tile before it on the same XCD and come from that XCD's L2.
-__device__ __forceinline__ bool column_tile(const sw::YZArgs &Y, uint32_t &ta, uint32_t &tb)
-{
-    const uint32_t lb = (blockIdx.x % NXCD) * Y.per_xcd + blockIdx.x / NXCD;
-    if (lb >= Y.ntile) return false;
-    ta = Y.nb.div(lb);
-    tb = lb - ta * Y.nb.d;
-    return true;
-}
 
 // x sweep of short rows: 2-D grid (ta, tb) of 4 rows x 64 faces.
 template <typename T, bool WZ, bool GLF>
@@ -67,7 +51,7 @@ __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_xfused_kernel(const T 
 {
     __shared__ T sq[sw::nq<pre_x<T>()>() * sw::XSEG_CELLS];
     __shared__ T hx[5 * sw::TILE * sw::ROWS];
-    const uint32_t tile = (blockIdx.x % NXCD) * per_xcd + blockIdx.x / NXCD;
+    const uint32_t tile = (blockIdx.x % sw::NXCD) * per_xcd + blockIdx.x / sw::NXCD;
     if (tile >= ntile) return;
     sw::sweep_tile_xseg_fused<T, WZ, GLF, pre_x<T>()>(u, flux, G, F, P, A, tile, sq, hx, xf);
 }
@@ -78,9 +62,9 @@ hipError_t launch_xfused(const T *u, T *flux, const Geom &G, const FaceBox &F, c
 {
     const long total = (long)F.cnt[0] * F.cnt[1] * F.cnt[2];
     const long nt = (total - 1 + sw::XFUSE_STRIDE - 1) / sw::XFUSE_STRIDE;
-    const long per = (nt + NXCD - 1) / NXCD;
-    if (per * NXCD >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((sweep_xfused_kernel<T, WZ, GLF>), dim3((unsigned)(per * NXCD)), dim3(sw::TILE, sw::ROWS), 0,
+    const long per = (nt + sw::NXCD - 1) / sw::NXCD;
+    if (per * sw::NXCD >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((sweep_xfused_kernel<T, WZ, GLF>), dim3((unsigned)(per * sw::NXCD)), dim3(sw::TILE, sw::ROWS), 0,
                        st, u, flux, G, F, P, xf, sw::xseg_args(F), (uint32_t)nt, (uint32_t)per);
     return hipGetLastError();
 }
@@ -99,7 +83,8 @@ __global__ __launch_bounds__(256) WW_TWO_WAVES void sweep_yz_kernel(const T *__r
     constexpr int PW = yz_pw<T>();
     __shared__ T sq[sw::NQ * sw::yz_cells<PW, YZ_FT>()];
     uint32_t ta, tb;
-    if (!column_tile(Y, ta, tb)) return;
+    uint32_t lb;
+    if (!sw::column_tile(Y, ta, tb, lb)) return;
     sw::sweep_tile_yz<DIR, PW, YZ_FT, T, WZ, GLF>(u, flux, G, F, P, Y, ta, tb, sq);
 }
 
@@ -108,9 +93,9 @@ hipError_t launch_yz(const T *u, T *flux, const Geom &G, const FaceBox &F, const
 {
     constexpr int PW = yz_pw<T>(), B = DIR == 1 ? 2 : 1;
     const long nt = ((long)F.cnt[0] * F.cnt[B] + PW - 1) / PW * ((F.cnt[DIR] + YZ_FT - 1) / YZ_FT);
-    if (nt + NXCD >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
-    const sw::YZArgs Y = sw::yz_args<DIR, PW, YZ_FT>(F, NXCD);
-    hipLaunchKernelGGL((sweep_yz_kernel<DIR, T, WZ, GLF>), dim3(Y.per_xcd * NXCD), dim3(sw::TILE, sw::ROWS), 0, st,
+    if (nt + sw::NXCD >= MAX_BLOCKS) return hipErrorInvalidConfiguration;
+    const sw::YZArgs Y = sw::yz_args<DIR, PW, YZ_FT>(F, sw::NXCD);
+    hipLaunchKernelGGL((sweep_yz_kernel<DIR, T, WZ, GLF>), dim3(Y.per_xcd * sw::NXCD), dim3(sw::TILE, sw::ROWS), 0, st,
                        u, flux, G, F, P, Y);
     return hipGetLastError();
 }

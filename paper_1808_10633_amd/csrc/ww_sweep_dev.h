@@ -692,88 +692,12 @@ __device__ __forceinline__ void sweep_tile_xrows(const T *__restrict__ u, T *__r
     __syncthreads();
 }
 
-// The rho, m, E update of one cell in the fused x sweeps, in two parts:
-// fused_cell_load issues the cell's global loads (its y and z faces' fluxes
-// and the RK arrays the stage form reads) before the tile's barrier, so that
-// they are in flight while the other waves finish their face fluxes;
-// fused_cell_rk forms L from the two x faces' fluxes and the loaded values
-// (the update kernel's expressions and order: x, y, z) and stores the RK
-// combination (rk_store_vars's expressions: identical results);
-// fused_cell_store takes the x fluxes from LDS.
+// Values of one cell of the fused x sweeps: its y and z faces' fluxes and the
+// RK arrays the stage form reads.
 template <typename T>
 struct FusedCell {
     T fyl[5], fyr[5], fzl[5], fzr[5], w0[5], w1[5];
-    long id;
 };
-
-template <typename T>
-__device__ __forceinline__ void fused_cell_load(const XFuse<T> &xf, const Geom &G, int i, int j, int k,
-                                                FusedCell<T> &c)
-{
-    const int hs[5] = { 0, 1, 2, 3, 6 }, hv[5] = { 0, 1, 2, 3, 7 };
-    c.id = G.base + i * G.s[0] + j * G.s[1] + (long)k * G.s[2];
-    const long yl = xf.by.idx(i, j, k), yr = xf.by.idx(i, j + 1, k);
-    const long zl = xf.bz.idx(i, j, k), zr = xf.bz.idx(i, j, k + 1);
-    const StageCoef &q = xf.c;
-    const bool u0 = (q.mode == 1 && q.s < 3) || q.mode == 2;
-    const bool ac = (q.mode == 1 && q.s > 0) || (q.mode == 2 && q.a1 != 0.0);
-#pragma unroll
-    for (int h = 0; h < 5; ++h) {
-        c.fyl[h] = xf.fy[hs[h] * xf.by.sc + yl];
-        c.fyr[h] = xf.fy[hs[h] * xf.by.sc + yr];
-        c.fzl[h] = xf.fz[hs[h] * xf.bz.sc + zl];
-        c.fzr[h] = xf.fz[hs[h] * xf.bz.sc + zr];
-        c.w0[h] = u0 ? xf.u0[c.id + hv[h] * G.sv] : T(0);
-        c.w1[h] = ac ? xf.acc_in[c.id + hv[h] * G.sv] : T(0);
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void fused_cell_rk(const XFuse<T> &xf, const Geom &G, const T (&xl)[5], const T (&xr)[5],
-                                              const FusedCell<T> &c)
-{
-    const int hv[5] = { 0, 1, 2, 3, 7 };
-    const T idx = T(G.idl[0]), idy = T(G.idl[1]), idz = T(G.idl[2]);
-    const StageCoef &q = xf.c;
-    const T bdt = T(q.bdt), cdt = T(q.cdt), a0 = T(q.a0), a1 = T(q.a1);
-    const long sv = G.sv, id = c.id;
-#pragma unroll
-    for (int h = 0; h < 5; ++h) {
-        T L = T(0);
-        L -= (xr[h] - xl[h]) * idx;
-        L -= (c.fyr[h] - c.fyl[h]) * idy;
-        L -= (c.fzr[h] - c.fzl[h]) * idz;
-        const long o = id + hv[h] * sv;
-        if (q.mode == 0) {
-            xf.out[o] = L;
-        } else if (q.mode == 2) {
-            xf.out[o] = q.a1 != 0.0 ? a0 * c.w0[h] + a1 * c.w1[h] + cdt * L : a0 * c.w0[h] + cdt * L;
-        } else if (q.s == 0) {
-            xf.acc_out[o] = c.w0[h] + bdt * L;
-            xf.out[o] = c.w0[h] + cdt * L;
-        } else if (q.s < 3) {
-            xf.acc_out[o] = c.w1[h] + bdt * L;
-            xf.out[o] = c.w0[h] + cdt * L;
-        } else {
-            xf.out[o] = c.w1[h] + cdt * L;
-        }
-    }
-}
-
-// The cell between tile faces tid and tid + 1, whose rho, m, E fluxes are in
-// LDS (hx, nh apart per component).
-template <typename T>
-__device__ __forceinline__ void fused_cell_store(const XFuse<T> &xf, const Geom &G, const T *hx, int nh, int tid,
-                                                 const FusedCell<T> &c)
-{
-    T xl[5], xr[5];
-#pragma unroll
-    for (int h = 0; h < 5; ++h) {
-        xl[h] = hx[h * nh + tid];
-        xr[h] = hx[h * nh + tid + 1];
-    }
-    fused_cell_rk<T>(xf, G, xl, xr, c);
-}
 
 // x sweep over the flattened (row, face) space, for rows of at least
 // XSEG_MIN faces: tile t takes the TILE*ROWS consecutive faces t*256 ..
@@ -859,9 +783,8 @@ __device__ __forceinline__ void sweep_tile_xseg(const T *__restrict__ u, T *__re
 
 // The cell between tile faces t and t + 1 of row s (face x index f): its y
 // and z faces' fluxes (offsets ry, rz) and RK arrays (offset rel), read at
-// 32-bit offsets from the tile's scalar bases (fused_cell_load's values,
-// without its 64-bit products: those and the row divisions were a fifth of
-// the fused sweep's VALU time).  A row of the x faces advances both face
+// 32-bit offsets from the tile's scalar bases (64-bit products and the row
+// divisions were a fifth of the fused sweep's VALU time).  A row of the x faces advances both face
 // boxes by a row of n0 + 2 faces; passing to the next plane, the y faces' rows
 // (one fewer per plane) lag by one.
 template <typename T>
@@ -905,8 +828,8 @@ __device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedT
     }
 }
 
-// The RK combination of that cell from its x fluxes and the loaded values
-// (fused_cell_rk's expressions: identical results).
+// The RK combination of that cell from its x fluxes and the loaded values (the
+// update kernel's expressions and order, x, y, z: identical results).
 template <typename T>
 __device__ __forceinline__ void fused_tile_store(const XFuse<T> &xf, const FusedTile<T> &B, const Geom &G,
                                                  const T *hx, int nh, int t, uint32_t rel, const FusedCell<T> &c)
@@ -1011,6 +934,23 @@ struct YZArgs {
     FastDiv na, nb;            // positions along x, tiles along the sweep axis
     uint32_t npos, ntile, per_xcd;
 };
+
+// Hardware block b runs on XCD b % 8 (blocks are dealt round-robin to the
+// eight XCDs, each with its own L2).
+constexpr int NXCD = 8;
+
+// y/z sweeps: tiles (ta: positions of the transverse plane, tb: faces along
+// the sweep axis) are renumbered so that each XCD walks whole columns of
+// tiles, tb fastest.  A tile's 5 halo rows along the sweep axis were staged
+// by the tile before it on the same XCD and come from that XCD's L2.
+__device__ __forceinline__ bool column_tile(const YZArgs &Y, uint32_t &ta, uint32_t &tb, uint32_t &lb)
+{
+    lb = (blockIdx.x % NXCD) * Y.per_xcd + blockIdx.x / NXCD;
+    if (lb >= Y.ntile) return false;
+    ta = Y.nb.div(lb);
+    tb = lb - ta * Y.nb.d;
+    return true;
+}
 
 // Tile (ta, tb) of a y/z sweep, one thread's place in it.  Element offsets
 // within a tile are 32-bit: they stay within one variable (or face
