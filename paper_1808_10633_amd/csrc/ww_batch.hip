@@ -449,7 +449,7 @@ __device__ __forceinline__ void update_b_patch(const T *fx, const T *fy, const T
             r = T(0); r -= (Ey1 - Ey0) * idx; r += (Ex1 - Ex0) * idy; bzl = r;
             r = T(0); r -= (Ey3 - Ey2) * idx; r += (Ex3 - Ex2) * idy; bzr = r;
             const T Lb[3] = { T(0.5) * (bxl + bxr), T(0.5) * (byl + byr), T(0.5) * (bzl + bzr) };
-            // rk_store_vars's expressions on the preloaded u0 / acc_in values
+            // rk_store_b's expressions on the preloaded u0 / acc_in values
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
                 T *const acc = B.acc_out + (4 + m) * B.sv, *const out = B.out + (4 + m) * B.sv;
@@ -617,7 +617,7 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
                 pos[0] = c % Q.G.n[0];
                 pos[1] = (c / Q.G.n[0]) % Q.G.n[1];
                 pos[2] = c / (Q.G.n[0] * Q.G.n[1]);
-                up::update_cell(ua, pos);
+                up::update_cell<7>(ua, pos);
             }
         }
         if (!whole) {
