@@ -320,11 +320,13 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
         ncu = 256;
     b->ncu = ncu;
     b->maxblocks = 4 * ncu;
-    // For the resident blocks of the usual shapes (FP32 three blocks per CU,
-    // FP64 two), with no more face scratch than the largest patch's per block.
-    // Split x sweeps take the flattened tiles.
+    // For four blocks per CU (FP32) or two (FP64): FP32 runs two or three, but
+    // the finer plan was 3-6 % faster on uneven patches (for two blocks per CU
+    // 7-12 % slower), FP64 one, and a plan for four 6 % slower on 512 patches of
+    // 16-32.  No more face scratch than the largest patch's per block.  Split x
+    // sweeps take the flattened tiles.
     b->plan = ww::batch_plan(
-        npatch, dims, (cfg->precision == WW_FP64 ? 2 : 3) * ncu, b->maxblocks, slot * b->maxblocks,
+        npatch, dims, (cfg->precision == WW_FP64 ? 2 : 4) * ncu, b->maxblocks, slot * b->maxblocks,
         [&](int p) { return felems[p]; }, [&](int p) { return b->hpd[p].xflat != 0; });
     auto fail_oom = [&](const char *what) {
         release(b);

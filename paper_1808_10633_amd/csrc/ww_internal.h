@@ -129,7 +129,7 @@ inline bool has_user_face(const Geom &G, const int bc[6])
 // same launch.  No user faces, JS weights, per-stencil LF speeds.
 // A box is small up to SMALL_TILES tiles of 256 faces, 3-D boxes without the
 // fused x sweep (rows under 86 faces) up to twice as many.  Steps with one
-// launch and with three: FP64 64^3 (3.3 k tiles) 356 us, 495; FP32 254, 510;
+// launch and with three (both with an update that was slower than now): FP64 64^3 (3.3 k tiles) 356 us, 495; FP32 254, 510;
 // FP64 80^3 (6.4 k) 763, 822; FP32 484, 640; 900^2 (6.4 k) 680, 635; 96^3
 // (11 k; fused x sweep) 1390, 950.
 constexpr long SMALL_TILES = 4096;
