@@ -142,24 +142,37 @@ __device__ __forceinline__ void store_dt(double mx, int bad, double cfl, double 
 // counting block waits until its stores are in the L2, then one wave writes
 // the L2 back and counts; in the waiting block one wave drops the CU's and the
 // L2's stale lines before the others go on (a fence per wave costs four of
-// each).
+// each).  The waits are written out: with none of a wave's own stores
+// outstanding the compiler leaves out the one between a release fence's
+// write-back and the atomic that it guards.
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void release_all()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    wait_memory();
+}
+__device__ __forceinline__ void acquire_all()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    wait_memory();
+}
 __device__ __forceinline__ void wait_count(const int32_t *count, int target)
 {
     if (threadIdx.x == 0 && threadIdx.y == 0) {
         while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target)
             __builtin_amdgcn_s_sleep(16);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        acquire_all();
     }
     __syncthreads();
 }
 // Returns the count after this item (in thread 0).
 __device__ __forceinline__ int count_done(int32_t *count)
 {
-    __builtin_amdgcn_s_waitcnt(0);
+    wait_memory();
     __syncthreads();
     int n = 0;
     if (threadIdx.x == 0 && threadIdx.y == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        release_all();
         n = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
     }
     return n;
@@ -639,11 +652,12 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
                     __hip_atomic_fetch_add(&dt->bad, bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 if (count_done(done) == S.n[0]) {                 // thread 0 of the last item
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    acquire_all();
                     const unsigned long long m = __hip_atomic_load(&dt->mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     const int nbad = __hip_atomic_load(&dt->bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     store_dt(__longlong_as_double((long long)m), nbad, a.cfl, &a.dt[p], &a.flag[p]);
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    wait_memory();
+                    release_all();
                     __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             } else {

@@ -325,9 +325,14 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
     // 7-12 % slower), FP64 one, and a plan for four 6 % slower on 512 patches of
     // 16-32.  No more face scratch than the largest patch's per block.  Split x
     // sweeps take the flattened tiles.
-    b->plan = ww::batch_plan(
-        npatch, dims, (cfg->precision == WW_FP64 ? 2 : 4) * ncu, b->maxblocks, slot * b->maxblocks,
-        [&](int p) { return felems[p]; }, [&](int p) { return b->hpd[p].xflat != 0; });
+    try {
+        b->plan = ww::batch_plan(
+            npatch, dims, (cfg->precision == WW_FP64 ? 2 : 4) * ncu, b->maxblocks, slot * b->maxblocks,
+            [&](int p) { return felems[p]; }, [&](int p) { return b->hpd[p].xflat != 0; });
+    } catch (const std::bad_alloc &) {
+        delete b;
+        return bfail(nullptr, WW_ERR_OOM, "host allocation failed");
+    }
     auto fail_oom = [&](const char *what) {
         release(b);
         delete b;
