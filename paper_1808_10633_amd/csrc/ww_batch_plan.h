@@ -193,24 +193,35 @@ BatchPlan batch_plan_try(int npatch, const int *dims, int workers, int whole_slo
 // The plan of the smallest span among whole patches only and four grains of
 // splitting.  FP32, whole only / the chosen one, ms a stage: 1024 patches of
 // 16-64 cells per axis 17.8 / 10.8, 64 of 32-64 17.4 / 1.9, 256 of 16-64
-// 13.4 / 3.0; one 64^3 patch 16 / 0.17.  Whole patches only where they end
-// within 5 % of an even share on half as many blocks (tuned shapes run half to
-// all of `workers`): there is nothing to gain, and splitting the largest of 4096
-// patches all the same cost 1 %.
+// 13.4 / 3.0; one 64^3 patch 16 / 0.17.  Where whole patches end within 5 % of
+// an even share on half as many blocks (tuned shapes run half to all of
+// `workers`) there is nothing to gain: splitting the largest of 4096 patches
+// all the same cost 1 %.  And a plan has to promise a tenth over whole patches
+// on three quarters or all of the blocks: 1100 equal patches on 1024 blocks,
+// promised a gain over 1024 but not over 768, were 5 % slower.
 template <typename Elems, typename CanSplit>
 BatchPlan batch_plan(int npatch, const int *dims, int workers, int whole_slots, long cap, Elems elems,
                      CanSplit can_split)
 {
-    BatchPlan best = batch_plan_try(npatch, dims, std::max(1, workers / 2), whole_slots, cap, elems, can_split, 1e300,
-                                    1.0);
-    if (best.span <= 1.05 * best.share) return best;
-    best = batch_plan_try(npatch, dims, workers, whole_slots, cap, elems, can_split, 1e300, 1.0);
+    auto plan = [&](int w, double above, double unit) {
+        return batch_plan_try(npatch, dims, std::max(1, w), whole_slots, cap, elems, can_split, above, unit);
+    };
+    const BatchPlan whole = plan(workers / 2, 1e300, 1.0);
+    if (whole.span <= 1.05 * whole.share) return whole;
+    const bool many = npatch > 1 << 17;         // a simulation takes 0.2 us a patch
+    double ratio = 1e300;
+    for (int q = many ? 4 : 3; q <= 4; ++q) {
+        const BatchPlan P = plan(workers * q / 4, 1e300, 1.0);
+        ratio = std::min(ratio, P.span / P.share);
+    }
+    BatchPlan best;
+    best.span = 1e300;
     const double grain[4][2] = { { 0.5, 0.25 }, { 1.0, 0.5 }, { 0.5, 0.125 }, { 0.5, 1.0 / 16.0 } };
-    for (int g = 0; g < (npatch > 1 << 17 ? 1 : 4); ++g) {      // (a simulation takes 0.2 us a patch)
-        BatchPlan P = batch_plan_try(npatch, dims, workers, whole_slots, cap, elems, can_split, grain[g][0], grain[g][1]);
+    for (int g = 0; g < (many ? 1 : 4); ++g) {
+        BatchPlan P = plan(workers, grain[g][0], grain[g][1]);
         if (P.span < best.span) best = std::move(P);
     }
-    return best;
+    return best.span / best.share < 0.9 * ratio ? best : whole;
 }
 
 }  // namespace ww

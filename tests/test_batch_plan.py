@@ -14,17 +14,19 @@ PROGRAM = r"""
 using namespace ww;
 #define CHECK(c) do { if (!(c)) { printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
 
-static int check(const std::vector<int> &dims, int workers, int slots, double capf, int never, int expect)
+static int check_one(const std::vector<int> &dims, int workers, int slots, double capf, int never, int expect, int grain)
 {
     const int np = (int)dims.size() / 3;
     auto elems = [&](int p) { return 7 * (long)batch_cost(&dims[3 * p]); };
     long biggest = 0;
     for (int p = 0; p < np; ++p) biggest = std::max(biggest, elems(p));
     const long cap = (long)(capf * biggest * slots);
-    const BatchPlan P = batch_plan(np, dims.data(), workers, slots, cap, elems,
-                                   [&](int p) { return !never || p % never != 0; });
+    auto can = [&](int p) { return !never || p % never != 0; };
+    const BatchPlan P = grain < 0 ? batch_plan(np, dims.data(), workers, slots, cap, elems, can)
+                                  : batch_plan_try(np, dims.data(), workers, slots, cap, elems, can, grain > 1 ? 1.0 : 0.5,
+                                                   1.0 / (2 << grain));
     const int ns = (int)P.split_patch.size();
-    if (expect >= 0) CHECK((ns > 0) == (expect > 0));
+    if (expect >= 0 && grain < 0) CHECK((ns > 0) == (expect > 0));
     CHECK((int)P.split.size() == ns && P.nwhole == np - ns);
     CHECK(ns == 0 || P.nslot * P.split_elems + std::min(P.nwhole, slots) * P.whole_elems <= cap);
     CHECK(ns == 0 || (P.nslot >= 1 && P.nslot <= ns));
@@ -64,6 +66,14 @@ static int check(const std::vector<int> &dims, int workers, int slots, double ca
     }
     for (int p = 0; p < np; ++p) CHECK(whole[p] == 1);
     CHECK(nw == P.nwhole);
+    return 0;
+}
+
+// The chosen plan, and every grain (buffers are handed on where the scratch is short).
+static int check(const std::vector<int> &dims, int workers, int slots, double capf, int never, int expect)
+{
+    for (int grain = -1; grain < 4; ++grain)
+        if (check_one(dims, workers, slots, capf, never, expect, grain)) { printf("grain %d\n", grain); return 1; }
     return 0;
 }
 

@@ -25,8 +25,8 @@ CASES = {
     "rows": ([(258, 12, 9), (4, 50, 61), (261, 5, 9)], [0, 1, 2]),
     # large ones among small whole patches
     "mixed": ([(4, 5, 6), (64, 48, 40), (5, 5, 5)] * 2 + [(4, 4, 4)] * 40, [0, 1, 2, 4, 45]),
-    # more split patches than face buffers: buffers are handed on
-    "handed_on": ([(16, 16, 16)] * 1100, [0, 1, 500, 1023, 1024, 1060, 1099]),
+    # more equal patches than blocks
+    "equal": ([(16, 16, 16)] * 1100, [0, 1, 500, 1023, 1024, 1060, 1099]),
 }
 
 
