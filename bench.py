@@ -29,36 +29,37 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3     # MI355X FP32 vector peak (packed)
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE and WRITE_SIZE runs (scaled
 # by a 1 GiB copy; see profiles/), valid only for the kernel source they were
-# taken on: sha256 of ww_sweep.hip + ww_sweep_dev.h (sweeps) or ww_update.hip
+# taken on: sha256 of ww_sweep.hip + ww_sweep_dev.h + ww_index.h (sweeps) or ww_update.hip
 # + ww_update_dev.h (update).
 MEASURED_TRAFFIC = {
     # y sweep (the VALU roofline's kernel) and the fused x sweep
-    ("b97c660155bc5f2d", "fp64", 512): {"read": 9.406e9, "write": 9.05e9,
+    ("c5d79eb5d3d34c79", "fp64", 512): {"read": 9.403e9, "write": 9.044e9,
                                       "profile": "profiles/fp64_512_turbulence_trace_and_hbm.md"},
-    ("b97c660155bc5f2d", "fp32", 512): {"read": 4.788e9, "write": 4.711e9,
+    ("c5d79eb5d3d34c79", "fp32", 512): {"read": 4.781e9, "write": 4.72e9,
                                       "profile": "profiles/fp32_512_turbulence_trace_and_hbm.md"},
-    ("b97c660155bc5f2d", "fp64_xfused", 512): {"read": 31.23e9, "write": 11.64e9,
+    ("c5d79eb5d3d34c79", "fp64_xfused", 512): {"read": 31.35e9, "write": 11.64e9,
                                              "profile": "profiles/fp64_512_turbulence_trace_and_hbm.md"},
-    ("b97c660155bc5f2d", "fp32_xfused", 512): {"read": 15.24e9, "write": 5.837e9,
+    ("c5d79eb5d3d34c79", "fp32_xfused", 512): {"read": 15.33e9, "write": 5.837e9,
                                              "profile": "profiles/fp32_512_turbulence_trace_and_hbm.md"},
 }
 MEASURED_UPDATE_TRAFFIC = {
     # B-only update, mean over the profiled launches (RK stage forms and L(U))
-    ("cf6b38782c5af04b", "fp64", 512): {"read": 11.8e9, "write": 5.585e9,
+    ("e86924a598e0365e", "fp64", 512): {"read": 11.9e9, "write": 5.582e9,
                                       "profile": "profiles/fp64_512_turbulence_trace_and_hbm.md"},
-    ("cf6b38782c5af04b", "fp32", 512): {"read": 5.73e9, "write": 2.818e9,
+    ("e86924a598e0365e", "fp32", 512): {"read": 5.745e9, "write": 2.818e9,
                                       "profile": "profiles/fp32_512_turbulence_trace_and_hbm.md"},
 }
 
 # HBM bytes per stage launch of the batched kernel on the 4096-patch set
 # (autotuned faces per y/z tile -> read, write), from the same counter runs,
 # valid only for the batched source they were taken on (sha256 of
-# ww_batch.hip, ww_batch.h, ww_sweep_dev.h, ww_update_dev.h, ww_internal.h).
+# ww_batch.hip, ww_batch.h, ww_batch_plan.h, ww_sweep_dev.h, ww_update_dev.h,
+# ww_index.h, ww_internal.h).
 MEASURED_BATCH_TRAFFIC = {
-    ("357f8b2041d60ec0", 4096, 4): (85.48e9, 32.26e9),
-    ("357f8b2041d60ec0", 4096, 8): (79.57e9, 32.72e9),
-    ("357f8b2041d60ec0", 4096, 12): (81.07e9, 31.47e9),
-    ("357f8b2041d60ec0", 4096, 16): (79.07e9, 32.45e9),
+    ("f33559fb491041f7", 4096, 4): (86.56e9, 32.22e9),
+    ("f33559fb491041f7", 4096, 8): (103.59e9, 30.64e9),
+    ("f33559fb491041f7", 4096, 12): (86.53e9, 32.08e9),
+    ("f33559fb491041f7", 4096, 16): (85.75e9, 32.04e9),
 }
 BATCH_TRAFFIC_PROFILE = "profiles/batched_4096_patches_hbm.md"
 
@@ -67,7 +68,8 @@ def batch_source_hash():
     import hashlib
     d = os.path.join(ROOT, "paper_1808_10633_amd", "csrc")
     src = b"".join(open(os.path.join(d, f), "rb").read()
-                   for f in ("ww_batch.hip", "ww_batch.h", "ww_sweep_dev.h", "ww_update_dev.h", "ww_internal.h"))
+                   for f in ("ww_batch.hip", "ww_batch.h", "ww_batch_plan.h", "ww_sweep_dev.h", "ww_update_dev.h",
+                             "ww_index.h", "ww_internal.h"))
     return hashlib.sha256(src).hexdigest()[:16]
 
 
@@ -79,7 +81,7 @@ def _source_hash(files):
 
 
 def sweep_source_hash():
-    return _source_hash(("ww_sweep.hip", "ww_sweep_dev.h"))
+    return _source_hash(("ww_sweep.hip", "ww_sweep_dev.h", "ww_index.h"))
 
 
 def update_source_hash():
@@ -168,7 +170,7 @@ def roofline_sweep(ms_y, n, prec, opcount, peak):
             "traffic_source": tr["profile"] if tr else None,
             "hbm_TBps": round(traffic / (ms_y * 1e-3) / 1e12, 3) if tr else None,
             "hbm_frac": round(traffic / (ms_y * 1e-3) / HBM_PEAK, 4) if tr else None,
-            "kernel": ("sweep_yz_kernel<1,32,double>" if prec == "fp64" else "sweep_kernel<1,8,float>") + " (y sweep)",
+            "kernel": f"sweep_yz_kernel<1, {'double' if prec == 'fp64' else 'float'}> (y sweep)",
             "ms": ms_y, "flop_per_interface": fpi, "interfaces_per_launch": nface,
             "frac_dense_count": round(dense / peak, 4),
             "dense_flop_per_interface": opcount.DENSE_FLOPS_PER_INTERFACE}
@@ -188,8 +190,8 @@ def roofline_update(ms_u, n, prec, opcount, fused_x=True):
     return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK / 1e9, "unit": "GB/s",
             "frac": round(achieved * 1e9 / HBM_PEAK, 4), "traffic": traffic, "traffic_unit": "bytes/launch",
             "traffic_source": tr["profile"] if tr else None,
-            "kernel": f"update_march_kernel<{'double' if es == 8 else 'float'}, {'true' if fused_x else 'false'}, "
-                      f"false> (RK stage forms{', B only' if fused_x else ''})",
+            "kernel": (f"update_march_kernel<{'double' if es == 8 else 'float'}, false> (RK stage forms, B only)"
+                       if fused_x else f"update_kernel<7, {'double' if es == 8 else 'float'}> (RK stage forms)"),
             "ms": ms_u, "algorithmic_bytes_per_cell": bpc, "cells_per_launch": n ** 3}
 
 

@@ -264,7 +264,8 @@ int wombat_weno_divb(wombat_weno_t *ctx, void *d_u, double *max_abs, double *l1)
  * passes), ms[6] the update writing L(U) only (the form of wombat_weno_rhs).
  * A step costs about ms[5] + stages * (ms[0] + ms[1] + ms[2] + ms[3] + ms[4]).
  * With slab_planes, ms[1..4] and ms[6] are the launches of all slabs of a
- * stage.
+ * stage.  The calls of small boxes run the ghost fill and the sweeps in one
+ * launch, cheaper than the separate kernels timed here.
  * d_u's ghosts are filled; the work arrays are overwritten.  Synchronous. */
 int wombat_weno_time_kernels(wombat_weno_t *ctx, void *d_u, int reps, double ms[7]);
 
@@ -310,10 +311,11 @@ typedef struct wombat_weno_batch wombat_weno_batch_t;
 /* Create a batch of npatch patches; dims (host) holds npatch x (nx, ny, nz),
  * each edge 4..1024 cells (the 3-deep periodic ghosts need at least 3).  From cfg only dx (the cell width of every
  * patch and axis), gamma, cfl, eps, precision, stream and device are used.
- * Allocates three work arenas, the face-flux scratch of up to 4 blocks per
- * CU, the patch table and the patch order (largest first; in each stage the
- * resident blocks take the next patch of that order from a shared counter
- * until none is left).  *out is written only on success.
+ * Allocates three work arenas, the face-flux scratch (at most that of the
+ * largest patch for 4 blocks per CU), the patch table and the list of work
+ * items (patches, largest first, or shares of a patch too large for one block;
+ * in each stage the resident blocks take the next item of that list from a
+ * shared counter until none is left).  *out is written only on success.
  * Errors: WW_ERR_INVALID_ARG, WW_ERR_OOM, WW_ERR_HIP, WW_ERR_UNSUPPORTED. */
 int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int32_t *dims,
                            wombat_weno_batch_t **out);

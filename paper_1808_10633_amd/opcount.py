@@ -13,25 +13,27 @@ STEPS = {
     # six stencil cells: velocities (3), total pressure (7), physical flux (24),
     # |lambda^s| for seven fields (6) and their running maxima (7)
     "cell fluxes and LF speeds (6 cells x 47)": 6 * 47,
-    # central combination (-F1 + 7F2 + 7F3 - F4)/12 of 7 components (42) and
-    # the 5 differences of F and U (70)
-    "central term and differences": 42 + 70,
+    # mean flux of 7 components, added at the end (21), and the 5 differences
+    # of F and U (70)
+    "mean flux and differences": 21 + 70,
     # mean state (22), sound/Alfven/fast/slow speeds and Roe-Balsara
     # normalisation (53), row/column coefficients (30)
     "interface state and eigen-system": 105,
     "divisions and square roots of the eigen-system": 5 + 8,
-    # dW/dU applied to 11 vectors (central term, 5 flux and 5 state
-    # differences): 4 x 3 + 14 flops, plus the rotation onto (beta, perp): 12
-    "primitive transform of 11 vectors (11 x 35)": 11 * 35,
+    # dW/dU applied to 10 vectors (5 flux and 5 state differences):
+    # 4 x 3 + 14 flops, plus the rotation onto (beta, perp): 12 (the mean flux
+    # is not projected: R L = I)
+    "primitive transform of 10 vectors (10 x 35)": 10 * 35,
     # projections onto the 7 left eigenvectors: fast and slow pairs
-    # (6 per vector + 22 sign combinations), Alfven (2 per vector + 22),
+    # (6 per vector + 20 sign combinations), Alfven (2 per vector + 20),
     # entropy (2 per vector)
-    "characteristic projections": 88 + 88 + 44 + 22,
+    "characteristic projections": 80 + 80 + 40 + 20,
     # per field: LF split of 5 differences on both sides as fused
-    # multiply-adds (20), two phi_N (smoothness indicators as expanded
-    # quadratic forms 22, squares 3, weights over one denominator 9,
-    # interpolant 12 = 46 each), eq. (1) combination (2)
-    "WENO5 weights and fluxes (7 fields x 114)": 7 * 114,
+    # multiply-adds (20), the nonlinear part of two phi_N (smoothness
+    # indicators as expanded quadratic forms 22, squares 3, weights over one
+    # denominator 7, interpolant 9 = 41 each), the linear part and the
+    # eq. (1) combination (8)
+    "WENO5 weights and fluxes (7 fields x 110)": 7 * 110,
     "WENO5 divisions (7 fields x 2)": 14,
     # back-projection: pair sums/differences and primitive columns (31),
     # rotation back (12), dU/dW (23)
