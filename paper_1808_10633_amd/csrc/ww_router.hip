@@ -616,7 +616,8 @@ __global__ __launch_bounds__(64) void router_sample_kernel(const T *__restrict__
 // faces it reads get their rho, m, E fluxes stored.  Both kinds of sweep are
 // bound by memory: 256^3, per RK stage, y 460 -> 373 us, z 433 -> 357, x with its
 // cells 812 -> 636 (column order, overlapping tiles, faces nobody reads left out).
-template <int DIR, bool FUSED = false>
+// FAR: see far_box (fused x tiles store at offsets within the tile in both).
+template <int DIR, bool FUSED, bool FAR>
 __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restrict__ u,
                                                            float *__restrict__ flux, Geom G,
                                                            FaceBox F, Phys P,
@@ -641,7 +642,10 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
     const int lane = threadIdx.x, w = threadIdx.y, tid = lane + 64 * w;
     int pos[3], off, cstr;
     bool act, own;                     // own: the tile stores and counts the face
-    uint32_t fo;                       // the face's offset in the flux box
+    // the face in the flux box: the tile's place (scalar) and the offset from
+    // there (long x rows under 256; elsewhere up to a whole component)
+    long fbase;
+    uint32_t fo;
     XTile X;
     uint32_t lb;                       // number of the tile
     sw::stage_begin();
@@ -658,8 +662,9 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
             sw::stage_end();
             act = tid < X.nface;
             const int t = act ? tid : X.nface - 1, s = X.row_of(t);
-            fo = X.g0 + t;
-            own = act && (tid < sw::XFUSE_STRIDE || fo == XA.total - 1);
+            fbase = X.g0;
+            fo = t;
+            own = act && (tid < sw::XFUSE_STRIDE || X.g0 + t == XA.total - 1);
             pos[0] = X.face_x(t, s);
             pos[1] = F.lo[1] + X.jj(s);
             pos[2] = F.lo[2] + X.kk(s);
@@ -686,6 +691,7 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
             pos[2] = F.lo[2] + row / F.cnt[1];
             off = w * sw::NCX + lane;
             act = own = row < nrows && pos[0] < F.cnt[0];
+            fbase = 0;
             fo = (uint32_t)F.idx(pos[0], pos[1], pos[2]);
         }
     } else {
@@ -702,12 +708,13 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
         pos[N] = t.f0 + t.fr;
         off = t.fr * YZ_PW + t.pl;
         act = own = t.pl < t.np && pos[N] < F.cnt[N];
-        fo = (uint32_t)t.face_base(F) + t.face_rel(F, YA, t.fr);
+        fbase = t.face_base(F);
+        fo = t.face_rel(F, YA, t.fr);
     }
     // --- features and the MLP
     bool troubled = false;
     if (force == 0 && reuse) {
-        troubled = act && mask[fo] != 0;
+        troubled = act && sw::uniform(mask + fbase)[fo] != 0;
     } else if (force == 0) {
         bf4 xb[12];
         {
@@ -741,7 +748,7 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
         troubled = !(lg <= thr);                // NaN features count as troubled
-        if (own) mask[fo] = troubled ? 1 : 0;
+        if (own) sw::uniform(mask + fbase)[fo] = troubled ? 1 : 0;
     }
     // smooth interfaces: the linear flux (stored below)
     float lin[7];
@@ -783,12 +790,13 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
         if constexpr (FUSED)
             hydro = tid == 0 || tfl[tid - 1] != 0 || (tid + 1 < X.nface && tfl[tid + 1] != 0);
         const int gc[7] = { 0, 1 + N, 1 + (N + 1) % 3, 1 + (N + 2) % 3, 4, 5, 6 };
-        sw::st32<float>(flux + gc[4] * F.sc, fo, lin[4]);
-        sw::st32<float>(flux + gc[5] * F.sc, fo, lin[5]);
+        float *const fb = flux + fbase;
+        sw::st_off<FAR && !FUSED>(fb + gc[4] * F.sc, fo, lin[4]);
+        sw::st_off<FAR && !FUSED>(fb + gc[5] * F.sc, fo, lin[5]);
         if (hydro) {
 #pragma unroll
             for (int c = 0; c < 7; ++c)
-                if (c != 4 && c != 5) sw::st32<float>(flux + gc[c] * F.sc, fo, lin[c]);
+                if (c != 4 && c != 5) sw::st_off<FAR && !FUSED>(fb + gc[c] * F.sc, fo, lin[c]);
         }
     }
     if constexpr (FUSED) {
@@ -811,6 +819,7 @@ __global__ __launch_bounds__(256) void routed_sweep_kernel(const float *__restri
 
 // The rho, m, E update of one cell left by the fused routed x sweep, its x
 // fluxes read back from the flux buffer.
+template <bool FAR>
 __device__ __forceinline__ void xfix_cell(const float *__restrict__ flux, const Geom &G, const FaceBox &F,
                                           const XFuse<float> &xf, int i, int j, int k)
 {
@@ -823,24 +832,25 @@ __device__ __forceinline__ void xfix_cell(const float *__restrict__ flux, const 
     B.acc_in = xf.acc_in + G.base;
     B.acc_out = xf.acc_out + G.base;
     B.out = xf.out + G.base;
-    const uint32_t rj = i + j * (uint32_t)B.nx2, fl = (uint32_t)F.idx(i, j, k);
-    const uint32_t rel = i + j * (uint32_t)G.s[1] + k * (uint32_t)G.s[2];
+    typedef sw::ElemOff<FAR> Off;      // anywhere in the box
+    const Off rj = i + j * (Off)B.nx2, fl = (Off)F.idx(i, j, k), rel = i + j * (Off)G.s[1] + k * (Off)G.s[2];
     const int hs[5] = { 0, 1, 2, 3, 6 };
     float x[10];
 #pragma unroll
     for (int h = 0; h < 5; ++h) {
-        x[2 * h] = sw::ld32(flux + hs[h] * F.sc, fl);
-        x[2 * h + 1] = sw::ld32(flux + hs[h] * F.sc + 1, fl);
+        x[2 * h] = sw::ld_off<FAR>(flux + hs[h] * F.sc, fl);
+        x[2 * h + 1] = sw::ld_off<FAR>(flux + hs[h] * F.sc + 1, fl);
     }
     sw::FusedCell<float> fc;
-    sw::fused_tile_load(xf, B, G.sv, rj + k * (uint32_t)xf.by.s[2], rj + k * (uint32_t)xf.bz.s[2], rel, fc);
-    sw::fused_tile_store(xf, B, G, x, 2, 0, rel, fc);
+    sw::fused_tile_load<FAR>(xf, B, G.sv, rj + k * (Off)xf.by.s[2], rj + k * (Off)xf.bz.s[2], rel, fc);
+    sw::fused_tile_store<FAR>(xf, B, G, x, 2, 0, rel, fc);
 }
 
 // After the troubled pass: the cells next to the troubled x faces of queue
 // region blockIdx.y.  Each such cell is taken once: the cell right of a
 // troubled face by that face's entry, the cell left of it only if its own
 // lower face is smooth (else that face's entry takes it).
+template <bool FAR>
 __global__ __launch_bounds__(128) void xfix_queue_kernel(const float *__restrict__ flux, Geom G, FaceBox F,
                                                          XFuse<float> xf,
                                                          const unsigned long long *__restrict__ queue,
@@ -853,8 +863,8 @@ __global__ __launch_bounds__(128) void xfix_queue_kernel(const float *__restrict
         const unsigned long long q = qr[e];
         const int i = (int)(q & 0x1fffff) - 1, j = (int)((q >> 21) & 0x1fffff) - 1, k = (int)(q >> 42) - 1;
         if (j < 0 || j >= G.n[1] || k < 0 || k >= G.n[2]) continue;
-        if (i < G.n[0]) xfix_cell(flux, G, F, xf, i, j, k);
-        if (i > 0 && mask[F.idx(i - 1, j, k)] == 0) xfix_cell(flux, G, F, xf, i - 1, j, k);
+        if (i < G.n[0]) xfix_cell<FAR>(flux, G, F, xf, i, j, k);
+        if (i > 0 && mask[F.idx(i - 1, j, k)] == 0) xfix_cell<FAR>(flux, G, F, xf, i - 1, j, k);
     }
 }
 
@@ -862,7 +872,7 @@ __global__ __launch_bounds__(128) void xfix_queue_kernel(const float *__restrict
 // stages its own six cells and computes one flux; blockIdx.y is the queue
 // region, whose length the routed sweep left in qcount[region], and the
 // blocks of a region stride over it.
-template <int DIR>
+template <int DIR, bool FAR>
 __global__ __launch_bounds__(128) void troubled_kernel(const float *__restrict__ u,
                                                        float *__restrict__ flux, Geom G, FaceBox F,
                                                        Phys P,
@@ -881,12 +891,13 @@ __global__ __launch_bounds__(128) void troubled_kernel(const float *__restrict__
         const unsigned long long q = qr[e];
         int pos[3] = { (int)(q & 0x1fffff) - 1, (int)((q >> 21) & 0x1fffff) - 1, (int)(q >> 42) - 1 };
         // all loads of the six cells before the arithmetic
-        const uint32_t id = (uint32_t)(G.base + pos[0] * G.s[0] + pos[1] * G.s[1] + pos[2] * G.s[2] - 3 * G.s[N]);
+        typedef sw::ElemOff<FAR> Off;
+        const Off id = (Off)(G.base + pos[0] * G.s[0] + pos[1] * G.s[1] + pos[2] * G.s[2] - 3 * G.s[N]);
         float q6[6][8];
 #pragma unroll
         for (int j = 0; j < 6; ++j)
 #pragma unroll
-            for (int v = 0; v < 8; ++v) q6[j][v] = sw::ld32(u + cm[v] * G.sv, id + j * (uint32_t)G.s[N]);
+            for (int v = 0; v < 8; ++v) q6[j][v] = sw::ld_off<FAR>(u + cm[v] * G.sv, id + j * (Off)G.s[N]);
 #pragma unroll
         for (int j = 0; j < 6; ++j) sw::stage_values<float>(q6[j], P.gamma, sq + j * 128 + t, 128 * 6);
         float out[7];
@@ -951,6 +962,16 @@ hipError_t launch_pack_mlp(const float *th, char *pk, hipStream_t st)
     return hipGetLastError();
 }
 
+// Boxes with a variable or a face component of 2^32 bytes or more (2^30 FP32
+// elements: 1024^3, 33000^2) address the queue's faces and cells and the
+// stored fluxes by 64-bit offsets, smaller ones by 32-bit offsets: with 64 bits
+// everywhere the learned 256^3 step takes 1 % longer (11.50 ms, 11.39).
+static bool far_box(const Geom &G, const FaceBox &F)
+{
+    constexpr long reach = (1L << 32) / (long)sizeof(float);
+    return G.sv >= reach || F.sc >= reach;
+}
+
 // Grid of the routed sweep of direction dir.
 static void routed_grid(int dir, const FaceBox &F, long &na, long &nb)
 {
@@ -1004,33 +1025,29 @@ hipError_t launch_routed_sweep(int dir, const float *u, float *flux, const Geom 
     const sw::XSegArgs XA = sw::xseg_args(F);
     const sw::YZArgs YA = dir == 2 ? sw::yz_args<2, rt::YZ_PW, rt::YZ_FT>(F, sw::NXCD)
                                    : sw::yz_args<1, rt::YZ_PW, rt::YZ_FT>(F, sw::NXCD);
-    switch (dir) {
-    case 0:
-        if (fused)
-            hipLaunchKernelGGL((rt::routed_sweep_kernel<0, true>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
-                               force, nsmooth, queue, qcount, cap, mask, reuse, *xf, XA, YA, ntile);
-        else
-            hipLaunchKernelGGL((rt::routed_sweep_kernel<0, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
+    auto launch = [&](auto axis, auto far) {
+        constexpr int D = decltype(axis)::value;
+        constexpr bool FAR = decltype(far)::value;
+        if (fused) {
+            if constexpr (D == 0)
+                hipLaunchKernelGGL((rt::routed_sweep_kernel<0, true, FAR>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
+                                   force, nsmooth, queue, qcount, cap, mask, reuse, *xf, XA, YA, ntile);
+        } else {
+            hipLaunchKernelGGL((rt::routed_sweep_kernel<D, false, FAR>), grid, blk, 0, st, u, flux, G, F, P, pk, thr,
                                force, nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA, ntile);
-        if (force == 0)
-            hipLaunchKernelGGL(rt::troubled_kernel<0>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
-        if (fused && force == 0)
-            hipLaunchKernelGGL(rt::xfix_queue_kernel, qgrid, qblk, 0, st, flux, G, F, *xf, queue, qcount, cap,
-                               mask);
-        break;
-    case 1:
-        hipLaunchKernelGGL((rt::routed_sweep_kernel<1, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr, force,
-                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA, ntile);
-        if (force == 0)
-            hipLaunchKernelGGL(rt::troubled_kernel<1>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
-        break;
-    default:
-        hipLaunchKernelGGL((rt::routed_sweep_kernel<2, false>), grid, blk, 0, st, u, flux, G, F, P, pk, thr, force,
-                           nsmooth, queue, qcount, cap, mask, reuse, nofuse, XA, YA, ntile);
-        if (force == 0)
-            hipLaunchKernelGGL(rt::troubled_kernel<2>, qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
-        break;
-    }
+        }
+        if (force != 0) return;
+        hipLaunchKernelGGL((rt::troubled_kernel<D, FAR>), qgrid, qblk, 0, st, u, flux, G, F, P, queue, qcount, cap);
+        if (fused)
+            hipLaunchKernelGGL(rt::xfix_queue_kernel<FAR>, qgrid, qblk, 0, st, flux, G, F, *xf, queue, qcount, cap, mask);
+    };
+    auto launch_axis = [&](auto far) {
+        if (dir == 0) launch(std::integral_constant<int, 0>{}, far);
+        else if (dir == 1) launch(std::integral_constant<int, 1>{}, far);
+        else launch(std::integral_constant<int, 2>{}, far);
+    };
+    if (far_box(G, F) || (fused && (far_box(G, xf->by) || far_box(G, xf->bz)))) launch_axis(std::true_type{});
+    else launch_axis(std::false_type{});
     return hipGetLastError();
 }
 

@@ -38,6 +38,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace ww {
 namespace sw {
 
@@ -311,7 +313,9 @@ __device__ __forceinline__ GlobalPtr<T> uniform(T *p)
     asm volatile("" : "+s"(g));
     return g;
 }
-// Load, store of the element at a 32-bit byte offset (per lane) from a uniform base.
+// Load, store of the element at a 32-bit byte offset (per lane) from a uniform
+// base: the offset is relative to a tile or to an array under 2^32 bytes (2^30
+// FP32 elements; a variable of a 1024^3 box is larger).
 template <typename T>
 __device__ __forceinline__ T ld32(const T *base, uint32_t elem)
 {
@@ -321,6 +325,21 @@ template <typename T>
 __device__ __forceinline__ void st32(T *base, uint32_t elem, T x)
 {
     *(GlobalPtr<T>)((GlobalPtr<char>)uniform(base) + (uint32_t)(elem * (uint32_t)sizeof(T))) = x;
+}
+// The same, or (FAR) at a 64-bit offset, for elements anywhere in an array.
+template <bool FAR>
+using ElemOff = typename std::conditional<FAR, uint64_t, uint32_t>::type;
+template <bool FAR, typename T>
+__device__ __forceinline__ T ld_off(const T *base, ElemOff<FAR> elem)
+{
+    if constexpr (FAR) return uniform(base)[elem];
+    else return ld32(base, elem);
+}
+template <bool FAR, typename T>
+__device__ __forceinline__ void st_off(T *base, ElemOff<FAR> elem, T x)
+{
+    if constexpr (FAR) uniform(base)[elem] = x;
+    else st32<T>(base, elem, x);
 }
 
 // Stage one cell: its variables read from the state (cm: sweep-frame order).
@@ -791,7 +810,8 @@ template <typename T>
 struct FusedTile {
     const T *fy, *fz;          // y, z face fluxes at row 0 of the tile, x face 0's cell
     const T *u0, *acc_in;      // RK arrays at the tile's first staged cell
-                               // (the batched form: at the patch's cell (0, 0, 0))
+                               // (the batched form: at the patch's cell (0, 0, 0);
+                               // FAR: at the box's)
     T *acc_out, *out;
     int nx2;                   // n0 + 2
 };
@@ -809,9 +829,9 @@ __device__ __forceinline__ FusedTile<T> fused_tile(const XFuse<T> &xf, long ubas
     return B;
 }
 
-template <typename T>
-__device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedTile<T> &B, long sv, uint32_t ry,
-                                                uint32_t rz, uint32_t rel, FusedCell<T> &c)
+template <bool FAR = false, typename T>
+__device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedTile<T> &B, long sv, ElemOff<FAR> ry,
+                                                ElemOff<FAR> rz, ElemOff<FAR> rel, FusedCell<T> &c)
 {
     const int hs[5] = { 0, 1, 2, 3, 6 }, hv[5] = { 0, 1, 2, 3, 7 };
     const StageCoef &q = xf.c;
@@ -819,20 +839,20 @@ __device__ __forceinline__ void fused_tile_load(const XFuse<T> &xf, const FusedT
     const bool ac = (q.mode == 1 && q.s > 0) || (q.mode == 2 && q.a1 != 0.0);
 #pragma unroll
     for (int h = 0; h < 5; ++h) {
-        c.fyl[h] = ld32(B.fy + hs[h] * xf.by.sc, ry);
-        c.fyr[h] = ld32(B.fy + hs[h] * xf.by.sc + B.nx2, ry);
-        c.fzl[h] = ld32(B.fz + hs[h] * xf.bz.sc, rz);
-        c.fzr[h] = ld32(B.fz + hs[h] * xf.bz.sc + xf.bz.s[2], rz);
-        c.w0[h] = u0 ? ld32(B.u0 + hv[h] * sv, rel) : T(0);
-        c.w1[h] = ac ? ld32(B.acc_in + hv[h] * sv, rel) : T(0);
+        c.fyl[h] = ld_off<FAR>(B.fy + hs[h] * xf.by.sc, ry);
+        c.fyr[h] = ld_off<FAR>(B.fy + hs[h] * xf.by.sc + B.nx2, ry);
+        c.fzl[h] = ld_off<FAR>(B.fz + hs[h] * xf.bz.sc, rz);
+        c.fzr[h] = ld_off<FAR>(B.fz + hs[h] * xf.bz.sc + xf.bz.s[2], rz);
+        c.w0[h] = u0 ? ld_off<FAR>(B.u0 + hv[h] * sv, rel) : T(0);
+        c.w1[h] = ac ? ld_off<FAR>(B.acc_in + hv[h] * sv, rel) : T(0);
     }
 }
 
 // The RK combination of that cell from its x fluxes and the loaded values (the
 // update kernel's expressions and order, x, y, z: identical results).
-template <typename T>
+template <bool FAR = false, typename T>
 __device__ __forceinline__ void fused_tile_store(const XFuse<T> &xf, const FusedTile<T> &B, const Geom &G,
-                                                 const T *hx, int nh, int t, uint32_t rel, const FusedCell<T> &c)
+                                                 const T *hx, int nh, int t, ElemOff<FAR> rel, const FusedCell<T> &c)
 {
     const int hv[5] = { 0, 1, 2, 3, 7 };
     const T idx = T(G.idl[0]), idy = T(G.idl[1]), idz = T(G.idl[2]);
@@ -846,17 +866,17 @@ __device__ __forceinline__ void fused_tile_store(const XFuse<T> &xf, const Fused
         L -= (c.fzr[h] - c.fzl[h]) * idz;
         T *const out = B.out + hv[h] * G.sv, *const acc = B.acc_out + hv[h] * G.sv;
         if (q.mode == 0) {
-            st32<T>(out, rel, L);
+            st_off<FAR, T>(out, rel, L);
         } else if (q.mode == 2) {
-            st32<T>(out, rel, q.a1 != 0.0 ? a0 * c.w0[h] + a1 * c.w1[h] + cdt * L : a0 * c.w0[h] + cdt * L);
+            st_off<FAR, T>(out, rel, q.a1 != 0.0 ? a0 * c.w0[h] + a1 * c.w1[h] + cdt * L : a0 * c.w0[h] + cdt * L);
         } else if (q.s == 0) {
-            st32<T>(acc, rel, c.w0[h] + bdt * L);
-            st32<T>(out, rel, c.w0[h] + cdt * L);
+            st_off<FAR, T>(acc, rel, c.w0[h] + bdt * L);
+            st_off<FAR, T>(out, rel, c.w0[h] + cdt * L);
         } else if (q.s < 3) {
-            st32<T>(acc, rel, c.w1[h] + bdt * L);
-            st32<T>(out, rel, c.w0[h] + cdt * L);
+            st_off<FAR, T>(acc, rel, c.w1[h] + bdt * L);
+            st_off<FAR, T>(out, rel, c.w0[h] + cdt * L);
         } else {
-            st32<T>(out, rel, c.w1[h] + cdt * L);
+            st_off<FAR, T>(out, rel, c.w1[h] + cdt * L);
         }
     }
 }
