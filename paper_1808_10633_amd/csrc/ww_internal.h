@@ -127,23 +127,31 @@ inline bool has_user_face(const Geom &G, const int bc[6])
 // The sweeps of a small box in one launch, ghost cells taken from their
 // interior images; with ghosts set the ghost zones of u are filled too, by the
 // same launch.  No user faces, JS weights, per-stencil LF speeds.
-// A box is small up to SMALL_TILES tiles of 256 faces, 3-D boxes without the
-// fused x sweep (rows under 86 faces) up to twice as many.  Steps with one
-// launch and with three (both with an update that was slower than now): FP64 64^3 (3.3 k tiles) 356 us, 495; FP32 254, 510;
-// FP64 80^3 (6.4 k) 763, 822; FP32 484, 640; 900^2 (6.4 k) 680, 635; 96^3
-// (11 k; fused x sweep) 1390, 950.
+// A box is small up to SMALL_TILES tiles of 256 faces; 3-D boxes without the
+// fused x sweep (rows under 86 faces) up to twice as many; 1-D boxes along x,
+// which have one sweep and six ghost cells to save a launch for, up to an
+// eighth.  Microseconds a step with one launch / with separate ones, FP64, FP32:
+//   1-D       2^16 cells (0.26 k tiles) 66 / 70, 62 / 60; 2^18 (1.0 k) 142 / 139,
+//             109 / 100; 10^6 (3.9 k) 444 / 420, 329 / 284
+//   2-D       600^2 (2.9 k) 302 / 309, 239 / 241; 760^2 (4.6 k) 440 / 434, 356 / 341;
+//             1000^2 (7.9 k) 760 / 740, 585 / 511
+//   3-D       64^3 (3.3 k) 323 / 477, 258 / 496; 84^3 (7.4 k) 699 / 770, 537 / 576
+//   3-D fused 88x50x50 (2.9 k) 298 / 316, 236 / 286; 88x60x60 (4.1 k) 398 / 400,
+//             318 / 323; 100x64x64 (5.2 k) 494 / 460, 390 / 367; 96^3 (11 k) 1049 / 948, 790 / 716
 constexpr long SMALL_TILES = 4096;
 long small_sweep_tiles(const Geom &G, const FaceBox F[3]);
-int sweep_x_fused_min_faces();
 template <typename T>
 hipError_t launch_small_sweeps(T *u, T *const flux[3], const Geom &G, const FaceBox F[3], const Phys &P,
                                const int bc[6], bool ghosts, hipStream_t st);
+inline long small_limit(const Geom &G, const FaceBox F[3])
+{
+    if (G.act[0] && !G.act[1] && !G.act[2]) return SMALL_TILES / 8;
+    return G.act[0] && G.act[1] && G.act[2] && F[0].cnt[0] < sweep_x_fused_min_faces() ? 2 * SMALL_TILES : SMALL_TILES;
+}
 inline bool small_box(const wombat_weno_config &c, const Geom &G, const FaceBox F[3])
 {
     return c.slab_planes == 0 && c.b_storage == WW_B_CELL && c.weights == WW_WEIGHTS_JS &&
-           c.lf_speed == WW_LF_LOCAL && !has_user_face(G, c.bc) &&
-           small_sweep_tiles(G, F) <=
-               (G.act[0] && G.act[1] && G.act[2] && F[0].cnt[0] < sweep_x_fused_min_faces() ? 2 : 1) * SMALL_TILES;
+           c.lf_speed == WW_LF_LOCAL && !has_user_face(G, c.bc) && small_sweep_tiles(G, F) <= small_limit(G, F);
 }
 
 // CFL reduction: partial maxima / flags to scratch, then dt to d_dt and the
