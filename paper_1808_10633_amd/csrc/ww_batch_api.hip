@@ -289,7 +289,7 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
     DevGuard dg(cfg->device);
     if (!dg.ok) { delete b; return bfail(nullptr, WW_ERR_HIP, "hipSetDevice failed"); }
     // arena layout (each patch aligned to 64 elements) and patch table
-    long off = 0, slot = 0;
+    long off = 0, slot = 0, largest = 0;               // largest: cells of a patch
     std::vector<long> felems(npatch);
     b->hpd.resize(npatch);
     b->soff.resize(npatch);
@@ -309,6 +309,7 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
         D.nf = ww::FastDiv(n[0] + 1);
         D.n1f = ww::FastDiv(n[1] + 2);
         D.nxp = ww::FastDiv(n[0] + 6);
+        largest = std::max(largest, (long)n[0] * n[1] * n[2]);
         b->soff[p] = off;
         off += (8 * G.sv + 63) / 64 * 64;
         felems[p] = ((long)ww::NFC * (F[0].sc + F[1].sc + F[2].sc) + 63) / 64 * 64;
@@ -367,7 +368,17 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
         delete b;
         return bfail(nullptr, WW_ERR_HIP, "batch set-up failed");
     }
-    int rc = set_shape(b, 4, 2);
+    // Until it is tuned, a batch runs 12 faces per tile at two blocks per CU (one
+    // fits in FP64).  The variants of 4 (FP64) and 8 faces (FP32) spill registers
+    // for their second and third block and gain where the patches are many and
+    // small: at least four per CU, of up to 16^3 cells.  us a step, 4 x 2 / 12 x 1
+    // in FP64, 8 x 3 / 12 x 2 in FP32: 16384 of 5^3 8590 / 10598, 5168 / 6163; 3000
+    // of 4-12 3023 / 3447, 1846 / 2065; 1100 of 16^3 9395 / 9511, 5572 / 5676; 2048
+    // of 18^3 20368 / 20164, 11452 / 11653; 512 of 24^3 11223 / 11254, 9603 / 7026;
+    // 256 of 24^3 9953 / 5673, 4623 / 4533; 64 of 32^3 4479 / 3846, 2888 / 2671; one
+    // of 4^3 179 / 146, 162 / 140.
+    const bool f64 = cfg->precision == WW_FP64, many_small = npatch >= 4 * ncu && largest <= 16 * 16 * 16;
+    int rc = many_small ? set_shape(b, f64 ? 4 : 8, f64 ? 2 : 3) : set_shape(b, 12, 2);
     if (rc) {
         std::string m = b->err;
         release(b);
