@@ -354,8 +354,8 @@ int wombat_weno_batch_shape(const wombat_weno_batch_t *b, int *ft, int *blocks_p
                             int *nblocks);
 
 /* Autotuner: if cache_path (a text file, one JSON object per line; may be
- * NULL) holds an entry for this patch set, precision and architecture, use
- * it; otherwise time every launch shape (faces per tile 4, 8, 12 or 16 x
+ * NULL) holds an entry for this patch set, precision, architecture, number of
+ * CUs and version of the kernels, use it; otherwise time every launch shape (faces per tile 4, 8, 12 or 16 x
  * 1..4 blocks per CU within the occupancy limit) by the median of five
  * launches of the second RK4 stage (its most expensive form), run on a copy
  * of d_arena in the batch's own work arenas with zero RK weights (so the

@@ -217,13 +217,19 @@ void release(wombat_weno_batch_t *b)
     for (int i = 0; i < 2; ++i) if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
 }
 
+// Raised with every change of the stage kernels or the plan that moves the best
+// shapes: entries of other versions are left in the file and not taken (12 faces
+// at one block per CU, best for 1024 patches of 16-64 cells while each was one
+// block's work, takes 61 ms a step with split patches, 12 at two blocks 43).
+constexpr int TUNE_VERSION = 2;
+
 std::string tune_key(const wombat_weno_batch_t *b)
 {
     unsigned long long h = 1469598103934665603ULL;
     for (int v : b->dims) { h ^= (unsigned)v; h *= 1099511628211ULL; }
     char buf[160];
-    snprintf(buf, sizeof buf, "gfx950|%s|%d|%016llx", b->cfg.precision == WW_FP64 ? "fp64" : "fp32",
-             b->npatch, h);
+    snprintf(buf, sizeof buf, "gfx950|v%d|%d CUs|%s|%d|%016llx", TUNE_VERSION, b->ncu,
+             b->cfg.precision == WW_FP64 ? "fp64" : "fp32", b->npatch, h);
     return buf;
 }
 

@@ -51,3 +51,26 @@ def test_default_and_every_shape(name, precision, tmp_path):
     for shape, a in got[1:]:
         assert torch.equal(a, got[0][1]), shape
     b.close()
+
+
+def test_cache_entries_of_earlier_kernels_are_not_taken(tmp_path):
+    # a key without the kernels' version names a shape that was best for others
+    dims = [(6, 5, 4)] * 3
+    h = 1469598103934665603
+    for d in dims:
+        for v in d:
+            h = ((h ^ v) * 1099511628211) % 2 ** 64
+    old = {"key": f"gfx950|fp32|{len(dims)}|{h:016x}", "ft": 4, "bpc": 1, "ms": 0.001}
+    cache = tmp_path / "tune.jsonl"
+    cache.write_text(json.dumps(old) + "\n")
+    b = W.Batch(dims, 1.0 / 64)
+    ar = b.new_arena()
+    for p, d in enumerate(dims):
+        b.view(ar, p).copy_(torch.from_numpy(random_smooth(*d, seed=p, amp=0.1)))
+    say("[batch shapes] cache of an earlier version")
+    assert b.autotune(ar, str(cache)) > 0.0
+    lines = [json.loads(x) for x in cache.read_text().splitlines()]
+    assert len(lines) == 2 and lines[0] == old and lines[1]["key"] != old["key"]
+    assert b.autotune(ar, str(cache)) == -1.0
+    assert b.shape()[:2] == (lines[1]["ft"], lines[1]["bpc"])
+    b.close()
