@@ -487,7 +487,8 @@ __device__ __forceinline__ void update_b_patch(const T *fx, const T *fy, const T
 // A patch's geometry and its face buffers, formed anew for each phase
 // (the patch number is made opaque): kept through all phases, the scalars of
 // one stood in the way of the next, with a thousand moves of spilled scalar
-// registers.
+// registers.  232-344 are spilled (to lanes of VGPRs) all the same, 57-88 with
+// whole patches only: the items' ranges and waits came on top.
 template <typename T>
 struct Patch {
     PatchDesc D;
@@ -670,7 +671,13 @@ __device__ __forceinline__ void batch_stage(const BatchArgs<T> &a)
 
 // Waves per SIMD: FP32 three up to 8 faces per tile, as the 48 KB of LDS
 // allow, else two; FP64 two at 4 faces per tile (70 KB), else the LDS tile
-// leaves room for one block per CU anyway.
+// leaves room for one block per CU anyway.  The registers do not suffice for it:
+// FP32 spills 18 VGPRs (76 B a lane) at 4 and 8 faces, FP64 51 (164 B) at 4; the
+// other variants spill none (187-191 VGPRs; FP64 294-298 with AGPRs).  Held to one
+// wave fewer these spill none either and are faster a block; more blocks win
+// where the patches are many and small.  ms a step, spilled at the higher count
+// / unspilled at the lower: 16384 patches of 5^3 FP32 5.17 / 6.10, FP64 8.59 / 10.52;
+// 1024 of 16-64 FP32 46.1 / 43.9 (43.1 at 12 or 16 faces).
 template <int FT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FT <= 8 ? 3 : 2))) void batch_stage_f32(BatchArgs<float> a)
 {

@@ -327,10 +327,10 @@ int wombat_weno_batch_init(const wombat_weno_config *cfg, int npatch, const int3
         ncu = 256;
     b->ncu = ncu;
     b->maxblocks = 4 * ncu;
-    // For four blocks per CU (FP32) or two (FP64): FP32 runs two or three, but
-    // the finer plan was 3-6 % faster on uneven patches (for two blocks per CU
-    // 7-12 % slower), FP64 one, and a plan for four 6 % slower on 512 patches of
-    // 16-32.  No more face scratch than the largest patch's per block.  Split x
+    // For four blocks per CU (FP32) or two (FP64), by trial: FP32 runs two or
+    // three, but the finer plan was 3-6 % faster on uneven patches (for two blocks
+    // per CU 7-12 % slower), FP64 one, and a plan for four 6 % slower on 512 patches
+    // of 16-32.  No more face scratch than the largest patch's per block.  Split x
     // sweeps take the flattened tiles.
     try {
         b->plan = ww::batch_plan(

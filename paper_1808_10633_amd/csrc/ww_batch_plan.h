@@ -74,7 +74,8 @@ struct BatchPlan {
 // Costs are in faces swept by one block.  An item's wait, device-wide fences
 // and count take a block as long as about 800 faces (1100 patches of 16^3,
 // FP32: 1.42 ms a stage as whole patches, 1.58 ms as 12100 items).  No item is
-// made smaller than 1024 faces.
+// made smaller than 1024 faces.  These costs, and the margins of batch_plan, come
+// from FP32 sets; FP64 uses them too.
 constexpr double ITEM_OVERHEAD = 800.0, ITEM_MIN_FACES = 1024.0;
 
 // Plan for `workers` resident blocks.  elems(p): face-flux elements of patch

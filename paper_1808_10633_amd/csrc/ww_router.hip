@@ -613,7 +613,11 @@ __global__ __launch_bounds__(64) void router_sample_kernel(const T *__restrict__
 // applies the rho, m, E update (RK stage xf.c) to every cell whose two x faces
 // are both smooth, with their fluxes from LDS (the fused x sweep's tail); the
 // cells next to troubled faces are left to xfix_queue_kernel, and only the
-// faces it reads get their rho, m, E fluxes stored.  Both kinds of sweep are
+// faces it reads get their rho, m, E fluxes stored.  Where the network is
+// evaluated, both tiles judge the face that they share, each for its own cell,
+// and the later one stores, counts and queues it: the cells come out right only
+// because both get the same bits (a face's features and its column of the
+// matrix products do not depend on its place in the tile).  Both kinds of sweep are
 // bound by memory: 256^3, per RK stage, y 460 -> 373 us, z 433 -> 357, x with its
 // cells 812 -> 636 (column order, overlapping tiles, faces nobody reads left out).
 // FAR: see far_box (fused x tiles store at offsets within the tile in both).

@@ -976,6 +976,7 @@ __device__ __forceinline__ bool column_tile(const YZArgs &Y, uint32_t &ta, uint3
 // within a tile are 32-bit: they stay within one variable (or face
 // component), and a context keeps at least three states of eight variables,
 // so that one variable holds at most 288 GB / 96 B = 3.0e9 < 2^32 elements.
+// (Their byte offsets can pass 2^32: they index by element, not by ld32, st32.)
 template <int DIR, int PW, int FT>
 struct YZTile {
     static constexpr int N = DIR, A = 0, B = DIR == 1 ? 2 : 1;
