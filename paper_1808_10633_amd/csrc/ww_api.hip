@@ -398,7 +398,7 @@ int operator_t(wombat_weno_t *c, T *us, const T *u0, const T *acc_in, T *acc_out
     if (c->router && c->router_force > 0) {
         // all interfaces full: the plain sweep (same face arithmetic); no smooth ones
         const long tot = c->nsm_blocks[0] + c->nsm_blocks[1] + c->nsm_blocks[2];
-        WW_CHECK(c, hipMemsetAsync(c->nsmooth, 0, sizeof(int32_t) * (tot > 0 ? tot : 1), c->st));
+        WW_CHECK(c, ww::launch_clear(c->nsmooth, tot > 0 ? tot : 1, c->st));
     }
     // with the fused x sweep the sweeps run y, z, x: the x sweep (plain or
     // routed) differences all three directions' rho, m, E fluxes and applies

@@ -18,6 +18,7 @@ hipError_t launch_router_sample(const T *u, const Geom &G, const Phys &P, const 
                                 int n, float *X, float *dev, float *ex, hipStream_t st);
 constexpr int MLP_PACKED_BYTES = 10 * 64 * 8 + 25 * 64 * 4;
 hipError_t launch_pack_mlp(const float *th, char *pk, hipStream_t st);
+hipError_t launch_clear(int32_t *p, long n, hipStream_t st);
 long routed_sweep_blocks(int dir, const FaceBox &F);
 // Troubled-queue entries the routed sweep of direction dir may need: 64
 // regions of ceil(blocks / 64) * 256 entries; qcount holds 64 counters.

@@ -910,9 +910,23 @@ __global__ __launch_bounds__(128) void troubled_kernel(const float *__restrict__
     }
 }
 
+__global__ __launch_bounds__(256) void clear_kernel(int32_t *__restrict__ p, long n)
+{
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
 }  // namespace rt
 
 // ---------------------------------------------------------------- launchers
+
+// Counters cleared by a kernel: memset nodes of a captured graph have given
+// wrong results on replays after the first.
+hipError_t launch_clear(int32_t *p, long n, hipStream_t st)
+{
+    hipLaunchKernelGGL(rt::clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n);
+    return hipGetLastError();
+}
 
 hipError_t launch_mlp_infer(const float *th, const float *X, int n, float *logit, hipStream_t st)
 {
@@ -1014,7 +1028,7 @@ hipError_t launch_routed_sweep(int dir, const float *u, float *flux, const Geom 
     const bool fused = xf != nullptr;
     if (fused && (dir != 0 || F.cnt[0] < sw::XSEG_MIN || !(G.act[0] && G.act[1] && G.act[2])))
         return hipErrorInvalidValue;
-    hipError_t e = hipMemsetAsync(qcount, 0, sizeof(int32_t) * rt::QREG, st);
+    hipError_t e = launch_clear(qcount, rt::QREG, st);
     if (e != hipSuccess) return e;
     long na, nb;
     routed_grid(dir, F, na, nb);
