@@ -33,20 +33,20 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3     # MI355X FP32 vector peak (packed)
 # + ww_update_dev.h (update).
 MEASURED_TRAFFIC = {
     # y sweep (the VALU roofline's kernel) and the fused x sweep
-    ("c5d79eb5d3d34c79", "fp64", 512): {"read": 9.403e9, "write": 9.044e9,
+    ("cf12dbd6fcbfa342", "fp64", 512): {"read": 9.422e9, "write": 9.034e9,
                                       "profile": "profiles/fp64_512_turbulence_trace_and_hbm.md"},
-    ("c5d79eb5d3d34c79", "fp32", 512): {"read": 4.781e9, "write": 4.72e9,
+    ("cf12dbd6fcbfa342", "fp32", 512): {"read": 4.783e9, "write": 4.719e9,
                                       "profile": "profiles/fp32_512_turbulence_trace_and_hbm.md"},
-    ("c5d79eb5d3d34c79", "fp64_xfused", 512): {"read": 31.35e9, "write": 11.64e9,
+    ("cf12dbd6fcbfa342", "fp64_xfused", 512): {"read": 31.41e9, "write": 11.64e9,
                                              "profile": "profiles/fp64_512_turbulence_trace_and_hbm.md"},
-    ("c5d79eb5d3d34c79", "fp32_xfused", 512): {"read": 15.33e9, "write": 5.837e9,
+    ("cf12dbd6fcbfa342", "fp32_xfused", 512): {"read": 15.33e9, "write": 5.837e9,
                                              "profile": "profiles/fp32_512_turbulence_trace_and_hbm.md"},
 }
 MEASURED_UPDATE_TRAFFIC = {
     # B-only update, mean over the profiled launches (RK stage forms and L(U))
-    ("e86924a598e0365e", "fp64", 512): {"read": 11.9e9, "write": 5.582e9,
+    ("e86924a598e0365e", "fp64", 512): {"read": 11.88e9, "write": 5.573e9,
                                       "profile": "profiles/fp64_512_turbulence_trace_and_hbm.md"},
-    ("e86924a598e0365e", "fp32", 512): {"read": 5.745e9, "write": 2.818e9,
+    ("e86924a598e0365e", "fp32", 512): {"read": 5.744e9, "write": 2.819e9,
                                       "profile": "profiles/fp32_512_turbulence_trace_and_hbm.md"},
 }
 
@@ -56,10 +56,10 @@ MEASURED_UPDATE_TRAFFIC = {
 # ww_batch.hip, ww_batch.h, ww_batch_plan.h, ww_sweep_dev.h, ww_update_dev.h,
 # ww_index.h, ww_internal.h).
 MEASURED_BATCH_TRAFFIC = {
-    ("f33559fb491041f7", 4096, 4): (86.56e9, 32.22e9),
-    ("f33559fb491041f7", 4096, 8): (103.59e9, 30.64e9),
-    ("f33559fb491041f7", 4096, 12): (86.53e9, 32.08e9),
-    ("f33559fb491041f7", 4096, 16): (85.75e9, 32.04e9),
+    ("0a2bd979aaa0b11b", 4096, 4): (87.10e9, 32.23e9),
+    ("0a2bd979aaa0b11b", 4096, 8): (103.34e9, 30.65e9),
+    ("0a2bd979aaa0b11b", 4096, 12): (85.95e9, 32.06e9),
+    ("0a2bd979aaa0b11b", 4096, 16): (85.68e9, 32.03e9),
 }
 BATCH_TRAFFIC_PROFILE = "profiles/batched_4096_patches_hbm.md"
 
